@@ -50,8 +50,7 @@ Geom make_geom(const wt_frame_desc& d, bool backward) {
   g.AL = (d.channels == 3) ? 6 : 4;
   g.dtype = d.coeff_dtype;
   // Largest power-of-two tile whose LDS working set fits one compute unit. Forward: FP64 endpoint masses
-  // (M + 1 per channel) and three FP64 colour sums, or, where the tile would hold more pixel/channels than a
-  // workgroup has threads or M > 32, FP64 coefficient sums plus FP64 accumulations. Backward: FP32 cells,
+  // (M + 1 per channel) and three FP64 colour sums, or, for M > 32, FP64 coefficient sums plus FP64 accumulations. Backward: FP32 cells,
   // FP64 cell adjoints and per-pixel gradient data.
   auto tile_for = [](uint32_t per_px) {
     const uint32_t px = std::max<uint32_t>(1, kLdsBytes / per_px);
@@ -71,15 +70,8 @@ Geom make_geom(const wt_frame_desc& d, bool backward) {
     px = std::min<uint32_t>(tile_for(8 * g.C * (g.M + 1) + 24 + 4 * g.C * g.M), floor_pow2(kTileThreads / g.C));
     g.ep = 1;
   } else {
-    px = tile_for(8 * g.C * (g.M + 1) + 24 + bpx);
-    // packed three-channel storage is converted on the endpoint path only: cap the tile so that every
-    // pixel/channel has a thread (rank <= 4 is checked by the API)
-    if (d.coeff_dtype == WT_E5B9G9R9) px = std::min<uint32_t>(px, floor_pow2(kTileThreads / g.C));
-    if (g.M <= 32 && px * g.C <= kTileThreads) {
-      g.ep = 1;
-    } else {
-      px = tile_for(8 * (g.C * g.M + g.AL) + bpx);
-    }
+    g.ep = g.M <= 32 ? 1 : 0;
+    px = g.ep ? tile_for(8 * g.C * (g.M + 1) + 24 + bpx) : tile_for(8 * (g.C * g.M + g.AL) + bpx);
   }
   uint32_t e = 0;
   while ((1u << e) < px) ++e;
@@ -721,15 +713,19 @@ __device__ __forceinline__ bool has_nan(const ChunkRegs<C, PER>& r, uint32_t k) 
   return bad;
 }
 
-// Record dword j of fragment k (tile-local pixel `local`, stream index `src`).
-// Forward binning stores each alpha as its absorbance step (binned_absorbance); records binned for the gradient
-// keep alpha.
-template <int C, int PER>
-__device__ __forceinline__ void to_absorbance(ChunkRegs<C, PER>& r) {
+// A record's words after the pixel and depth (alphas `a`, colours `c`) from the fragment's to the forward binning's: each
+// alpha as its absorbance step (binned_absorbance) and the colour times the clamped alpha, the two forms in which the
+// tile kernels use them. Records binned for the gradient keep alpha and the plain colour.
+template <int C>
+__device__ __forceinline__ void to_forward(uint32_t* a, uint32_t* c) {
 #pragma unroll
-  for (int i = 0; i < C * PER; ++i) r.a[i] = binned_absorbance(r.a[i]);
+  for (int q = 0; q < 3; ++q)
+    c[q] = __float_as_uint(__uint_as_float(c[q]) * alpha_clamped(__uint_as_float(a[C == 1 ? 0 : q])));
+#pragma unroll
+  for (int q = 0; q < C; ++q) a[q] = __float_as_uint(binned_absorbance(__uint_as_float(a[q])));
 }
 
+// Record dword j of fragment k (tile-local pixel `local`, stream index `src`), with the fragment's own alpha and colour.
 template <int C, int PER>
 __device__ __forceinline__ uint32_t record_word(const ChunkRegs<C, PER>& r, uint32_t k, uint32_t local, uint32_t src,
                                                 uint32_t j) {
@@ -864,7 +860,6 @@ __global__ __launch_bounds__(THREADS, PER == 4 ? 8 : (THREADS == 512 ? 4 : 1)) v
     if (threadIdx.x == 0) scatter_refuse(hdr);
     return;
   }
-  if constexpr (!IDX) to_absorbance<C, PER>(r);
   __syncthreads();
   uint32_t tile[PER], rank[PER], local[PER];
   uint32_t nan_count = 0, mine = 0;
@@ -929,6 +924,9 @@ __global__ __launch_bounds__(THREADS, PER == 4 ? 8 : (THREADS == 512 ? 4 : 1)) v
       lds_get<HW>(sh + (size_t)sidx * HW, hw);
       lds_get<DT>(st + (size_t)sidx * DT, tw);
       const uint64_t slot = (uint32_t)(gb[hw[DH]] + r0 + sidx);
+      // converted here, where every lane has a record and little else is live (before the ranking, the products and
+      // logarithms cost the 64-register kernel spills: smoke scatter 1.66 -> 2.6 ms)
+      if constexpr (!IDX) to_forward<C>(hw + 2, tw);
       Words<DH> h;
 #pragma unroll
       for (uint32_t j = 0; j < DH; ++j) h.w[j] = hw[j];
@@ -962,7 +960,6 @@ __global__ __launch_bounds__(THREADS) void k_scatter_global(wt_fragments f, Geom
   ChunkRegs<C, kPer> r;
   const uint32_t i0 = threadIdx.x * kPer;
   load_chunk<C, kPer>(f, base, i0, n, vec, r);
-  if constexpr (!IDX) to_absorbance<C, kPer>(r);
   uint32_t nan_count = 0;
 #pragma unroll
   for (uint32_t k = 0; k < kPer; ++k) {
@@ -975,10 +972,14 @@ __global__ __launch_bounds__(THREADS) void k_scatter_global(wt_fragments f, Geom
       scatter_refuse(hdr);
       continue;
     }
+    uint32_t w[DH + DT];
 #pragma unroll
-    for (uint32_t j = 0; j < DH; ++j) head[pos * DH + j] = record_word<C, kPer>(r, k, local, base + i0 + k, j);
+    for (uint32_t j = 0; j < DH + DT; ++j) w[j] = record_word<C, kPer>(r, k, local, base + i0 + k, j);
+    if constexpr (!IDX) to_forward<C>(w + 2, w + DH);
 #pragma unroll
-    for (uint32_t j = 0; j < DT; ++j) tail[pos * DT + j] = record_word<C, kPer>(r, k, local, base + i0 + k, DH + j);
+    for (uint32_t j = 0; j < DH; ++j) head[pos * DH + j] = w[j];
+#pragma unroll
+    for (uint32_t j = 0; j < DT; ++j) tail[pos * DT + j] = w[DH + j];
   }
   nan_count = wave_sum(nan_count);
   if ((threadIdx.x & 63) == 0 && nan_count) atomicAdd(&hdr->dropped, (unsigned long long)nan_count);
@@ -1012,16 +1013,17 @@ __global__ void k_scatter_serial(wt_fragments f, Geom g, uint32_t* __restrict__ 
     *cur = pos + 1;
     const float x = f.depth[i];
     bool bad = isnan(x);
-    uint32_t* h = head + (uint64_t)pos * DH;
-    h[0] = local;
-    h[1] = __float_as_uint(x);
+    uint32_t w[DH + 3] = {local, __float_as_uint(x)};
     for (int c = 0; c < C; ++c) {
-      const float al = f.alpha[i * C + c];
-      bad |= isnan(al);
-      h[2 + c] = __float_as_uint(IDX ? al : binned_absorbance(al));
+      bad |= isnan(f.alpha[i * C + c]);
+      w[2 + c] = __float_as_uint(f.alpha[i * C + c]);
     }
+    for (int q = 0; q < 3; ++q) w[DH + q] = __float_as_uint(f.rgb[i * 3 + q]);
+    if (!IDX) to_forward<C>(w + 2, w + DH);
+    uint32_t* h = head + (uint64_t)pos * DH;
+    for (uint32_t q = 0; q < DH; ++q) h[q] = w[q];
     uint32_t* t = tail + (uint64_t)pos * DT;
-    for (int q = 0; q < 3; ++q) t[q] = __float_as_uint(f.rgb[i * 3 + q]);
+    for (uint32_t q = 0; q < 3; ++q) t[q] = w[DH + q];
     if (IDX) t[3] = (uint32_t)i;
     nan_count += bad ? 1 : 0;
   }

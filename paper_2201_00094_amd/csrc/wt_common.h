@@ -33,7 +33,6 @@ __device__ __forceinline__ __half narrow_d<__half>(double v) { return __ushort_a
 template <>
 __device__ __forceinline__ bf16_t narrow_d<bf16_t>(double v) { return bf16_t{f64_to_bf16_bits(v)}; }
 
-
 // E5B9G9R9 coefficient storage (section 2.1): one 32-bit word per coefficient index holds the magnitudes of the
 // three channels' coefficients, a shared 5-bit exponent (bias 15) in bits 27-31 and 9-bit mantissas without an
 // implicit one, B in bits 18-26, G in 9-17, R in 0-8; value = mantissa * 2^(e - 24).
@@ -166,8 +165,7 @@ __device__ __forceinline__ float absorbance(float al_clamped) { return neg_log1m
 
 // What a forward binning stores for each alpha of a fragment: the absorbance step of the clamped alpha, computed
 // once where the binning waits on memory rather than in every pass of the tile kernels; NaN stays NaN (the tile
-// kernels skip such fragments). alpha_of gives the clamped alpha back, 1 - exp(-a), within a few ulp.
+// kernels skip such fragments).
 __device__ __forceinline__ float binned_absorbance(float al) { return isnan(al) ? al : absorbance(alpha_clamped(al)); }
-__device__ __forceinline__ float alpha_of(float a) { return -expm1f(-a); }
 
 }  // namespace wt

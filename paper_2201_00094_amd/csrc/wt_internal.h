@@ -95,11 +95,10 @@ __host__ __device__ inline uint32_t f64_to_f32_odd_bits(double v) {
   uint32_t u;
   __builtin_memcpy(&u, &f, 4);
   const double b = (double)f;
-  if (b != v) {
-    if (__builtin_fabs(b) > __builtin_fabs(v)) u -= 1u;  // rounded away from zero: one place back toward it
-    u |= 1u;
-  }
-  return u;
+  // rounded away from zero: one place back toward it (selects: a branch per coefficient would split the conversion of
+  // a column into dozens of blocks, across which its masses stay live)
+  const uint32_t toward = __builtin_fabs(b) > __builtin_fabs(v) ? u - 1u : u;
+  return b != v ? toward | 1u : u;
 }
 
 // FP64 -> FP16 bit pattern, rounded once to nearest even: round to odd in FP32, then the FP32 -> FP16 conversion
@@ -118,8 +117,8 @@ __host__ __device__ inline uint16_t f64_to_f16_bits(double v) {
 // bit pattern (a carry out of the mantissa moves into the exponent, up to infinity); NaN stays a quiet NaN.
 __host__ __device__ inline uint16_t f64_to_bf16_bits(double v) {
   const uint32_t u = f64_to_f32_odd_bits(v);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
-  return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
+  const uint32_t rounded = u + 0x7fffu + ((u >> 16) & 1u);
+  return (uint16_t)(((u & 0x7fffffffu) > 0x7f800000u ? u | 0x400000u : rounded) >> 16);
 }
 
 // Frame geometry as the kernels see it.
@@ -139,7 +138,7 @@ struct Geom {
   uint32_t AW;           // accum floats per pixel in global memory: 4 (C = 1) or 8 (C = 3)
   uint32_t AL;           // accumulation floats per pixel in LDS: 4 (C = 1) or 6 (C = 3)
   uint32_t dtype;        // wt_dtype of the coefficient storage
-  uint32_t ep;           // 1: the build accumulates endpoint masses (M <= 32, one pixel/channel per thread)
+  uint32_t ep;           // 1: the build accumulates endpoint masses (M <= 32)
   uint32_t tight;        // 1: per-pixel depth bounds (WT_TIGHT_DEPTH); the tile kernels keep them in LDS
   uint32_t temporal;     // 1: tiles sized for the one-pass render against the previous frame (WT_TEMPORAL)
   uint32_t serial;       // 1: WT_DETERMINISTIC (stream-order binning by one thread, one thread per tile's records)
@@ -151,7 +150,8 @@ struct Geom {
 // Binned fragment records, two arrays of structures in the same order:
 //   head [cap][2 + C]: tile-local pixel index, depth, and per channel the absorbance -ln(1 - alpha) of the clamped
 //                      alpha (forward binning) or alpha itself (binning for the gradient)   (all the build reads)
-//   tail [cap][3 or 4]: rgb[3], then the stream index when recorded
+//   tail [cap][3 or 4]: rgb[3], times the clamped alpha (forward binning) or plain (binning for the gradient), then
+//                      the stream index when recorded
 constexpr uint32_t head_dwords(uint32_t C) { return 2 + C; }
 constexpr uint32_t tail_dwords(bool with_index) { return 3 + (with_index ? 1 : 0); }
 constexpr uint32_t record_dwords(uint32_t C, bool with_index) { return head_dwords(C) + tail_dwords(with_index); }
