@@ -194,7 +194,7 @@ wt_status wt_render(const wt_frame_desc* desc, const wt_fragments* frags, const 
  *   Limit: a frame whose workspace (wt_workspace_bytes(desc, frags->count) without the gradient's layout) exceeds
  *   WT_SCRATCH_BYTES is refused with WT_ERR_RANGE before anything is enqueued: about 9.5 million fragments at one
  *   channel (28 bytes per binned fragment) and 7.4 million at three (36 bytes), half as many for frames of more than
- *   4096 screen tiles (binned in two levels, each with its own copy).
+ *   8192 screen tiles (binned in two levels, each with its own copy).
  *   Sharing: every call on one GPU uses that GPU's one array, which keeps the last call's contents (each call clears
  *   what it needs zeroed with its own fill kernels). Calls that overlap in time on one GPU (on different streams, or
  *   from different threads without ordering) race on the array: the caller serialises them, for example on one

@@ -31,10 +31,78 @@
 
 namespace wt {
 
-static uint32_t floor_pow2(uint32_t v) {
-  uint32_t r = 1;
-  while (r * 2 <= v) r *= 2;
-  return r;
+// Super-tiles of a frame of tx x ty tiles that is binned in two levels: SW (a power of two) x SH tiles, at most kMaxSub,
+// at most kMaxSupers of them (as many as it takes when that cannot be), chosen so that the split, which gives a compute
+// unit one super-tile at a time, ends with full rounds. Returns the tiles on the fullest unit.
+static uint64_t pick_supers(uint32_t tx, uint32_t ty, uint32_t& lSW, uint32_t& SH) {
+  uint64_t best = ~0ull, fewest = ~0ull;
+  for (uint32_t l = 1; l <= 3; ++l) {
+    for (uint32_t sh = 2; (sh << l) <= kMaxSub; ++sh) {
+      const uint64_t n = ((uint64_t)(tx + (1u << l) - 1) >> l) * ((ty + sh - 1) / sh);
+      const uint64_t cost = n <= kMaxSupers ? (n + kComputeUnits - 1) / kComputeUnits * (sh << l) : ~0ull;
+      if (cost < best || (best == ~0ull && n < fewest)) {
+        best = cost;
+        fewest = n;
+        lSW = l;
+        SH = sh;
+      }
+    }
+  }
+  return best == ~0ull ? (fewest + kComputeUnits - 1) / kComputeUnits * (SH << lSW) : best;
+}
+
+// Tile of a frame, from the LDS bytes per pixel: TW a power of two, TH any height in [TW/2, 2 TW), and the workgroup size
+// of the tile kernels.
+//
+// A compute unit takes its tiles one after the other (its LDS holds one large tile, or several small ones that share its
+// lanes), so a frame costs about (tiles on the fullest unit) x (pixels per tile + what a tile costs by itself), the
+// latter worth about kTileFixedPx pixels of a frame with 24 fragments per pixel; a frame binned in two levels costs its
+// fullest unit's super-tiles in the split besides. The shape that makes this least is taken, the larger one where it
+// changes nothing: as large as the LDS allows for a large frame (few tiles also make the binning's runs long), a divisor
+// of the frame that leaves no nearly empty last round for a middle one, and tiles small enough to reach every compute
+// unit for a small one. M > 32 keeps power-of-two tiles: there the tile is a few dozen pixels or less.
+static void pick_tile(Geom& g, uint32_t per_px) {
+  uint32_t most = std::min<uint32_t>(std::max<uint32_t>(1, kLdsBytes / per_px), kMaxTilePx);
+  uint32_t e = 0;  // the largest power-of-two tile
+  while ((2u << e) <= most) ++e;
+  g.lTW = (e + 1) / 2;
+  g.TH = 1u << (e / 2);
+  g.ntiles_large = (((g.W - 1) >> g.lTW) + 1) * ((g.H - 1) / g.TH + 1);
+  if (g.M <= 32) {
+    // a column of coefficients per thread where the columns are long (one more pass over the threads for a few columns
+    // costs as much as a full one)
+    if (g.M >= 16) most = std::min<uint32_t>(most, kTileThreads / g.C);
+    uint64_t best = ~0ull;
+    for (uint32_t l = 3; l <= 6; ++l) {
+      const uint32_t tw = 1u << l;
+      for (uint32_t th = std::min(2 * tw - 1, most / tw); th >= tw / 2 && tw * th >= kMinTilePx; --th) {
+        const uint32_t px = tw * th, tx = (g.W - 1) / tw + 1, ty = (g.H - 1) / th + 1;
+        const uint64_t nt = (uint64_t)tx * ty;
+        uint64_t cost = (nt + kComputeUnits - 1) / kComputeUnits * (px + kTileFixedPx);
+        uint32_t lsw, sh;
+        if (nt > kTwoLevelTiles) cost += pick_supers(tx, ty, lsw, sh) * px;
+        if (nt > kMaxLdsBins * kMaxSub) cost = nt << 24;  // past the tables of two levels: as few tiles as can be
+        if (cost < best || (cost == best && px > g.TH << g.lTW)) {
+          best = cost;
+          g.lTW = l;
+          g.TH = th;
+        }
+      }
+    }
+  }
+  g.TW = 1u << g.lTW;
+  g.divTH = make_fastdiv(g.TH);
+  g.mulTH = g.H <= (1u << 14) && g.TH >= 4 ? ((1u << 20) + g.TH - 1) / g.TH : 0;
+  g.tile_px = g.TW * g.TH;
+  g.tilesX = (g.W - 1) / g.TW + 1;
+  g.tilesY = (g.H - 1) / g.TH + 1;
+  g.ntiles = g.tilesX * g.tilesY;
+  // as many threads as fill a compute unit together with the other tiles it holds, at least four per pixel of a tile
+  // that is alone on it
+  const uint32_t together =
+      std::min<uint32_t>(kLdsBytes / (g.tile_px * per_px), (g.ntiles - 1) / kComputeUnits + 1);
+  g.tthreads = together >= 4 ? kTileThreads / 4 : together >= 2 ? kTileThreads / 2 : kTileThreads;
+  while (g.tthreads > kTileThreads / 4 && g.tthreads >= 8 * g.tile_px) g.tthreads /= 2;
 }
 
 Geom make_geom(const wt_frame_desc& d, bool backward) {
@@ -49,41 +117,19 @@ Geom make_geom(const wt_frame_desc& d, bool backward) {
   g.AW = (d.channels == 3) ? 8 : 4;
   g.AL = (d.channels == 3) ? 6 : 4;
   g.dtype = d.coeff_dtype;
-  // Largest power-of-two tile whose LDS working set fits one compute unit. Forward: FP64 endpoint masses
-  // (M + 1 per channel) and three FP64 colour sums, or, for M > 32, FP64 coefficient sums plus FP64 accumulations. Backward: FP32 cells,
-  // FP64 cell adjoints and per-pixel gradient data.
-  auto tile_for = [](uint32_t per_px) {
-    const uint32_t px = std::max<uint32_t>(1, kLdsBytes / per_px);
-    return std::min<uint32_t>(floor_pow2(px), kMaxTilePx);
-  };
-  uint32_t px;
-  g.ep = 0;
+  // LDS of a tile's pixel. Forward: FP64 endpoint masses (M + 1 per channel) and three FP64 colour sums, or, for
+  // M > 32, FP64 coefficient sums plus FP64 accumulations; the one-pass render adds the previous frame's FP32 cells
+  // (M <= 32 and no depth bounds are checked by the API). Backward: FP32 cells, FP64 cell adjoints and per-pixel
+  // gradient data. Depth bounds are two FP32.
   g.tight = (d.flags & WT_TIGHT_DEPTH) ? 1 : 0;
   g.serial = (d.flags & WT_DETERMINISTIC) ? 1 : 0;
-  const uint32_t bpx = g.tight ? 8 : 0;  // per-pixel depth bounds (two FP32) in LDS
-  if (backward) {
-    px = tile_for(12 * g.C * g.M + 4 * (3 + g.C) + bpx);
-  } else if (d.flags & WT_TEMPORAL) {
-    // one-pass render: endpoint masses, colour sums and the previous frame's FP32 cells (M <= 32 and no depth
-    // bounds are checked by the API); every pixel/channel has a thread
-    g.temporal = 1;
-    px = std::min<uint32_t>(tile_for(8 * g.C * (g.M + 1) + 24 + 4 * g.C * g.M), floor_pow2(kTileThreads / g.C));
-    g.ep = 1;
-  } else {
-    g.ep = g.M <= 32 ? 1 : 0;
-    px = g.ep ? tile_for(8 * g.C * (g.M + 1) + 24 + bpx) : tile_for(8 * (g.C * g.M + g.AL) + bpx);
-  }
-  uint32_t e = 0;
-  while ((1u << e) < px) ++e;
-  g.lTW = (e + 1) / 2;
-  g.lTH = e / 2;
-  g.TW = 1u << g.lTW;
-  g.TH = 1u << g.lTH;
+  g.temporal = !backward && (d.flags & WT_TEMPORAL) ? 1 : 0;
+  g.ep = !backward && g.M <= 32 ? 1 : 0;
+  const uint32_t per_px = (backward ? 12 * g.C * g.M + 4 * (3 + g.C)
+                           : g.ep   ? 8 * g.C * (g.M + 1) + 24 + (g.temporal ? 4 * g.C * g.M : 0)
+                                    : 8 * (g.C * g.M + g.AL)) + (g.tight ? 8 : 0);
+  pick_tile(g, per_px);
   g.divW = make_fastdiv(g.W);
-  g.tile_px = g.TW * g.TH;
-  g.tilesX = (g.W + g.TW - 1) / g.TW;
-  g.tilesY = (g.H + g.TH - 1) / g.TH;
-  g.ntiles = g.tilesX * g.tilesY;
   // One LDS tile table for the scatter (up to kTwoLevelTiles tiles; beyond, two levels below)
   g.lds_bins = g.ntiles <= kTwoLevelTiles ? 1 : 0;
   g.rb = g.ntiles;
@@ -94,41 +140,34 @@ Geom make_geom(const wt_frame_desc& d, bool backward) {
   // each super-tile's records into its tiles (runs of hundreds of records, no atomics).
   g.two = 0;
   g.SW = g.SH = 1;
+  g.lSW = 0;
   if (g.ntiles > kTwoLevelTiles) {
-    auto supers = [&](uint32_t sw, uint32_t sh) {
-      return ((g.tilesX + sw - 1) / sw) * ((g.tilesY + sh - 1) / sh);
-    };
-    while (supers(g.SW, g.SH) > kMaxSupers && g.SW * g.SH < kMaxSub) {
-      if (g.SW <= g.SH) g.SW *= 2;
-      else g.SH *= 2;
-    }
+    pick_supers(g.tilesX, g.tilesY, g.lSW, g.SH);
+    g.SW = 1u << g.lSW;
     // super-tile tables must fit the scatter's LDS; beyond that (about half a million tiles) the stream is
     // binned with one global atomic per fragment
-    g.two = supers(g.SW, g.SH) <= kMaxLdsBins ? 1 : 0;
+    g.two = (uint64_t)((g.tilesX - 1) / g.SW + 1) * ((g.tilesY - 1) / g.SH + 1) <= kMaxLdsBins ? 1 : 0;
     g.lds_bins = g.two;
   }
-  g.lSW = 0;
-  while ((1u << g.lSW) < g.SW) ++g.lSW;
-  g.lSH = 0;
-  while ((1u << g.lSH) < g.SH) ++g.lSH;
   g.sX = (g.tilesX + g.SW - 1) / g.SW;
   g.sY = (g.tilesY + g.SH - 1) / g.SH;
   g.nsuper = g.sX * g.sY;
   g.NX = g.lds_bins ? kClasses : 1;
   // Scatter: two workgroups per compute unit where the tile tables (of the binning level that scatters) and a
-  // 1024-record round fit half the LDS and a 4096-fragment chunk still holds two records per bin on average, so
+  // 1024-record round fit half the LDS and a 4096-fragment chunk still holds more than one record per bin, so
   // that one workgroup's loads overlap the other's ranking, staging and writes: one channel, 1024 threads with 4
   // fragments each (64 registers, eight waves per SIMD); three channels, 512 threads with 8 fragments each (the
   // three-channel fragment needs about 110 registers: four waves per SIMD). Otherwise one workgroup of 1024 threads
   // with 8 fragments each per compute unit. Chunks are powers of two.
-  // (Glass 3840x2160: the three-channel form took the scatter phases from 7.86 to 7.22 ms. Smoke frame at rank 4,
-  // 4,080 tiles: one workgroup per compute unit, two records per bin and chunk, 2.10 -> 2.07 ms.)
+  // (Glass 3840x2160: the three-channel form took the scatter phases from 7.86 to 7.22 ms. One channel, 50 M fragments:
+  // 2,280 bins 0.718 ms with one workgroup per compute unit, 0.678 with two; 3,000 bins 0.725 and 0.692; at 4,080 one
+  // is faster, smoke frame 2.10 -> 2.07 ms.)
   // (a one-channel record stages in at most 32 bytes, index or not, a three-channel one in at most 40: 1024 of
   // them take 32 or 40 KB)
   g.sthreads = 1024;
   g.kper = kPer;
   const uint32_t bins = g.two ? g.nsuper : g.rb;
-  const bool two_wg = g.lds_bins && bins <= 2048 &&
+  const bool two_wg = g.lds_bins && bins <= kTwoWgBins &&
                       8ull * bins + 1024ull * (g.C == 1 ? 32 : 40) <= kLdsBytes / 2 - 1024;
   if (two_wg && g.C == 1) g.kper = 4;
   if (two_wg && g.C == 3) g.sthreads = 512;
@@ -139,9 +178,10 @@ Geom make_geom(const wt_frame_desc& d, bool backward) {
 Geom super_geom(const Geom& g) {
   Geom s = g;
   s.lTW = g.lTW + g.lSW;
-  s.lTH = g.lTH + g.lSH;
   s.TW = 1u << s.lTW;
-  s.TH = 1u << s.lTH;
+  s.TH = g.TH * g.SH;
+  s.divTH = make_fastdiv(s.TH);
+  s.mulTH = g.H <= (1u << 14) && s.TH <= 64 ? ((1u << 20) + s.TH - 1) / s.TH : 0;
   s.tile_px = s.TW * s.TH;
   s.tilesX = g.sX;
   s.tilesY = g.sY;
@@ -149,7 +189,7 @@ Geom super_geom(const Geom& g) {
   s.rb = s.hrb = g.nsuper;
   s.two = 0;
   s.SW = s.SH = 1;
-  s.lSW = s.lSH = 0;
+  s.lSW = 0;
   s.sX = s.tilesX;
   s.sY = s.tilesY;
   return s;  // NX, kper and chunk stay those of g: the first level uses the classes the histogram counted
@@ -614,7 +654,7 @@ __global__ __launch_bounds__(256) void k_super_counts(const uint32_t* __restrict
   const uint32_t sx = sidx % g.sX, sy = sidx / g.sX;
   uint32_t sum = 0;
   for (uint32_t j = 0; j < g.SW * g.SH; ++j) {
-    const uint32_t tx = (sx << g.lSW) + (j & (g.SW - 1)), ty = (sy << g.lSH) + (j >> g.lSW);
+    const uint32_t tx = (sx << g.lSW) + (j & (g.SW - 1)), ty = sy * g.SH + (j >> g.lSW);
     if (tx < g.tilesX && ty < g.tilesY) sum += counts[x * g.ntiles + ty * g.tilesX + tx];
   }
   counts1[id] = sum;
@@ -1064,7 +1104,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_split(Geom g, const uint32_t*
   const uint32_t lTWs = g.lTW + g.lSW;  // super-tile width in pixels is 2^lTWs
   if (threadIdx.x < nsub) {
     const uint32_t j = threadIdx.x;
-    const uint32_t tx = (sx << g.lSW) + (j & (g.SW - 1)), ty = (sy << g.lSH) + (j >> g.lSW);
+    const uint32_t tx = (sx << g.lSW) + (j & (g.SW - 1)), ty = sy * g.SH + (j >> g.lSW);
     cur[j] = (tx < g.tilesX && ty < g.tilesY) ? offsets[(ty * g.tilesX + tx) * g.NX] : 0u;
   }
   for (uint32_t c0 = beg; c0 < end; c0 += RECS) {
@@ -1082,8 +1122,9 @@ __global__ __launch_bounds__(kSplitThreads) void k_split(Geom g, const uint32_t*
         for (uint32_t w = 0; w < DT; ++w) tw[k][w] = tail1[(uint64_t)i * DT + w];
         const uint32_t loc = hw[k][0];  // pixel within the super-tile
         const uint32_t lx = loc & ((1u << lTWs) - 1), ly = loc >> lTWs;
-        sub[k] = ((ly >> g.lTH) << g.lSW) + (lx >> g.lTW);
-        hw[k][0] = ((ly & (g.TH - 1)) << g.lTW) + (lx & (g.TW - 1));  // pixel within the tile
+        const uint32_t ty = fastdiv(ly, g.divTH);
+        sub[k] = (ty << g.lSW) + (lx >> g.lTW);
+        hw[k][0] = ((ly - ty * g.TH) << g.lTW) + (lx & (g.TW - 1));  // pixel within the tile
         rank[k] = atomicAdd(&cnt[sub[k]], 1u);
       }
     }

@@ -17,12 +17,19 @@ constexpr uint32_t kCursorPad = 1;  // words per write cursor in the workspace's
 constexpr uint32_t kPer = 8;               // fragments per scatter thread (held in registers)
 constexpr uint32_t kMaxLdsBins = 8192;     // bins one scatter table holds (super-tiles of a two-level binning)
 constexpr uint32_t kMaxHistBins = 36864;   // tiles one histogram table holds (144 KB of LDS)
-constexpr uint32_t kTwoLevelTiles = 4096;  // frames with more tiles are binned in two levels (super-tiles, then tiles)
+constexpr uint32_t kTwoWgBins = 3584;      // bins up to which two scatter workgroups share a compute unit
+// Frames with more tiles are binned in two levels (super-tiles, then tiles): past the tables of one level. Below, runs of
+// single records cost less than moving every record twice (scatter phases, one level against two: three channels,
+// 56 M fragments, 6,200 tiles 1.35 and 1.61 ms; one channel, 133 M, 8,160 tiles 2.72 and 2.93 ms).
+constexpr uint32_t kTwoLevelTiles = 8192;
 constexpr uint32_t kMaxSupers = 1024;      // super-tiles of the first level at most
 constexpr uint32_t kMaxSub = 64;           // tiles per super-tile at most
 constexpr uint32_t kLdsBytes = 160 * 1024; // LDS of one CDNA4 compute unit (also the per-workgroup limit)
+constexpr uint32_t kComputeUnits = 256;    // of one MI355X
 constexpr uint32_t kMaxTilePx = 2048;
-constexpr uint32_t kTileThreads = 1024;    // workgroup size of the per-tile kernels
+constexpr uint32_t kMinTilePx = 64;
+constexpr uint32_t kTileFixedPx = 160;     // what a tile costs by itself, in pixels (pick_tile)
+constexpr uint32_t kTileThreads = 1024;    // largest workgroup of the per-tile kernels
 constexpr uint32_t kScanRange = 16384;     // segments one scan workgroup covers (a multiple of kClasses)
 constexpr float kAlphaMax = 0.99999994f;   // 1 - 2^-24
 
@@ -125,15 +132,16 @@ __host__ __device__ inline uint16_t f64_to_bf16_bits(double v) {
 struct Geom {
   uint32_t W, H, P;      // frame
   uint32_t C, rank, M, L;// channels, rank, coefficients per channel (2^L), L = rank + 1
-  uint32_t TW, TH;       // tile extent in pixels (powers of two)
-  uint32_t lTW, lTH;     // log2 of TW, TH
-  FastDiv divW;          // division by W
+  uint32_t TW, TH;       // tile extent in pixels (TW a power of two)
+  uint32_t lTW;          // log2 of TW
+  FastDiv divW, divTH;   // division by W and by TH
+  uint32_t mulTH;        // ceil(2^20 / TH) where y / TH is (y mulTH) >> 20 for every row (row_tile), or 0
   uint32_t tilesX, tilesY, ntiles, tile_px;
   uint32_t NX;           // write-frontier classes (kClasses, or 1 when the tile count is large)
   uint32_t lds_bins;     // 1: LDS-staged scatter; 0: one global atomic per fragment
   uint32_t rb;           // bins of the scatter table (tiles of a one-level binning)
   uint32_t two;          // 1: two-level binning (super-tiles of SW x SH tiles, then tiles)
-  uint32_t SW, SH, lSW, lSH, sX, sY, nsuper;
+  uint32_t SW, SH, lSW, sX, sY, nsuper;
   uint32_t hrb;          // tiles per histogram table (range)
   uint32_t AW;           // accum floats per pixel in global memory: 4 (C = 1) or 8 (C = 3)
   uint32_t AL;           // accumulation floats per pixel in LDS: 4 (C = 1) or 6 (C = 3)
@@ -142,6 +150,8 @@ struct Geom {
   uint32_t tight;        // 1: per-pixel depth bounds (WT_TIGHT_DEPTH); the tile kernels keep them in LDS
   uint32_t temporal;     // 1: tiles sized for the one-pass render against the previous frame (WT_TEMPORAL)
   uint32_t serial;       // 1: WT_DETERMINISTIC (stream-order binning by one thread, one thread per tile's records)
+  uint32_t ntiles_large; // tiles of the frame if they were the largest power-of-two tiles
+  uint32_t tthreads;     // workgroup size of the tile kernels
   uint32_t sthreads;     // scatter workgroup size
   uint32_t kper;         // fragments per scatter thread (4 or kPer)
   uint32_t chunk;        // fragments per scatter workgroup = sthreads * kper (also the class granularity)

@@ -121,10 +121,7 @@ __device__ __forceinline__ void resolve_tile(const Geom& g, const TileRef& r, co
 // Records whose pixel, cell and offset a thread keeps in registers from the build to the evaluation, which then reads
 // only their colours: a tile of up to kKept * blockDim.x records has its heads read from memory once instead of twice
 // (three times with depth bounds); a deeper one re-reads the others, the latest built first.
-// As many as the conversion between the two leaves registers for (128 per thread at 1024 threads). Together with the
-// conversion in place and the batches of for_records: glass 3840x2160 (7,000 records per tile, all kept) tile kernel
-// 2.95 -> 2.51 ms, 1280x720 at rank 4 with 24 fragments per pixel 0.209 -> 0.168 ms, depth bounds at 1920x1080 0.57 ->
-// 0.43 ms; the smoke frame (65,000 per tile) stays at 0.89 ms, bound by its reads (without any LDS work 0.88 ms).
+// As many as the conversion between the two leaves registers for (128 per thread at 1024 threads).
 template <int C, bool TIGHT>
 constexpr int kept() { return C == 1 && !TIGHT ? 16 : 12; }
 
@@ -201,10 +198,7 @@ __global__ __launch_bounds__(kTileThreads) void k_render(Binned b, Geom g, TS* _
 #pragma unroll
     for (int k = 0; k < K; ++k)
       if (kept[k].key != kNoRecord) bounds_add(lb, TP, f[k].lp, f[k].x);
-    for (uint32_t i = r.beg + threadIdx.x; i < rest; i += T) {
-      Head<C> f0;
-      if (load_head<C>(b, i, f0)) bounds_add(lb, TP, f0.lp, f0.x);
-    }
+    bounds_range<C>(b, r.beg, rest, lb, TP);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -457,7 +451,7 @@ hipError_t launch_render(const Geom& g, const Binned& b, const float* bg, void* 
     }
     hipError_t err = prep(k, lds);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(kTileThreads), lds, s, b, g, (TS*)coeffs, bg[0], bg[1], bg[2], out);
+    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(g.tthreads), lds, s, b, g, (TS*)coeffs, bg[0], bg[1], bg[2], out);
     return hipGetLastError();
   });
 }
@@ -472,7 +466,7 @@ hipError_t launch_render_temporal(const Geom& g, const Binned& b, const float* b
     auto k = k_render_temporal<C, TS>;
     hipError_t err = prep(k, lds);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(kTileThreads), lds, s, b, g, (const TS*)prev, map, (TS*)coeffs,
+    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(g.tthreads), lds, s, b, g, (const TS*)prev, map, (TS*)coeffs,
                        bg[0], bg[1], bg[2], out);
     return hipGetLastError();
   });

@@ -98,72 +98,10 @@ __device__ __forceinline__ void load_tail(const Binned& b, uint32_t i, float (&w
 template <int C>
 constexpr bool last_read_nt() { return C == 1; }
 
-// ------------------------------------------------------------------------------------------- depth bounds
-
-// Per-pixel depth bounds of the tile (section 2.1, step 1): lb[lp] = lo, lb[TP + lp] = hi as FP32 bit patterns,
-// over the clamped depths of the tile's valid fragments (non-negative floats order like their bit patterns, so
-// LDS u32 min/max atomics take them). Ends with a barrier.
-__device__ __forceinline__ void bounds_add(uint32_t* lb, uint32_t TP, uint32_t lp, float x) {
-  const uint32_t xb = __float_as_uint(fminf(fmaxf(x, 0.f), 1.f));
-  atomicMin(lb + lp, xb);
-  atomicMax(lb + TP + lp, xb);
-}
-
-__device__ __forceinline__ void bounds_clear(uint32_t* lb, uint32_t TP) {
-  for (uint32_t lp = threadIdx.x; lp < TP; lp += blockDim.x) {
-    lb[lp] = __float_as_uint(1.f);
-    lb[TP + lp] = 0u;
-  }
-}
-
-template <int C>
-__device__ __forceinline__ void bounds_tile(const Binned& b, const Geom& g, const TileRef& r, uint32_t* lb) {
-  const uint32_t TP = g.tile_px;
-  bounds_clear(lb, TP);
-  __syncthreads();
-  for (uint32_t i = r.beg + threadIdx.x; i < r.end; i += blockDim.x) {
-    Head<C> f;
-    if (!load_head<C>(b, i, f)) continue;
-    bounds_add(lb, TP, f.lp, f.x);
-  }
-  __syncthreads();
-}
-// ------------------------------------------------------------------------------------------- build
-
-// On-chip sums are FP64: on gfx950 an LDS FP64 atomic add sustains about nine times the rate of an FP32 one,
-// and every FP32 term then rounds once while the sum rounds nowhere.
-using acc_t = double;
-
 // Binned records each thread keeps in flight in the build and evaluate loops (memory-level parallelism of one
 // workgroup per compute unit).
 constexpr int kBuildUnroll = 8;
 constexpr int kEvalUnroll = 4;
-
-// A fragment's contribution to every coefficient depends on its depth only through its finest cell j and the
-// offset t = M x - j in it: 1 - x and every tent tau(2^n x - k) are linear on a finest cell (their kinks lie on
-// cell boundaries for n <= N). So the N + 2 closed-form updates of section 2.3.1 factor exactly through two
-// endpoint masses, e_j += a (1 - t) and e_{j+1} += a t, per fragment and channel:
-//   chi     = sum_m e_m (1 - m/M),   d_{n,k} = -sum_m e_m tau(2^n m / M - k),   sum a = sum_m e_m,
-// with exact dyadic weights and all terms of one sign (no cancellation). Two LDS atomics per fragment instead
-// of N + 2, and the absorbance total comes for free.
-template <int C>
-__device__ __forceinline__ void ep_add(acc_t* le, uint32_t TP, uint32_t M1, uint32_t lp, uint32_t j, float t, float omt,
-                                       const float (&al)[C]) {
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    acc_t* e = le + (c * M1 + j) * TP + lp;
-    atomicAdd(e, (acc_t)(al[c] * omt));
-    atomicAdd(e + TP, (acc_t)(al[c] * t));
-  }
-}
-
-template <int C>
-__device__ __forceinline__ void build_ep_add(acc_t* le, const Geom& g, const Head<C>& f, const uint32_t* lb) {
-  uint32_t j;
-  float t, omt;
-  cell_coord(f.x, lb, g.tile_px, f.lp, g.M, j, t, omt);
-  ep_add<C>(le, g.tile_px, g.M + 1, f.lp, j, t, omt, f.al);
-}
 
 // Records [beg, end) dealt to the workgroup's threads in batches of U per thread, all of a batch's loads in flight before
 // its first use: load(i, u) reads record i into the batch's slot u and says whether it counts, use(u) applies it. Whole
@@ -203,6 +141,72 @@ __device__ __forceinline__ void for_records(uint32_t beg, uint32_t end, Load&& l
     last(std::integral_constant<int, U>{});
   else if (end > base)
     last(std::integral_constant<int, U / 2>{});
+}
+
+// ------------------------------------------------------------------------------------------- depth bounds
+
+// Per-pixel depth bounds of the tile (section 2.1, step 1): lb[lp] = lo, lb[TP + lp] = hi as FP32 bit patterns,
+// over the clamped depths of the tile's valid fragments (non-negative floats order like their bit patterns, so
+// LDS u32 min/max atomics take them). Ends with a barrier.
+__device__ __forceinline__ void bounds_add(uint32_t* lb, uint32_t TP, uint32_t lp, float x) {
+  const uint32_t xb = __float_as_uint(fminf(fmaxf(x, 0.f), 1.f));
+  atomicMin(lb + lp, xb);
+  atomicMax(lb + TP + lp, xb);
+}
+
+__device__ __forceinline__ void bounds_clear(uint32_t* lb, uint32_t TP) {
+  for (uint32_t lp = threadIdx.x; lp < TP; lp += blockDim.x) {
+    lb[lp] = __float_as_uint(1.f);
+    lb[TP + lp] = 0u;
+  }
+}
+
+template <int C>
+__device__ __forceinline__ void bounds_range(const Binned& b, uint32_t beg, uint32_t end, uint32_t* lb, uint32_t TP) {
+  Head<C> f[kBuildUnroll];
+  for_records<kBuildUnroll>(
+      beg, end, [&](uint32_t i, int u) { return load_head<C>(b, i, f[u]); },
+      [&](int u) { bounds_add(lb, TP, f[u].lp, f[u].x); });
+}
+
+template <int C>
+__device__ __forceinline__ void bounds_tile(const Binned& b, const Geom& g, const TileRef& r, uint32_t* lb) {
+  bounds_clear(lb, g.tile_px);
+  __syncthreads();
+  bounds_range<C>(b, r.beg, r.end, lb, g.tile_px);
+  __syncthreads();
+}
+
+// ------------------------------------------------------------------------------------------- build
+
+// On-chip sums are FP64: on gfx950 an LDS FP64 atomic add sustains about nine times the rate of an FP32 one,
+// and every FP32 term then rounds once while the sum rounds nowhere.
+using acc_t = double;
+
+// A fragment's contribution to every coefficient depends on its depth only through its finest cell j and the
+// offset t = M x - j in it: 1 - x and every tent tau(2^n x - k) are linear on a finest cell (their kinks lie on
+// cell boundaries for n <= N). So the N + 2 closed-form updates of section 2.3.1 factor exactly through two
+// endpoint masses, e_j += a (1 - t) and e_{j+1} += a t, per fragment and channel:
+//   chi     = sum_m e_m (1 - m/M),   d_{n,k} = -sum_m e_m tau(2^n m / M - k),   sum a = sum_m e_m,
+// with exact dyadic weights and all terms of one sign (no cancellation). Two LDS atomics per fragment instead
+// of N + 2, and the absorbance total comes for free.
+template <int C>
+__device__ __forceinline__ void ep_add(acc_t* le, uint32_t TP, uint32_t M1, uint32_t lp, uint32_t j, float t, float omt,
+                                       const float (&al)[C]) {
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    acc_t* e = le + (c * M1 + j) * TP + lp;
+    atomicAdd(e, (acc_t)(al[c] * omt));
+    atomicAdd(e + TP, (acc_t)(al[c] * t));
+  }
+}
+
+template <int C>
+__device__ __forceinline__ void build_ep_add(acc_t* le, const Geom& g, const Head<C>& f, const uint32_t* lb) {
+  uint32_t j;
+  float t, omt;
+  cell_coord(f.x, lb, g.tile_px, f.lp, g.M, j, t, omt);
+  ep_add<C>(le, g.tile_px, g.M + 1, f.lp, j, t, omt, f.al);
 }
 
 // Applies records [beg, end) to the endpoint masses.

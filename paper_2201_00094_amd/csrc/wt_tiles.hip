@@ -286,7 +286,7 @@ hipError_t launch_build(const Geom& g, const Binned& b, void* coeffs, hipStream_
     auto k = k_build<C, TS>;
     hipError_t err = prep(k, lds);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(kTileThreads), lds, s, b, g, (TS*)coeffs);
+    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(g.tthreads), lds, s, b, g, (TS*)coeffs);
     return hipGetLastError();
   });
 }
@@ -299,7 +299,7 @@ hipError_t launch_evaluate(const Geom& g, const Binned& b, const void* coeffs, f
     auto k = (g.M <= 32) ? k_evaluate<C, TS, true> : k_evaluate<C, TS, false>;
     hipError_t err = prep(k, lds);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(kTileThreads), lds, s, b, g, (const TS*)coeffs, accum);
+    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(g.tthreads), lds, s, b, g, (const TS*)coeffs, accum);
     return hipGetLastError();
   });
 }

@@ -39,3 +39,54 @@ def test_record_counts(orc, channels, tight, rank, dtype):
         assert (gc[o["coeffs"] == 0] == 0).all()
         assert (np.abs(gc - o["coeffs"]) <= 1e-5 * np.abs(o["coeffs"])).all(), F
         assert np.abs(out.cpu().double().numpy() - o["out"]).max() <= 1e-4, F
+
+
+# Tiles of heights that are no power of two, last rows and columns cut, one and two binning levels (super-tiles of odd
+# heights), small frames with small tiles: (width, height, rank, channels, tight, mean fragments per pixel)
+SHAPES = [(70, 45, 3, 1, False, 9.0), (333, 201, 3, 3, False, 6.0), (640, 360, 4, 1, True, 3.0), (517, 1031, 2, 3, False, 2.0),
+          (2100, 1701, 3, 3, False, 0.4), (1601, 1203, 4, 3, True, 0.5), (65, 16500, 3, 1, False, 0.6)]
+
+
+@pytest.mark.parametrize("width,height,rank,channels,tight,mean", SHAPES)
+def test_tile_shapes(orc, width, height, rank, channels, tight, mean):
+    import torch
+    import paper_2201_00094_amd as wt
+    say("case tile shapes", width, height, rank, channels, tight)
+    rng = np.random.default_rng(width)
+    F = int(width * height * mean)
+    pixel, depth, alpha, rgb = _stream(rng, width * height, F, channels)
+    pixel[:2] = 0, width * height - 1
+    spec = wt.FrameSpec(width, height, rank, channels, tight=tight)
+    fr = wt.Fragments.from_numpy(pixel, depth, alpha, rgb)
+    coeffs, ws = spec.new_coeffs(), wt.Workspace(spec, F)
+    out = wt.render(spec, fr, (0.1, 0.2, 0.3), ws, coeffs=coeffs)
+    torch.cuda.synchronize()
+    assert wt.dropped_count(ws) == 0
+    o = orc.resolve(width, height, rank, pixel, depth, alpha, rgb, bg=(0.1, 0.2, 0.3), channels=channels, tight=tight,
+                    want=("coeffs", "out"))
+    gc = coeffs.cpu().double().numpy()
+    assert (gc[o["coeffs"] == 0] == 0).all()
+    assert (np.abs(gc - o["coeffs"]) <= 1e-5 * np.abs(o["coeffs"])).all()
+    assert np.abs(out.cpu().double().numpy() - o["out"]).max() <= 1e-4
+
+
+@pytest.mark.parametrize("width,height,rank,channels", [(1700, 1401, 3, 3), (2203, 1703, 4, 1)])
+def test_gradient_two_levels(orc, width, height, rank, channels):
+    """Records that keep the stream index through super-tiles and the split (more than 8192 gradient tiles)."""
+    import torch
+    import paper_2201_00094_amd as wt
+    say("case gradient two levels", width, height, rank, channels)
+    rng = np.random.default_rng(height)
+    F = width * height // 3
+    pixel, depth, alpha, rgb = _stream(rng, width * height, F, channels)
+    spec = wt.FrameSpec(width, height, rank, channels)
+    fr = wt.Fragments.from_numpy(pixel, depth, alpha, rgb)
+    ws, coeffs, accum = wt.Workspace(spec, F), spec.new_coeffs(), spec.new_accum()
+    wt.build(spec, fr, coeffs, ws)
+    wt.evaluate(spec, fr, coeffs, accum, ws)
+    g = rng.standard_normal((width * height, 3)).astype(np.float32)
+    ga, gr = wt.backward(spec, fr, coeffs, accum, (0.1, 0.2, 0.3), torch.from_numpy(g).cuda(), ws)
+    torch.cuda.synchronize()
+    oa, og = orc.backward(width, height, rank, pixel, depth, alpha, rgb, g, bg=(0.1, 0.2, 0.3), channels=channels)
+    assert np.abs(ga.cpu().double().numpy().reshape(F, channels) - oa).max() <= 1e-3
+    assert np.abs(gr.cpu().double().numpy() - og).max() <= 1e-4
