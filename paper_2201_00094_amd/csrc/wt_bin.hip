@@ -282,33 +282,47 @@ unsigned long long count_stamp(const Geom& g, const Layout& l, const wt_fragment
   return stamp_words(w, 12);
 }
 
-// Start of a count: no complete binning and no count in the workspace any more; the drop counter and the scatter
-// fault restart. The sticky error bits stay until wt_dropped_count reports them.
-__global__ void k_header_reset(WsHeader* h) {
-  if (h->magic != kWsMagic) {  // a workspace the device has not written yet: no errors to keep
-    h->errors = 0;
-    h->magic = kWsMagic;
+// Start of a count: the tile counts start from zero; no complete binning and no count in the workspace any more; the
+// drop counter and the scatter's progress restart. The sticky error bits stay until wt_dropped_count reports them.
+__global__ __launch_bounds__(256) void k_count_reset(WsHeader* h, uint32_t* __restrict__ counts, uint64_t n) {
+  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
+    counts[i] = 0u;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (h->magic != kWsMagic) {  // a workspace the device has not written yet: no errors to keep
+      h->errors = 0;
+      h->magic = kWsMagic;
+    }
+    h->dropped = 0;
+    h->fault = 0;
+    h->counted = 0;
+    h->binned = 0;
   }
-  h->dropped = 0;
-  h->fault = 0;
-  h->counted = 0;
-  h->binned = 0;
 }
 
 // End of a scatter: the binning is complete when the count before it was this stream's under this layout, the
 // scatter did not refuse, and every write cursor reached the end of its segment (so each segment holds exactly the
 // records counted for it). Then the header gets `stamp`, else 0.
-// One workgroup. cursors are [NX][nt] (row stride kCursorPad words), offsets [nt * NX + 1].
+// One workgroup. cursors are [NX][nt] (row stride kCursorPad words), offsets [nt * NX + 1]. A thread has a tile's
+// cursors and segment ends in flight together (one at a time, with a division each, the check was a chain of memory
+// latencies: 2,280 tiles 17 us). (Checked by the scatter's last workgroup instead, after a ticket per workgroup, it cost
+// the smoke frame's scatter 28 us against 10 for this launch.)
+template <uint32_t NX>
 __global__ __launch_bounds__(1024) void k_seal(WsHeader* h, const uint32_t* __restrict__ cursors,
-                                                const uint32_t* __restrict__ offsets, uint32_t NX, uint32_t nt,
+                                                const uint32_t* __restrict__ offsets, uint32_t nt,
                                                 unsigned long long cstamp, unsigned long long stamp) {
   __shared__ int bad;
   if (threadIdx.x == 0) bad = 0;
   __syncthreads();
   int mine = 0;
-  for (uint32_t e = threadIdx.x; e < NX * nt; e += blockDim.x) {
-    const uint32_t x = e / nt, t = e - x * nt;
-    mine |= cursors[(size_t)e * kCursorPad] != offsets[t * NX + x + 1];
+  for (uint32_t t = threadIdx.x; t < nt; t += 1024) {
+    uint32_t c[NX], end[NX];
+#pragma unroll
+    for (uint32_t x = 0; x < NX; ++x) {
+      c[x] = cursors[(x * nt + t) * kCursorPad];
+      end[x] = offsets[(uint64_t)t * NX + x + 1];
+    }
+#pragma unroll
+    for (uint32_t x = 0; x < NX; ++x) mine |= c[x] != end[x];
   }
   if (mine) bad = 1;
   __syncthreads();
@@ -318,6 +332,12 @@ __global__ __launch_bounds__(1024) void k_seal(WsHeader* h, const uint32_t* __re
     // a scatter that did not belong to its count (another stream, arrays changed since the count, run twice)
     if (!ok) ws_raise(h, kWsErrScatter);
   }
+}
+
+static void launch_seal(WsHeader* h, const uint32_t* cursors, const uint32_t* offsets, uint32_t NX, uint32_t nt,
+                        unsigned long long cstamp, unsigned long long stamp, hipStream_t s) {
+  auto k = NX == 1 ? k_seal<1> : k_seal<kClasses>;
+  hipLaunchKernelGGL(k, dim3(1), dim3(1024), 0, s, h, cursors, offsets, nt, cstamp, stamp);
 }
 
 // After the split of a two-level binning: complete when the first level was (the split only moves its records).
@@ -482,9 +502,48 @@ __device__ __forceinline__ uint32_t size_class(uint32_t c) {
   return e * 8 + m;
 }
 
-// Exclusive scan over segments in (tile, class) order (counts/cursors are class-major [NX][ntiles]), then the
-// tile order for the tile kernels: heaviest first by size class (a bucket sort; ties in any order), so the last
-// workgroups to start are the light ones.
+// Scan of the tiles [t0, t0 + kScanThreads * TPT): a thread holds the class counts of its TPT tiles in registers (loaded
+// together, consecutive lanes on consecutive tiles), so the scan is one memory latency, one block prefix per TPT and the
+// stores. counts and cursors are class-major [NX][ntiles], offsets tile-major; cnt receives each tile's records.
+template <uint32_t NX, uint32_t TPT>
+__device__ __forceinline__ void scan_tiles(const uint32_t* __restrict__ counts, const Geom& g, uint32_t t0,
+                                           uint32_t* __restrict__ offsets, uint32_t* __restrict__ cursors,
+                                           uint32_t* wsum, uint32_t& carry, uint32_t (&cnt)[TPT]) {
+  uint32_t c[TPT][NX];
+#pragma unroll
+  for (uint32_t k = 0; k < TPT; ++k) {
+    const uint32_t t = t0 + k * kScanThreads + threadIdx.x;
+    cnt[k] = 0;
+    if (t0 + k * kScanThreads >= g.ntiles) continue;
+#pragma unroll
+    for (uint32_t x = 0; x < NX; ++x) {
+      c[k][x] = t < g.ntiles ? counts[x * g.ntiles + t] : 0u;
+      cnt[k] += c[k][x];
+    }
+  }
+#pragma unroll
+  for (uint32_t k = 0; k < TPT; ++k) {
+    if (t0 + k * kScanThreads >= g.ntiles) break;
+    const uint32_t t = t0 + k * kScanThreads + threadIdx.x;
+    uint32_t total;
+    uint32_t run = carry + block_exclusive(cnt[k], wsum, &total);
+    carry += total;
+    if (t >= g.ntiles) continue;
+#pragma unroll
+    for (uint32_t x = 0; x < NX; ++x) {
+      offsets[(uint64_t)t * NX + x] = run;
+      cursors[(x * g.ntiles + t) * kCursorPad] = run;
+      run += c[k][x];
+    }
+  }
+}
+
+// Exclusive scan over segments in (tile, class) order by one workgroup, then the tile order for the tile kernels:
+// heaviest first by size class (a bucket sort; ties in any order), so the last workgroups to start are the light ones.
+constexpr uint32_t kScanTiles = 8;  // tiles per thread
+static_assert(kTwoLevelTiles <= kScanTiles * kScanThreads && kMaxLdsBins <= kScanTiles * kScanThreads,
+              "one pass holds the tiles of a binning level");
+
 __global__ __launch_bounds__(kScanThreads) void k_scan(const uint32_t* __restrict__ counts, Geom g,
                                                        uint32_t* __restrict__ offsets,
                                                        uint32_t* __restrict__ cursors,
@@ -493,136 +552,81 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(const uint32_t* __restric
   if (hdr && threadIdx.x == 0) hdr->counted = stamp;  // the last scan of a count (seen by later kernels)
   __shared__ uint32_t wsum[kScanThreads / 64 + 1];
   __shared__ uint32_t bucket[kOrderBuckets];
-  const uint64_t n = (uint64_t)g.ntiles * g.NX;
   const uint32_t tid = threadIdx.x;
-  uint32_t carry = 0;
-  for (uint64_t seg = 0; seg < n; seg += (uint64_t)kScanThreads * kScanItems) {
-    uint32_t v[kScanItems];
-    uint32_t s = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-      const uint64_t e = seg + (uint64_t)tid * kScanItems + k;
-      v[k] = 0;
-      if (e < n) {
-        const uint32_t t = (uint32_t)(e / g.NX), x = (uint32_t)(e % g.NX);
-        v[k] = counts[x * g.ntiles + t];
-      }
-      s += v[k];
-    }
-    uint32_t total;
-    uint32_t run = carry + block_exclusive(s, wsum, &total);
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-      const uint64_t e = seg + (uint64_t)tid * kScanItems + k;
-      if (e < n) {
-        const uint32_t t = (uint32_t)(e / g.NX), x = (uint32_t)(e % g.NX);
-        offsets[e] = run;
-        cursors[(x * g.ntiles + t) * kCursorPad] = run;
-      }
-      run += v[k];
-    }
-    carry += total;
-  }
-  if (tid == 0) offsets[n] = carry;
-  if (!with_order) return;
-  // bucket sort by size class, largest class first
   for (uint32_t b = tid; b < kOrderBuckets; b += kScanThreads) bucket[b] = 0;
+  uint32_t carry = 0, cnt[kScanTiles];
+  scan_tiles<kClasses, kScanTiles>(counts, g, 0, offsets, cursors, wsum, carry, cnt);
+  if (tid == 0) offsets[(uint64_t)g.ntiles * kClasses] = carry;
+  if (!with_order) return;
   __syncthreads();
-  for (uint32_t t = tid; t < g.ntiles; t += kScanThreads) {
-    uint32_t c = 0;
-    for (uint32_t x = 0; x < g.NX; ++x) c += counts[x * g.ntiles + t];
-    atomicAdd(&bucket[kOrderBuckets - 1 - size_class(c)], 1u);
-  }
+#pragma unroll
+  for (uint32_t k = 0; k < kScanTiles; ++k)
+    if (k * kScanThreads + tid < g.ntiles) atomicAdd(&bucket[kOrderBuckets - 1 - size_class(cnt[k])], 1u);
   __syncthreads();
   uint32_t total;
   const uint32_t bc = tid < kOrderBuckets ? bucket[tid] : 0u;
   const uint32_t start = block_exclusive(bc, wsum, &total);
   if (tid < kOrderBuckets) bucket[tid] = start;
   __syncthreads();
-  for (uint32_t t = tid; t < g.ntiles; t += kScanThreads) {
-    uint32_t c = 0;
-    for (uint32_t x = 0; x < g.NX; ++x) c += counts[x * g.ntiles + t];
-    order[atomicAdd(&bucket[kOrderBuckets - 1 - size_class(c)], 1u)] = t;
+#pragma unroll
+  for (uint32_t k = 0; k < kScanTiles; ++k) {
+    const uint32_t t = k * kScanThreads + tid;
+    if (t < g.ntiles) order[atomicAdd(&bucket[kOrderBuckets - 1 - size_class(cnt[k])], 1u)] = t;
   }
 }
 
-// The same scan and tile order for frames with many segments, over several workgroups: workgroup w owns the
+// The same scan and tile order for frames with many tiles, over several workgroups: workgroup w owns the
 // segments [w R, (w + 1) R) (R = kScanRange, whole tiles since R is a multiple of NX). Pass one: each workgroup's
 // segment total and the size classes of its tiles (part[w][0], part[w][1 + k] for reversed class k). Pass two:
 // each workgroup adds the totals of the workgroups before it, scans its range, and places its tiles in the
 // heaviest-first order after every heavier class and after its class's tiles of earlier workgroups.
+template <uint32_t NX>
 __global__ __launch_bounds__(kScanThreads) void k_scan_part(const uint32_t* __restrict__ counts, Geom g,
                                                             uint32_t* __restrict__ part) {
   __shared__ uint32_t wsum[kScanThreads / 64 + 1];
   __shared__ uint32_t bucket[kOrderBuckets];
-  const uint64_t n = (uint64_t)g.ntiles * g.NX;
-  const uint64_t e0 = (uint64_t)blockIdx.x * kScanRange;
-  const uint32_t tid = threadIdx.x;
+  constexpr uint32_t TPT = kScanItems / NX;
+  const uint32_t tid = threadIdx.x, t0 = blockIdx.x * (kScanRange / NX);
   for (uint32_t b = tid; b < kOrderBuckets; b += kScanThreads) bucket[b] = 0;
-  uint32_t s = 0;
-  for (uint32_t k = tid; k < kScanRange; k += kScanThreads) {
-    const uint64_t e = e0 + k;
-    if (e < n) {
-      const uint32_t t = (uint32_t)(e / g.NX), x = (uint32_t)(e % g.NX);
-      s += counts[x * g.ntiles + t];
-    }
+  uint32_t cnt[TPT], s = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < TPT; ++k) {
+    const uint32_t t = t0 + k * kScanThreads + tid;
+    cnt[k] = 0;
+#pragma unroll
+    for (uint32_t x = 0; x < NX; ++x) cnt[k] += t < g.ntiles ? counts[x * g.ntiles + t] : 0u;
+    s += cnt[k];
   }
   uint32_t total;
-  block_exclusive(s, wsum, &total);
-  __syncthreads();
-  const uint32_t t0 = (uint32_t)(e0 / g.NX), t1 = (uint32_t)std::min<uint64_t>((e0 + kScanRange) / g.NX, g.ntiles);
-  for (uint32_t t = t0 + tid; t < t1; t += kScanThreads) {
-    uint32_t c = 0;
-    for (uint32_t x = 0; x < g.NX; ++x) c += counts[x * g.ntiles + t];
-    atomicAdd(&bucket[kOrderBuckets - 1 - size_class(c)], 1u);
-  }
+  block_exclusive(s, wsum, &total);  // its barriers also order the bucket clears before the adds
+#pragma unroll
+  for (uint32_t k = 0; k < TPT; ++k)
+    if (t0 + k * kScanThreads + tid < g.ntiles) atomicAdd(&bucket[kOrderBuckets - 1 - size_class(cnt[k])], 1u);
   __syncthreads();
   uint32_t* mine = part + (size_t)blockIdx.x * (1 + kOrderBuckets);
   if (tid == 0) mine[0] = total;
   for (uint32_t b = tid; b < kOrderBuckets; b += kScanThreads) mine[1 + b] = bucket[b];
 }
 
+template <uint32_t NX>
 __global__ __launch_bounds__(kScanThreads) void k_scan_apply(const uint32_t* __restrict__ counts, Geom g,
                                                              const uint32_t* __restrict__ part,
                                                              uint32_t* __restrict__ offsets,
                                                              uint32_t* __restrict__ cursors,
-                                                             uint32_t* __restrict__ order, int with_order,
-                                                             WsHeader* hdr, unsigned long long stamp) {
+                                                             uint32_t* __restrict__ order, WsHeader* hdr,
+                                                             unsigned long long stamp) {
   __shared__ uint32_t wsum[kScanThreads / 64 + 1];
   __shared__ uint32_t start[kOrderBuckets];
-  const uint64_t n = (uint64_t)g.ntiles * g.NX;
-  const uint32_t G = gridDim.x, w = blockIdx.x, tid = threadIdx.x;
-  const uint64_t e0 = (uint64_t)w * kScanRange;
+  constexpr uint32_t TPT = kScanItems / NX;
+  const uint32_t G = gridDim.x, w = blockIdx.x, tid = threadIdx.x, t0 = w * (kScanRange / NX);
   if (hdr && w == 0 && tid == 0) hdr->counted = stamp;
   // segments of the workgroups before this one
-  uint32_t c = 0;
-  for (uint32_t v = tid; v < w; v += kScanThreads) c += part[(size_t)v * (1 + kOrderBuckets)];
-  uint32_t carry;
-  block_exclusive(c, wsum, &carry);
-  // this range's segments, kScanItems consecutive per thread
-  uint32_t v[kScanItems];
-  uint32_t s = 0;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint64_t e = e0 + (uint64_t)tid * kScanItems + k;
-    v[k] = 0;
-    if (e < n) v[k] = counts[(uint32_t)(e % g.NX) * g.ntiles + (uint32_t)(e / g.NX)];
-    s += v[k];
-  }
-  uint32_t total;
-  uint32_t run = carry + block_exclusive(s, wsum, &total);
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint64_t e = e0 + (uint64_t)tid * kScanItems + k;
-    if (e < n) {
-      const uint32_t t = (uint32_t)(e / g.NX), x = (uint32_t)(e % g.NX);
-      offsets[e] = run;
-      cursors[(x * g.ntiles + t) * kCursorPad] = run;
-    }
-    run += v[k];
-  }
-  if (w == G - 1 && tid == 0) offsets[n] = carry + total;
-  if (!with_order) return;
+  uint32_t before = 0;
+  for (uint32_t v = tid; v < w; v += kScanThreads) before += part[(size_t)v * (1 + kOrderBuckets)];
+  uint32_t carry, cnt[TPT];
+  block_exclusive(before, wsum, &carry);
+  scan_tiles<NX, TPT>(counts, g, t0, offsets, cursors, wsum, carry, cnt);
+  if (w == G - 1 && tid == 0) offsets[(uint64_t)g.ntiles * NX] = carry;
   // start of this workgroup's tiles in each size class: all heavier classes, then earlier workgroups' tiles of
   // the same class
   uint32_t tot = 0, pre = 0;
@@ -637,11 +641,10 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(const uint32_t* __r
   const uint32_t base = block_exclusive(tid < kOrderBuckets ? tot : 0u, wsum, &all);
   if (tid < kOrderBuckets) start[tid] = base + pre;
   __syncthreads();
-  const uint32_t t0 = (uint32_t)(e0 / g.NX), t1 = (uint32_t)std::min<uint64_t>((e0 + kScanRange) / g.NX, g.ntiles);
-  for (uint32_t t = t0 + tid; t < t1; t += kScanThreads) {
-    uint32_t cnt = 0;
-    for (uint32_t x = 0; x < g.NX; ++x) cnt += counts[x * g.ntiles + t];
-    order[atomicAdd(&start[kOrderBuckets - 1 - size_class(cnt)], 1u)] = t;
+#pragma unroll
+  for (uint32_t k = 0; k < TPT; ++k) {
+    const uint32_t t = t0 + k * kScanThreads + tid;
+    if (t < g.ntiles) order[atomicAdd(&start[kOrderBuckets - 1 - size_class(cnt[k])], 1u)] = t;
   }
 }
 
@@ -1205,11 +1208,10 @@ template <int C, bool IDX>
 static hipError_t launch_scatter(const Geom& g, const wt_fragments& f, int vec, uint32_t* cursors,
                                  uint32_t* head, uint32_t* tail, WsHeader* hdr,
                                  unsigned long long cstamp, uint32_t cap, uint32_t nchunks, hipStream_t s) {
-  if (g.kper == 4)
-    return launch_scatter_t<C, IDX, 4, 1024>(g, f, vec, cursors, head, tail, hdr, cstamp, cap, nchunks, s);
-  if (g.sthreads == 512)
-    return launch_scatter_t<C, IDX, kPer, 512>(g, f, vec, cursors, head, tail, hdr, cstamp, cap, nchunks, s);
-  return launch_scatter_t<C, IDX, kPer, 1024>(g, f, vec, cursors, head, tail, hdr, cstamp, cap, nchunks, s);
+  auto run = g.kper == 4         ? launch_scatter_t<C, IDX, 4, 1024>
+             : g.sthreads == 512 ? launch_scatter_t<C, IDX, kPer, 512>
+                                 : launch_scatter_t<C, IDX, kPer, 1024>;
+  return run(g, f, vec, cursors, head, tail, hdr, cstamp, cap, nchunks, s);
 }
 
 hipError_t launch_bin_count(const Geom& g, const wt_fragments& f, void* ws, const Layout& l, hipStream_t s) {
@@ -1221,9 +1223,8 @@ hipError_t launch_bin_count(const Geom& g, const wt_fragments& f, void* ws, cons
   unsigned long long* dropped = &hdr->dropped;
   const uint64_t ncount = (uint64_t)g.NX * g.ntiles;
   // reset the header and zero the tile counts (kernels, not memsets: safe inside captured graphs)
-  hipLaunchKernelGGL(k_header_reset, dim3(1), dim3(1), 0, s, hdr);
-  hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)std::min<uint64_t>((ncount + 255) / 256, 4096)), dim3(256), 0, s,
-                     counts, ncount, 0u);
+  hipLaunchKernelGGL(k_count_reset, dim3((unsigned)std::min<uint64_t>((ncount + 255) / 256, 4096)), dim3(256), 0, s,
+                     hdr, counts, ncount);
   const uint32_t F = (uint32_t)f.count;
   const uint32_t nchunks = (uint32_t)(((uint64_t)F + g.chunk - 1) / g.chunk);
   const int vec = aligned16(f.pixel);
@@ -1250,16 +1251,18 @@ hipError_t launch_bin_count(const Geom& g, const wt_fragments& f, void* ws, cons
   }
   const unsigned long long cstamp = count_stamp(g, l, f);
   const uint64_t nseg = (uint64_t)g.NX * g.ntiles;
-  if (nseg <= 2 * (uint64_t)kScanRange) {
+  if (g.NX == kClasses && g.ntiles <= kScanTiles * kScanThreads) {
     hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanThreads), 0, s, counts, g, offsets, cursors,
                        (uint32_t*)(b + l.order), 1, g.two ? nullptr : hdr, cstamp);
   } else {
-    // many segments (two-level and global-atomic binnings): the scan over several workgroups
+    // many tiles (two-level and global-atomic binnings): the scan over several workgroups
     uint32_t* part = (uint32_t*)(b + l.scan);
     const uint32_t G = (uint32_t)((nseg + kScanRange - 1) / kScanRange);
-    hipLaunchKernelGGL(k_scan_part, dim3(G), dim3(kScanThreads), 0, s, counts, g, part);
-    hipLaunchKernelGGL(k_scan_apply, dim3(G), dim3(kScanThreads), 0, s, counts, g, part, offsets, cursors,
-                       (uint32_t*)(b + l.order), 1, g.two ? nullptr : hdr, cstamp);
+    auto sum = g.NX == 1 ? k_scan_part<1> : k_scan_part<kClasses>;
+    auto apply = g.NX == 1 ? k_scan_apply<1> : k_scan_apply<kClasses>;
+    hipLaunchKernelGGL(sum, dim3(G), dim3(kScanThreads), 0, s, counts, g, part);
+    hipLaunchKernelGGL(apply, dim3(G), dim3(kScanThreads), 0, s, counts, g, part, offsets, cursors,
+                       (uint32_t*)(b + l.order), g.two ? nullptr : hdr, cstamp);
   }
   if (g.two) {
     // first level: per-class super-tile counts, and their segments and cursors
@@ -1293,39 +1296,24 @@ hipError_t launch_bin_scatter(const Geom& g, const wt_fragments& f, void* ws, co
     auto k = g.C == 1 ? (record_index ? k_scatter_serial<1, true> : k_scatter_serial<1, false>)
                       : (record_index ? k_scatter_serial<3, true> : k_scatter_serial<3, false>);
     hipLaunchKernelGGL(k, dim3(1), dim3(64), 0, s, f, g, cursors, offsets, head, tail, hdr, cstamp);
-    hipLaunchKernelGGL(k_seal, dim3(1), dim3(1024), 0, s, hdr, cursors, offsets, g.NX, g.ntiles, cstamp, stamp);
-    return hipGetLastError();
-  }
-  if (!g.two) {
-    if (F > 0) {
-      if (g.C == 1)
-        e = record_index ? launch_scatter<1, true>(g, f, vec, cursors, head, tail, hdr, cstamp, cap, nchunks, s)
-                         : launch_scatter<1, false>(g, f, vec, cursors, head, tail, hdr, cstamp, cap, nchunks, s);
-      else
-        e = record_index ? launch_scatter<3, true>(g, f, vec, cursors, head, tail, hdr, cstamp, cap, nchunks, s)
-                         : launch_scatter<3, false>(g, f, vec, cursors, head, tail, hdr, cstamp, cap, nchunks, s);
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_seal, dim3(1), dim3(1024), 0, s, hdr, cursors, offsets, g.NX, g.ntiles, cstamp, stamp);
+    launch_seal(hdr, cursors, offsets, g.NX, g.ntiles, cstamp, stamp, s);
     return hipGetLastError();
   }
   // two levels: the stream into super-tiles (first-level arrays), then each super-tile into its tiles
-  const Geom gs = super_geom(g);
-  uint32_t* cursors1 = (uint32_t*)(b + l.cursors1);
-  uint32_t* head1 = (uint32_t*)(b + l.heads1);
-  uint32_t* tail1 = (uint32_t*)(b + l.tails1);
-  const uint32_t* offsets1 = (const uint32_t*)(b + l.offsets1);
-  const unsigned long long stamp1 = level1_stamp(stamp);
+  const Geom gs = g.two ? super_geom(g) : g;
+  uint32_t* cursors1 = g.two ? (uint32_t*)(b + l.cursors1) : cursors;
+  uint32_t* head1 = g.two ? (uint32_t*)(b + l.heads1) : head;
+  uint32_t* tail1 = g.two ? (uint32_t*)(b + l.tails1) : tail;
+  const uint32_t* offsets1 = g.two ? (const uint32_t*)(b + l.offsets1) : offsets;
+  const unsigned long long stamp1 = g.two ? level1_stamp(stamp) : stamp;
   if (F > 0) {
-    if (g.C == 1)
-      e = record_index ? launch_scatter<1, true>(gs, f, vec, cursors1, head1, tail1, hdr, cstamp, cap, nchunks, s)
-                       : launch_scatter<1, false>(gs, f, vec, cursors1, head1, tail1, hdr, cstamp, cap, nchunks, s);
-    else
-      e = record_index ? launch_scatter<3, true>(gs, f, vec, cursors1, head1, tail1, hdr, cstamp, cap, nchunks, s)
-                       : launch_scatter<3, false>(gs, f, vec, cursors1, head1, tail1, hdr, cstamp, cap, nchunks, s);
+    auto scatter = g.C == 1 ? (record_index ? launch_scatter<1, true> : launch_scatter<1, false>)
+                            : (record_index ? launch_scatter<3, true> : launch_scatter<3, false>);
+    e = scatter(gs, f, vec, cursors1, head1, tail1, hdr, cstamp, cap, nchunks, s);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_seal, dim3(1), dim3(1024), 0, s, hdr, cursors1, offsets1, gs.NX, g.nsuper, cstamp, stamp1);
+  launch_seal(hdr, cursors1, offsets1, gs.NX, gs.ntiles, cstamp, stamp1, s);
+  if (!g.two) return hipGetLastError();
   auto split = [&](auto kern, uint32_t rb, uint32_t per) -> hipError_t {
     const size_t lds = (size_t)kSplitThreads * per * rb;
     if (lds > 65536) {
