@@ -154,7 +154,7 @@ wt_status wt_bin(const wt_frame_desc* desc, const wt_fragments* frags, void* ws,
   WT_TRY(check_lds(g));
   wt::Layout l;
   WT_TRY(check_ws(g, ws, ws_bytes, frags->count, &l));
-  hipError_t e = wt::launch_bin(g, *frags, ws, l, false, stream);
+  hipError_t e = wt::launch_bin(g, *frags, ws, l, wt::GradOut{}, stream);
   if (e != hipSuccess) return hip_fail(e, "wt_bin");
   return WT_OK;
 }
@@ -180,7 +180,7 @@ wt_status wt_bin_scatter(const wt_frame_desc* desc, const wt_fragments* frags, v
   WT_TRY(check_lds(g));
   wt::Layout l;
   WT_TRY(check_ws(g, ws, ws_bytes, frags->count, &l));
-  hipError_t e = wt::launch_bin_scatter(g, *frags, ws, l, false, stream);
+  hipError_t e = wt::launch_bin_scatter(g, *frags, ws, l, wt::GradOut{}, stream);
   if (e != hipSuccess) return hip_fail(e, "wt_bin_scatter");
   return WT_OK;
 }
@@ -258,7 +258,7 @@ wt_status wt_render(const wt_frame_desc* desc, const wt_fragments* frags, const 
   WT_TRY(check_lds(g));
   wt::Layout l;
   WT_TRY(check_ws(g, ws, ws_bytes, frags->count, &l));
-  hipError_t e = wt::launch_bin(g, *frags, ws, l, false, stream);
+  hipError_t e = wt::launch_bin(g, *frags, ws, l, wt::GradOut{}, stream);
   if (e != hipSuccess) return hip_fail(e, "wt_render (bin)");
   e = wt::launch_render(g, wt::binned_view(g, l, ws, false), bg_rgb, coeffs, out, stream);
   if (e != hipSuccess) return hip_fail(e, "wt_render");
@@ -280,7 +280,7 @@ wt_status wt_render_noalloc(const wt_frame_desc* desc, const wt_fragments* frags
   WT_TRY(scratch_here(&ws));
   wt::Layout l;
   WT_TRY(check_ws(g, ws, kScratchBytes, frags->count, &l));
-  hipError_t e = wt::launch_bin(g, *frags, ws, l, false, stream);
+  hipError_t e = wt::launch_bin(g, *frags, ws, l, wt::GradOut{}, stream);
   if (e != hipSuccess) return hip_fail(e, "wt_render_noalloc (bin)");
   e = wt::launch_render(g, wt::binned_view(g, l, ws, false), bg_rgb, coeffs, out, stream);
   if (e != hipSuccess) return hip_fail(e, "wt_render_noalloc");
@@ -340,10 +340,10 @@ wt_status wt_backward(const wt_frame_desc* desc, const wt_fragments* frags, cons
                 wt::lds_backward_bytes(g));
   wt::Layout l;
   WT_TRY(check_ws(g, ws, ws_bytes, frags->count, &l));
-  hipError_t e = wt::launch_bin(g, *frags, ws, l, true, stream);
+  hipError_t e = wt::launch_bin(g, *frags, ws, l, wt::GradOut{true, grad_alpha, grad_rgb}, stream);
   if (e != hipSuccess) return hip_fail(e, "wt_backward (bin)");
   e = wt::launch_backward(g, wt::binned_view(g, l, ws, true), coeffs, accum, bg_rgb, grad_out, grad_alpha, grad_rgb,
-                          frags->count, stream);
+                          stream);
   if (e == hipErrorNotSupported) return fail(WT_ERR_UNSUPPORTED, "wt_backward: not available for this frame");
   if (e != hipSuccess) return hip_fail(e, "wt_backward");
   return WT_OK;

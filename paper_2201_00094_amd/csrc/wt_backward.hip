@@ -16,215 +16,263 @@
 // which needs O(M) work per pixel and O(1) per fragment for any rank.
 #include <algorithm>
 
-#include "wt_common.h"
+#include "wt_tile.h"
 
 namespace wt {
 
-constexpr int kBwdThreads = 512;
+// Record i of a binning made with stream indices (alpha and plain colour).
+template <int C>
+struct GradRecord {
+  Head<C> h;  // al: alpha
+  float rgb[3];
+  uint32_t src;
+};
 
-__device__ __forceinline__ float clamp01_b(float x) { return fminf(fmaxf(x, 0.f), 1.f); }
-
-// Cell value Abar_j of one pixel/channel whose rows are TP floats apart: read directly (cells) or
-// synthesised from the coefficients.
-__device__ __forceinline__ float cell_value(const float* cf, uint32_t TP, const Geom& g, uint32_t j, bool cells) {
-  if (cells) return cf[j * TP];
-  float A = cf[0];
-  for (uint32_t n = 0; n <= g.rank; ++n) {
-    const uint32_t k = j >> (g.L - n);
-    const float d = cf[((1u << n) + k) * TP];
-    A += ((j >> (g.L - 1 - n)) & 1u) ? -d : d;
-  }
-  return A;
+template <int C, bool NT>
+__device__ __forceinline__ bool load_grad(const Binned& b, uint32_t i, GradRecord<C>& f) {
+  const uint32_t* t = b.tail + (uint64_t)i * b.DT;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) f.rgb[q] = __uint_as_float(load_word<NT>(t + q));
+  f.src = load_word<NT>(t + 3);
+  return load_head<C, NT>(b, i, f.h);
 }
 
-template <int M>
-__device__ __forceinline__ void synth_fixed_b(float* cf, uint32_t TP) {
-  float v[M];
-  v[0] = cf[0];
+// What the second pass needs of a fragment: where it is (pixel, cell, offsets), its alpha, and per channel
+// v sum_q g_q c_q and alpha v.
+template <int C>
+struct GradKept {
+  uint32_t key, src;  // pixel | cell << 16; the stream index
+  float t, omt, al[C], vg[C], av[C];
+};
+
+// Fragments whose GradKept a thread holds in registers between the passes: the second pass reads nothing for them and
+// takes no exponential. (512x512, 32 fragments per pixel: gradient with its binning 436 us at four, 416 at eight, 388 at
+// sixteen, all that 128 registers hold; the kernel before, 512 threads and one record in flight per thread, with the
+// gradients cleared first, 537. Writing the gradients at their scattered stream positions is 140 of the kernel's 265 us;
+// as non-temporal stores three channels take 4.5 ms instead of 2.1, 1024x768.)
+template <int C>
+constexpr int grad_kept() { return C == 1 ? 16 : 8; }
+
+struct GradTile {
+  double* adj;        // [C * M][TP] cell adjoints, then their suffix sums
+  const float* cell;  // [C * M][TP] cell values, or coefficients where M > 32
+  const float* grad;  // [3][TP] dL/dout
+  const float* back;  // [C][TP] background transmittance
+  const uint32_t* lb; // [2][TP] depth bounds, or null
+};
+
+// First pass, one fragment: its visibility, its terms of the cell adjoints, and what the second pass needs.
+template <int C, bool CELLS>
+__device__ __forceinline__ void grad_first(const GradTile& s, const Geom& g, const GradRecord<C>& f, bool add,
+                                           GradKept<C>& k) {
+  const uint32_t TP = g.tile_px, lp = f.h.lp;
+  uint32_t j;
+  cell_coord(f.h.x, s.lb, TP, lp, g.M, j, k.t, k.omt);
+  k.key = lp | j << 16;
+  k.src = f.src;
+  const float gq[3] = {s.grad[lp], s.grad[TP + lp], s.grad[2 * TP + lp]};
 #pragma unroll
-  for (int s = 1; s < M; s <<= 1) {
+  for (int c = 0; c < C; ++c) {
+    const float* cf = s.cell + (c * g.M) * TP + lp;
+    const float hi = CELLS ? cf[j * TP] : cell_from_coeffs(cf, TP, g, j);
+    const uint32_t jb = j ? j - 1 : 0u;
+    const float below = CELLS ? cf[jb * TP] : cell_from_coeffs(cf, TP, g, jb);
+    const float v = __expf(-fmaf(k.t, hi, k.omt * (j ? below : 0.f)));
+    const float alc = alpha_clamped(f.h.al[c]);
+    const float gc = (C == 1) ? (gq[0] * f.rgb[0] + gq[1] * f.rgb[1] + gq[2] * f.rgb[2]) : gq[c] * f.rgb[c];
+    k.al[c] = f.h.al[c];
+    k.vg[c] = v * gc;
+    k.av[c] = alc * v;
+    if (add) {
+      const float sg = alc * v * gc;
+      double* a = s.adj + (c * g.M) * TP + lp;
+      if (j) atomicAdd(a + (j - 1) * TP, (double)(-sg * k.omt));
+      atomicAdd(a + j * TP, (double)(-sg * k.t));
+    }
+  }
+}
+
+// Second pass, one fragment: its gradients, written at its stream position.
+template <int C>
+__device__ __forceinline__ void grad_second(const GradTile& s, const Geom& g, const float (&bg)[3],
+                                            const GradKept<C>& k, float* __restrict__ grad_alpha,
+                                            float* __restrict__ grad_rgb) {
+  const uint32_t TP = g.tile_px, lp = k.key & 0xffffu, j = k.key >> 16;
+  const uint64_t src = k.src;
+  const float gq[3] = {s.grad[lp], s.grad[TP + lp], s.grad[2 * TP + lp]};
+  float out[3];
 #pragma unroll
-    for (int k = s - 1; k >= 0; --k) {
-      const float d = cf[(s + k) * TP];
-      const float a = v[k];
-      v[2 * k] = a + d;
-      v[2 * k + 1] = a - d;
+  for (int c = 0; c < C; ++c) {
+    const double* S = s.adj + (c * g.M) * TP + lp;
+    const double Sj = S[j * TP];
+    const double Sj1 = (j + 1 < g.M) ? S[(j + 1) * TP] : 0.0;
+    const float through_cells = (float)((double)k.omt * (Sj - Sj1) + Sj1);
+    const float gbg = (C == 1) ? (gq[0] * bg[0] + gq[1] * bg[1] + gq[2] * bg[2]) : gq[c] * bg[c];
+    const float dLda = through_cells - gbg * s.back[c * TP + lp];
+    const bool inside = k.al[c] > 0.f && k.al[c] < kAlphaMax;
+    grad_alpha[src * C + c] = inside ? k.vg[c] + dLda / (1.f - alpha_clamped(k.al[c])) : 0.f;
+    if (C == 1) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) out[q] = gq[q] * k.av[c];
+    } else {
+      out[c] = gq[c] * k.av[c];
     }
   }
 #pragma unroll
-  for (int j = 0; j < M; ++j) cf[j * TP] = v[j];
+  for (int q = 0; q < 3; ++q) grad_rgb[src * 3 + q] = out[q];
 }
 
-__device__ __forceinline__ void synth_b(float* cf, uint32_t TP, uint32_t M) {
-  switch (M) {
-    case 2: synth_fixed_b<2>(cf, TP); break;
-    case 4: synth_fixed_b<4>(cf, TP); break;
-    case 8: synth_fixed_b<8>(cf, TP); break;
-    case 16: synth_fixed_b<16>(cf, TP); break;
-    default: synth_fixed_b<32>(cf, TP); break;
-  }
-}
-
-__global__ void k_zero_f32(float* __restrict__ p, uint64_t n) {
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    p[i] = 0.f;
-}
-
-template <int C>
-struct BFrag {
-  uint32_t lp, src;
-  float x, al[C], rgb[3];
-};
-
-// Record i of a binning made with stream indices; false for a NaN fragment.
-template <int C>
-__device__ __forceinline__ bool load_bfrag(const Binned& b, uint32_t i, BFrag<C>& f) {
-  const uint32_t* r = b.head + (uint64_t)i * b.DH;
-  const uint32_t* rt = b.tail + (uint64_t)i * b.DT;
-  f.lp = r[0];
-  f.x = __uint_as_float(r[1]);
-  bool bad = isnan(f.x);
+// Cells of one pixel and channel from its stored row, or its coefficients as they are (M > 32), into column lc.
+template <typename TS, int M>
+__device__ __forceinline__ void grad_cells(const TS* row, uint32_t c, float* lc, uint32_t TP) {
+  float v[M];
 #pragma unroll
-  for (int c = 0; c < C; ++c) {
-    f.al[c] = __uint_as_float(r[2 + c]);
-    bad |= isnan(f.al[c]);
+  for (int m = 0; m < M; ++m) v[m] = 0.f;
+  if (row) {
+    if constexpr (is_e5<TS>::value) {
+      uint32_t w[M];
+      load_row<uint32_t, M>((const uint32_t*)row, w);
+#pragma unroll
+      for (int m = 0; m < M; ++m) v[m] = e5_sign(m) * e5_unpack(w[m], c);
+    } else {
+      TS s[M];
+      load_row<TS, M>(row, s);
+#pragma unroll
+      for (int m = 0; m < M; ++m) v[m] = widen<TS>(s[m]);
+    }
+    synth_regs<M>(v);
   }
 #pragma unroll
-  for (int q = 0; q < 3; ++q) f.rgb[q] = __uint_as_float(rt[q]);
-  f.src = rt[3];
-  return !bad;
+  for (int m = 0; m < M; ++m) lc[m * TP] = v[m];
 }
 
-// LDS rows of TP values: ladj [C*M] FP64 cell adjoints, then their suffix sums; lc [C*M] FP32 cell values;
-// lg [3] dL/dout; lT [C] background transmittance.
+// LDS rows of TP values: cell adjoints [C*M] FP64, cell values [C*M] FP32, dL/dout [3], background transmittance [C],
+// depth bounds [2].
 template <int C, typename TS, bool CELLS>
-__global__ __launch_bounds__(kBwdThreads) void k_backward(Binned b, Geom g, const TS* __restrict__ coeffs,
-                                                          const float* __restrict__ accum, float bg0, float bg1,
-                                                          float bg2, const float* __restrict__ grad_out,
-                                                          float* __restrict__ grad_alpha,
-                                                          float* __restrict__ grad_rgb) {
+__global__ __launch_bounds__(kTileThreads) void k_backward(Binned b, Geom g, const TS* __restrict__ coeffs,
+                                                           const float* __restrict__ accum, float bg0, float bg1,
+                                                           float bg2, const float* __restrict__ grad_out,
+                                                           float* __restrict__ grad_alpha,
+                                                           float* __restrict__ grad_rgb) {
   extern __shared__ double smem_b[];
-  const uint32_t TP = g.tile_px, per = C * g.M;
+  constexpr int K = grad_kept<C>(), U = 4;
+  constexpr bool kNT = last_read_nt<C>();
+  const uint32_t TP = g.tile_px, per = C * g.M, T = blockDim.x;
   double* ladj = smem_b;
   float* lc = (float*)(ladj + per * TP);
   float* lg = lc + per * TP;
   float* lT = lg + 3 * TP;
-  uint32_t* lb = g.tight ? (uint32_t*)(lT + C * TP) : nullptr;  // per-pixel depth bounds
-  uint32_t t;
-  if (!binned_ok(b, g, t)) return;
-  const uint32_t x0 = (t % g.tilesX) * g.TW, y0 = (t / g.tilesX) * g.TH;
-  for (uint32_t lp = threadIdx.x; lp < TP; lp += blockDim.x) {
-    const uint32_t px = x0 + (lp & (g.TW - 1)), py = y0 + (lp >> g.lTW);
-    const bool in = px < g.W && py < g.H;
-    const uint64_t p = in ? (uint64_t)py * g.W + px : 0;
-    for (uint32_t e = 0; e < per; ++e) {
-      if constexpr (is_e5<TS>::value) {
-        // packed storage (three channels): word [p][m] holds the magnitudes of coefficient m of every channel
-        const uint32_t c = e / g.M, m = e - c * g.M;
-        const float v = in ? e5_unpack(((const uint32_t*)coeffs)[p * g.M + m], c) : 0.f;
-        lc[e * TP + lp] = m ? -v : v;
-      } else {
-        lc[e * TP + lp] = in ? widen<TS>(coeffs[p * per + e]) : 0.f;
-      }
-      ladj[e * TP + lp] = 0.0;
-    }
+  uint32_t* lb = g.tight ? (uint32_t*)(lT + C * TP) : nullptr;
+  uint32_t tile;
+  if (!binned_ok(b, g, tile)) return;
+  const TileRef r = tile_ref(g, b, tile);
+  const float bg[3] = {bg0, bg1, bg2};
+  for (uint32_t e = threadIdx.x; e < per * TP; e += T) ladj[e] = 0.0;
+  for (uint32_t lp = threadIdx.x; lp < TP; lp += T) {
+    uint64_t p;
+    const bool in = tile_pixel(g, r, lp, p);
     for (uint32_t q = 0; q < 3; ++q) lg[q * TP + lp] = in ? grad_out[p * 3 + q] : 0.f;
     for (uint32_t c = 0; c < C; ++c)
       lT[c * TP + lp] = in ? __expf(-accum[p * g.AW + (C == 1 ? 3 : 4 + c)]) : 0.f;
   }
-  __syncthreads();
-  if (CELLS)
-    for (uint32_t q = threadIdx.x; q < TP * C; q += blockDim.x) {
-      const uint32_t c = q / TP, lp = q - c * TP;
-      synth_b(lc + (c * g.M) * TP + lp, TP, g.M);
-    }
-  __syncthreads();
-  const uint32_t beg = b.offsets[t * g.NX], end = b.offsets[(t + 1) * g.NX];
-  if (lb) {
-    // depth bounds over the tile's valid fragments (section 2.1, step 1): u32 extremes of the FP32 bit patterns
-    for (uint32_t lp = threadIdx.x; lp < TP; lp += blockDim.x) {
-      lb[lp] = __float_as_uint(1.f);
-      lb[TP + lp] = 0u;
-    }
-    __syncthreads();
-    for (uint32_t i = beg + threadIdx.x; i < end; i += blockDim.x) {
-      BFrag<C> f;
-      if (!load_bfrag<C>(b, i, f)) continue;
-      const uint32_t xb = __float_as_uint(clamp01_b(f.x));
-      atomicMin(lb + f.lp, xb);
-      atomicMax(lb + TP + f.lp, xb);
-    }
-    __syncthreads();
+  if constexpr (CELLS) {
+    with_m(g, [&](auto mm) {
+      constexpr int M = decltype(mm)::value;
+      for (uint32_t q = threadIdx.x; q < TP * C; q += T) {
+        const uint32_t c = C == 1 ? 0 : q / TP, lp = q - c * TP;
+        uint64_t p;
+        const bool in = tile_pixel(g, r, lp, p);
+        // packed storage: the three channels share the pixel's row of words
+        const TS* row = in ? coeffs + (is_e5<TS>::value ? p * M : (p * C + c) * M) : nullptr;
+        grad_cells<TS, M>(row, c, lc + (c * M) * TP + lp, TP);
+      }
+    });
+  } else {
+    coeff_tile_io<C, TS, 0>(g, r, lc, const_cast<TS*>(coeffs));
   }
-  // pass 1: cell adjoints (one thread in binned order under WT_DETERMINISTIC)
-  const uint32_t i1 = g.serial ? (threadIdx.x ? end : beg) : beg + threadIdx.x, di1 = g.serial ? 1 : blockDim.x;
-  for (uint32_t i = i1; i < end; i += di1) {
-    BFrag<C> f;
-    if (!load_bfrag<C>(b, i, f)) continue;
-    uint32_t j;
-    float tt, omt;
-    cell_coord(f.x, lb, TP, f.lp, g.M, j, tt, omt);
-    const float gq[3] = {lg[f.lp], lg[TP + f.lp], lg[2 * TP + f.lp]};
+  __syncthreads();
+  if (lb) bounds_tile<C>(b, g, r, lb);
+  const GradTile s{ladj, lc, lg, lT, lb};
+  const uint32_t rest = g.serial ? r.end : r.end - min(r.end - r.beg, (uint32_t)K * T);  // kept from here on
+  const uint32_t i0 = rest + threadIdx.x;
+  // pass 1: cell adjoints
+  GradKept<C> kept[K];
+  bool ok[K];
+  GradRecord<C> f[U];
+  if (serial_records(g, r.beg, r.end, [&](uint32_t i) {
+        GradRecord<C> one;
+        GradKept<C> k;
+        if (load_grad<C, false>(b, i, one)) grad_first<C, CELLS>(s, g, one, true, k);
+      })) {
+  } else {
+    for_records<U>(
+        r.beg, rest, [&](uint32_t i, int u) { return load_grad<C, false>(b, i, f[u]); },
+        [&](int u) {
+          GradKept<C> k;
+          grad_first<C, CELLS>(s, g, f[u], true, k);
+        });
+  }
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      const float* cf = lc + (c * g.M) * TP + f.lp;
-      const float hi = cell_value(cf, TP, g, j, CELLS);
-      const float lo = j ? cell_value(cf, TP, g, j - 1, CELLS) : 0.f;
-      const float v = __expf(-fmaf(tt, hi, omt * lo));
-      const float alc = alpha_clamped(f.al[c]);
-      const float gc = (C == 1) ? (gq[0] * f.rgb[0] + gq[1] * f.rgb[1] + gq[2] * f.rgb[2]) : gq[c] * f.rgb[c];
-      const float s = alc * v * gc;
-      double* adj = ladj + (c * g.M) * TP + f.lp;
-      if (j) atomicAdd(adj + (j - 1) * TP, (double)(-s * omt));
-      atomicAdd(adj + j * TP, (double)(-s * tt));
+  for (int k = 0; k < K; ++k) {
+    ok[k] = false;
+    kept[k].src = kNoRecord;
+  }
+#pragma unroll
+  for (int k0 = 0; k0 < K; k0 += U) {
+    if (rest + k0 * T >= r.end) break;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t i = i0 + (k0 + u) * T;
+      ok[k0 + u] = load_grad<C, kNT>(b, min(i, r.end - 1), f[u]) && i < r.end;
+      if (i < r.end) kept[k0 + u].src = f[u].src;
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (ok[k0 + u]) grad_first<C, CELLS>(s, g, f[u], true, kept[k0 + u]);
   }
   __syncthreads();
   // suffix sums of the cell adjoints
-  for (uint32_t q = threadIdx.x; q < TP * C; q += blockDim.x) {
-    const uint32_t c = q / TP, lp = q - c * TP;
+  for (uint32_t q = threadIdx.x; q < TP * C; q += T) {
+    const uint32_t c = C == 1 ? 0 : q / TP, lp = q - c * TP;
     double* adj = ladj + (c * g.M) * TP + lp;
     double run = 0.0;
+#pragma unroll 8
     for (int m = (int)g.M - 1; m >= 0; --m) {
       run += adj[m * TP];
       adj[m * TP] = run;
     }
   }
   __syncthreads();
-  // pass 2: per-fragment gradients, written at the fragment's stream position
-  const float bg[3] = {bg0, bg1, bg2};
-  for (uint32_t i = beg + threadIdx.x; i < end; i += blockDim.x) {
-    BFrag<C> f;
-    if (!load_bfrag<C>(b, i, f)) continue;
-    const uint64_t src = f.src;
-    uint32_t j;
-    float tt, omt;
-    cell_coord(f.x, lb, TP, f.lp, g.M, j, tt, omt);
-    const float gq[3] = {lg[f.lp], lg[TP + f.lp], lg[2 * TP + f.lp]};
+  // pass 2: per-fragment gradients; a dropped fragment's are zero
+  auto dropped = [&](uint32_t at) {
+    const uint64_t src = at;
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      const float* cf = lc + (c * g.M) * TP + f.lp;
-      const float hi = cell_value(cf, TP, g, j, CELLS);
-      const float lo = j ? cell_value(cf, TP, g, j - 1, CELLS) : 0.f;
-      const float v = __expf(-fmaf(tt, hi, omt * lo));
-      const float alc = alpha_clamped(f.al[c]);
-      const double* S = ladj + (c * g.M) * TP + f.lp;
-      const double Sj = S[j * TP];
-      const double Sj1 = (j + 1 < g.M) ? S[(j + 1) * TP] : 0.0;
-      const float through_cells = (float)((double)omt * (Sj - Sj1) + Sj1);
-      const float gbg = (C == 1) ? (gq[0] * bg[0] + gq[1] * bg[1] + gq[2] * bg[2]) : gq[c] * bg[c];
-      const float dLda = through_cells - gbg * lT[c * TP + f.lp];
-      const float gc = (C == 1) ? (gq[0] * f.rgb[0] + gq[1] * f.rgb[1] + gq[2] * f.rgb[2]) : gq[c] * f.rgb[c];
-      const bool inside = f.al[c] > 0.f && f.al[c] < kAlphaMax;
-      grad_alpha[src * C + c] = inside ? v * gc + dLda / (1.f - alc) : 0.f;
-      if (C == 1) {
+    for (int c = 0; c < C; ++c) grad_alpha[src * C + c] = 0.f;
 #pragma unroll
-        for (int q = 0; q < 3; ++q) grad_rgb[src * 3 + q] = gq[q] * alc * v;
-      } else {
-        grad_rgb[src * 3 + c] = gq[c] * alc * v;
-      }
-    }
+    for (int q = 0; q < 3; ++q) grad_rgb[src * 3 + q] = 0.f;
+  };
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    if (ok[k])
+      grad_second<C>(s, g, bg, kept[k], grad_alpha, grad_rgb);
+    else if (kept[k].src != kNoRecord)
+      dropped(kept[k].src);
   }
+  for_records<U, true>(
+      r.beg, rest,
+      [&](uint32_t i, int u) {
+        if (!load_grad<C, kNT>(b, i, f[u])) f[u].h.lp = kNoRecord;
+        return true;
+      },
+      [&](int u) {
+        if (f[u].h.lp == kNoRecord) {
+          dropped(f[u].src);
+          return;
+        }
+        GradKept<C> k;
+        grad_first<C, CELLS>(s, g, f[u], false, k);
+        grad_second<C>(s, g, bg, k, grad_alpha, grad_rgb);
+      });
 }
 
 size_t lds_backward_bytes(const Geom& g) {
@@ -232,49 +280,19 @@ size_t lds_backward_bytes(const Geom& g) {
 }
 
 hipError_t launch_backward(const Geom& g, const Binned& b, const void* coeffs, const float* accum, const float* bg,
-                           const float* grad_out, float* grad_alpha, float* grad_rgb, uint64_t count,
-                           hipStream_t s) {
-  if (count) {
-    const unsigned za = (unsigned)std::min<uint64_t>((count * g.C + 255) / 256, 8192);
-    const unsigned zr = (unsigned)std::min<uint64_t>((count * 3 + 255) / 256, 8192);
-    hipLaunchKernelGGL(k_zero_f32, dim3(za), dim3(256), 0, s, grad_alpha, count * g.C);
-    hipLaunchKernelGGL(k_zero_f32, dim3(zr), dim3(256), 0, s, grad_rgb, count * 3);
-  }
+                           const float* grad_out, float* grad_alpha, float* grad_rgb, hipStream_t s) {
   const size_t lds = lds_backward_bytes(g);
   if (lds > kLdsBytes) return hipErrorNotSupported;
-  hipError_t err = hipSuccess;
-#define WT_BWD_LAUNCH(CC, TT, CELLS)                                                                              \
-  do {                                                                                                           \
-    auto k = k_backward<CC, TT, CELLS>;                                                                          \
-    if (lds > 65536) err = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
-    if (err == hipSuccess)                                                                                       \
-      hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(kBwdThreads), lds, s, b, g, (const TT*)coeffs, accum, bg[0],     \
-                         bg[1], bg[2], grad_out, grad_alpha, grad_rgb);                                          \
-  } while (0)
-#define WT_BWD_CELLS(CC, TT)               \
-  do {                                     \
-    if (g.M <= 32)                         \
-      WT_BWD_LAUNCH(CC, TT, true);         \
-    else                                   \
-      WT_BWD_LAUNCH(CC, TT, false);        \
-  } while (0)
-#define WT_BWD_TYPE(CC)                                   \
-  do {                                                    \
-    if (g.dtype == WT_F32) WT_BWD_CELLS(CC, float);       \
-    else if (g.dtype == WT_F16) WT_BWD_CELLS(CC, __half); \
-    else if (g.dtype == WT_BF16) WT_BWD_CELLS(CC, bf16_t); \
-    else if (CC == 3) WT_BWD_CELLS(CC, e5_t);             \
-    else err = hipErrorInvalidValue;                      \
-  } while (0)
-  if (g.C == 1)
-    WT_BWD_TYPE(1);
-  else
-    WT_BWD_TYPE(3);
-#undef WT_BWD_TYPE
-#undef WT_BWD_CELLS
-#undef WT_BWD_LAUNCH
-  if (err != hipSuccess) return err;
-  return hipGetLastError();
+  return dispatch(g, [&](auto cc, auto* tag) {
+    constexpr int C = decltype(cc)::value;
+    using TS = std::remove_pointer_t<decltype(tag)>;
+    auto k = g.M <= 32 ? k_backward<C, TS, true> : k_backward<C, TS, false>;
+    hipError_t err = prep(k, lds);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(g.tthreads), lds, s, b, g, (const TS*)coeffs, accum, bg[0], bg[1], bg[2],
+                       grad_out, grad_alpha, grad_rgb);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace wt

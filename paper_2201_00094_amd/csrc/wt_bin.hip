@@ -865,6 +865,16 @@ __device__ __forceinline__ void lds_get(const uint32_t* d, uint32_t* w) {
 // rounds of S records (S = stage, a power of two chosen by the host to fit the LDS).
 // PER = 4 is meant for two workgroups per compute unit (LDS <= 80 KB, <= 64 VGPRs at eight waves per SIMD):
 // one workgroup's loads and stores overlap the other's ranking and staging.
+// The gradient of a fragment that is in no tile (its pixel is out of range) is written where the binning leaves it out;
+// every other gradient is written by the tile kernel.
+template <int C>
+__device__ __forceinline__ void zero_gradient(const GradOut& go, uint64_t i) {
+#pragma unroll
+  for (int q = 0; q < C; ++q) go.alpha[C * i + q] = 0.f;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) go.rgb[3 * i + q] = 0.f;
+}
+
 // Refusal of a scatter that does not belong to the count before it, or whose stream puts more records in a segment
 // than were counted: nothing more is written and the binning is not sealed.
 __device__ __forceinline__ void scatter_refuse(WsHeader* hdr) {
@@ -879,7 +889,7 @@ __global__ __launch_bounds__(THREADS, PER == 4 ? 8 : (THREADS == 512 ? 4 : 1)) v
                                                                     uint32_t* __restrict__ head,
                                                                     uint32_t* __restrict__ tail,
                                                                     WsHeader* hdr, unsigned long long cstamp,
-                                                                    uint32_t cap) {
+                                                                    uint32_t cap, GradOut go) {
   constexpr uint32_t DH = head_dwords(C), DT = tail_dwords(IDX), HW = DH + 1;
   extern __shared__ uint4 sm4[];
   uint32_t* sh = (uint32_t*)sm4;               // [stage][HW]: head words, then the tile
@@ -914,6 +924,8 @@ __global__ __launch_bounds__(THREADS, PER == 4 ? 8 : (THREADS == 512 ? 4 : 1)) v
       rank[k] = atomicAdd(&cnt[tile[k]], 1u);
       nan_count += has_nan<C, PER>(r, k) ? 1u : 0u;
       ++mine;
+    } else if constexpr (IDX) {
+      if (i0 + k < n) zero_gradient<C>(go, (uint64_t)base + i0 + k);
     }
   }
   mine = wave_sum(mine);
@@ -991,7 +1003,7 @@ __global__ __launch_bounds__(THREADS) void k_scatter_global(wt_fragments f, Geom
                                                                     uint32_t* __restrict__ head,
                                                                     uint32_t* __restrict__ tail,
                                                                     WsHeader* hdr, unsigned long long cstamp,
-                                                                    uint32_t cap) {
+                                                                    uint32_t cap, GradOut go) {
   constexpr uint32_t DH = head_dwords(C), DT = tail_dwords(IDX);
   if (hdr->counted != cstamp) {
     if (threadIdx.x == 0) scatter_refuse(hdr);
@@ -1006,7 +1018,11 @@ __global__ __launch_bounds__(THREADS) void k_scatter_global(wt_fragments f, Geom
   uint32_t nan_count = 0;
 #pragma unroll
   for (uint32_t k = 0; k < kPer; ++k) {
-    if (r.p[k] >= g.P) continue;
+    if (r.p[k] >= g.P) {
+      if constexpr (IDX)
+        if (i0 + k < n) zero_gradient<C>(go, (uint64_t)base + i0 + k);
+      continue;
+    }
     uint32_t tile, local;
     tile_locate(g, r.p[k], tile, local);
     nan_count += has_nan<C, kPer>(r, k) ? 1u : 0u;
@@ -1033,7 +1049,7 @@ __global__ __launch_bounds__(THREADS) void k_scatter_global(wt_fragments f, Geom
 template <int C, bool IDX>
 __global__ void k_scatter_serial(wt_fragments f, Geom g, uint32_t* __restrict__ cursors,
                                  const uint32_t* __restrict__ offsets, uint32_t* __restrict__ head,
-                                 uint32_t* __restrict__ tail, WsHeader* hdr, unsigned long long cstamp) {
+                                 uint32_t* __restrict__ tail, WsHeader* hdr, unsigned long long cstamp, GradOut go) {
   constexpr uint32_t DH = head_dwords(C), DT = tail_dwords(IDX);
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   if (hdr->counted != cstamp) {
@@ -1043,7 +1059,10 @@ __global__ void k_scatter_serial(wt_fragments f, Geom g, uint32_t* __restrict__ 
   unsigned long long nan_count = 0;
   for (uint64_t i = 0; i < f.count; ++i) {
     const uint32_t p = f.pixel[i];
-    if (p >= g.P) continue;
+    if (p >= g.P) {
+      if (IDX) zero_gradient<C>(go, i);
+      continue;
+    }
     uint32_t tile, local;
     tile_locate(g, p, tile, local);
     const uint32_t cls = (uint32_t)((i / g.chunk) % g.NX);
@@ -1180,7 +1199,7 @@ constexpr uint32_t kStageTwoWg = 1024;
 template <int C, bool IDX, int PER, int THREADS>
 static hipError_t launch_scatter_t(const Geom& g, const wt_fragments& f, int vec, uint32_t* cursors,
                                    uint32_t* head, uint32_t* tail, WsHeader* hdr,
-                                   unsigned long long cstamp, uint32_t cap, uint32_t nchunks, hipStream_t s) {
+                                   unsigned long long cstamp, uint32_t cap, const GradOut& go, uint32_t nchunks, hipStream_t s) {
   if (g.lds_bins) {
     constexpr uint32_t RB = staged_record_bytes(C, IDX);
     // largest power-of-two round beside the tile tables (1 KB left for static LDS), within half the LDS when two
@@ -1196,10 +1215,10 @@ static hipError_t launch_scatter_t(const Geom& g, const wt_fragments& f, int vec
       if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k, dim3(nchunks), dim3(THREADS), lds, s, f, g, vec, stage, cursors, head, tail, hdr, cstamp,
-                       cap);
+                       cap, go);
   } else {
     hipLaunchKernelGGL((k_scatter_global<C, IDX, THREADS>), dim3(nchunks), dim3(THREADS), 0, s, f, g, vec, cursors,
-                       head, tail, hdr, cstamp, cap);
+                       head, tail, hdr, cstamp, cap, go);
   }
   return hipGetLastError();
 }
@@ -1207,11 +1226,11 @@ static hipError_t launch_scatter_t(const Geom& g, const wt_fragments& f, int vec
 template <int C, bool IDX>
 static hipError_t launch_scatter(const Geom& g, const wt_fragments& f, int vec, uint32_t* cursors,
                                  uint32_t* head, uint32_t* tail, WsHeader* hdr,
-                                 unsigned long long cstamp, uint32_t cap, uint32_t nchunks, hipStream_t s) {
+                                 unsigned long long cstamp, uint32_t cap, const GradOut& go, uint32_t nchunks, hipStream_t s) {
   auto run = g.kper == 4         ? launch_scatter_t<C, IDX, 4, 1024>
              : g.sthreads == 512 ? launch_scatter_t<C, IDX, kPer, 512>
                                  : launch_scatter_t<C, IDX, kPer, 1024>;
-  return run(g, f, vec, cursors, head, tail, hdr, cstamp, cap, nchunks, s);
+  return run(g, f, vec, cursors, head, tail, hdr, cstamp, cap, go, nchunks, s);
 }
 
 hipError_t launch_bin_count(const Geom& g, const wt_fragments& f, void* ws, const Layout& l, hipStream_t s) {
@@ -1276,8 +1295,9 @@ hipError_t launch_bin_count(const Geom& g, const wt_fragments& f, void* ws, cons
   return hipGetLastError();
 }
 
-hipError_t launch_bin_scatter(const Geom& g, const wt_fragments& f, void* ws, const Layout& l, bool record_index,
+hipError_t launch_bin_scatter(const Geom& g, const wt_fragments& f, void* ws, const Layout& l, const GradOut& go,
                               hipStream_t s) {
+  const bool record_index = go.on;
   char* b = (char*)ws;
   uint32_t* cursors = (uint32_t*)(b + l.cursors);
   const uint32_t* offsets = (const uint32_t*)(b + l.offsets);
@@ -1295,7 +1315,7 @@ hipError_t launch_bin_scatter(const Geom& g, const wt_fragments& f, void* ws, co
     // deterministic: straight into the tile segments, whatever the number of levels
     auto k = g.C == 1 ? (record_index ? k_scatter_serial<1, true> : k_scatter_serial<1, false>)
                       : (record_index ? k_scatter_serial<3, true> : k_scatter_serial<3, false>);
-    hipLaunchKernelGGL(k, dim3(1), dim3(64), 0, s, f, g, cursors, offsets, head, tail, hdr, cstamp);
+    hipLaunchKernelGGL(k, dim3(1), dim3(64), 0, s, f, g, cursors, offsets, head, tail, hdr, cstamp, go);
     launch_seal(hdr, cursors, offsets, g.NX, g.ntiles, cstamp, stamp, s);
     return hipGetLastError();
   }
@@ -1309,7 +1329,7 @@ hipError_t launch_bin_scatter(const Geom& g, const wt_fragments& f, void* ws, co
   if (F > 0) {
     auto scatter = g.C == 1 ? (record_index ? launch_scatter<1, true> : launch_scatter<1, false>)
                             : (record_index ? launch_scatter<3, true> : launch_scatter<3, false>);
-    e = scatter(gs, f, vec, cursors1, head1, tail1, hdr, cstamp, cap, nchunks, s);
+    e = scatter(gs, f, vec, cursors1, head1, tail1, hdr, cstamp, cap, go, nchunks, s);
     if (e != hipSuccess) return e;
   }
   launch_seal(hdr, cursors1, offsets1, gs.NX, gs.ntiles, cstamp, stamp1, s);
@@ -1335,11 +1355,11 @@ hipError_t launch_bin_scatter(const Geom& g, const wt_fragments& f, void* ws, co
   return hipGetLastError();
 }
 
-hipError_t launch_bin(const Geom& g, const wt_fragments& f, void* ws, const Layout& l, bool record_index,
+hipError_t launch_bin(const Geom& g, const wt_fragments& f, void* ws, const Layout& l, const GradOut& go,
                       hipStream_t s) {
   hipError_t e = launch_bin_count(g, f, ws, l, s);
   if (e != hipSuccess) return e;
-  return launch_bin_scatter(g, f, ws, l, record_index, s);
+  return launch_bin_scatter(g, f, ws, l, go, s);
 }
 
 }  // namespace wt

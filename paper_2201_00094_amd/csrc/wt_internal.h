@@ -251,11 +251,18 @@ unsigned long long count_stamp(const Geom& g, const Layout& l, const wt_fragment
 // Fill n words at p with v (a kernel: safe inside captured graphs).
 hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s);
 
+// A binning for the gradient (on; its records keep alpha and the stream index) and the gradient arrays (which may be
+// null for an empty stream), or a forward binning.
+struct GradOut {
+  bool on;
+  float* alpha;
+  float* rgb;
+};
+
 // Launchers (return hipError_t of the launch).
-hipError_t launch_bin(const Geom& g, const wt_fragments& f, void* ws, const Layout& l, bool record_index,
-                      hipStream_t s);
+hipError_t launch_bin(const Geom& g, const wt_fragments& f, void* ws, const Layout& l, const GradOut& go, hipStream_t s);
 hipError_t launch_bin_count(const Geom& g, const wt_fragments& f, void* ws, const Layout& l, hipStream_t s);
-hipError_t launch_bin_scatter(const Geom& g, const wt_fragments& f, void* ws, const Layout& l, bool record_index,
+hipError_t launch_bin_scatter(const Geom& g, const wt_fragments& f, void* ws, const Layout& l, const GradOut& go,
                               hipStream_t s);
 hipError_t launch_build(const Geom& g, const Binned& b, void* coeffs, hipStream_t s);
 hipError_t launch_evaluate(const Geom& g, const Binned& b, const void* coeffs, float* accum, hipStream_t s);
@@ -266,7 +273,6 @@ hipError_t launch_render_temporal(const Geom& g, const Binned& b, const float* b
 hipError_t launch_resolve_chromatic(const Geom& g, const float* accum, const float* bgimg, const float* offset,
                                    float dispersion, uint32_t taps, float* out, hipStream_t s);
 hipError_t launch_backward(const Geom& g, const Binned& b, const void* coeffs, const float* accum, const float* bg,
-                           const float* grad_out, float* grad_alpha, float* grad_rgb, uint64_t count,
-                           hipStream_t s);
+                           const float* grad_out, float* grad_alpha, float* grad_rgb, hipStream_t s);
 
 }  // namespace wt

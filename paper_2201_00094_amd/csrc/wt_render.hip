@@ -125,8 +125,6 @@ __device__ __forceinline__ void resolve_tile(const Geom& g, const TileRef& r, co
 template <int C, bool TIGHT>
 constexpr int kept() { return C == 1 && !TIGHT ? 16 : 12; }
 
-constexpr uint32_t kNoRecord = 0xffffffffu;
-
 // One kept record: pixel | cell << 16, the offset in the cell, and with depth bounds 1 - t (rounded from FP64 on its
 // own; otherwise 1 - t is exact or rounds the same way again).
 template <bool TIGHT>

@@ -84,6 +84,8 @@ __device__ __forceinline__ bool load_head(const Binned& b, uint32_t i, Head<C>& 
   return !bad;
 }
 
+constexpr uint32_t kNoRecord = 0xffffffffu;
+
 template <bool NT>
 __device__ __forceinline__ void load_tail(const Binned& b, uint32_t i, float (&w)[3]) {
   const uint32_t* r = b.tail + (uint64_t)i * b.DT;
@@ -503,7 +505,6 @@ static hipError_t dispatch(const Geom& g, F&& f) {
   if (g.dtype == WT_F32) return f(std::integral_constant<int, 3>{}, (float*)nullptr);
   if (g.dtype == WT_F16) return f(std::integral_constant<int, 3>{}, (__half*)nullptr);
   if (g.dtype == WT_E5B9G9R9) {
-    if (!g.ep) return hipErrorInvalidValue;  // make_geom puts packed storage on the endpoint path
     return f(std::integral_constant<int, 3>{}, (e5_t*)nullptr);
   }
   return f(std::integral_constant<int, 3>{}, (bf16_t*)nullptr);
