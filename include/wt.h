@@ -183,6 +183,11 @@ wt_status wt_resolve_chromatic(const wt_frame_desc* desc, const float* accum, co
 wt_status wt_render(const wt_frame_desc* desc, const wt_fragments* frags, const float* bg_rgb, void* coeffs,
                     float* out, void* ws, size_t ws_bytes, hipStream_t stream);
 
+/* wt_render that also writes the accumulation ([P][4] or [P][8] as wt_evaluate leaves it from zeros, overwritten), for
+ * a following wt_backward: what a differentiated frame needs in one pass. coeffs and accum must not be NULL. */
+wt_status wt_render_accum(const wt_frame_desc* desc, const wt_fragments* frags, const float* bg_rgb, void* coeffs,
+                          float* accum, float* out, void* ws, size_t ws_bytes, hipStream_t stream);
+
 /* Bytes of the per-GPU device array that wt_render_noalloc bins into (256 MiB). */
 #define WT_SCRATCH_BYTES ((size_t)256 << 20)
 

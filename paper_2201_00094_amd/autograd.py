@@ -1,5 +1,6 @@
-"""torch.autograd.Function over the resolve: forward runs the build, evaluate and resolve kernels; backward runs
-the gradient kernel (wt_backward) for alpha and rgb. Depth receives no gradient."""
+"""torch.autograd.Function over the resolve: forward bins and renders in one pass over the binned stream (coefficients and
+accumulation kept for the gradient); backward runs the gradient kernel (wt_backward) for alpha and rgb. Depth receives
+no gradient."""
 from __future__ import annotations
 
 import torch
@@ -15,12 +16,11 @@ class WaveletComposite(torch.autograd.Function):
         frags = _wt.Fragments(pixel, depth.detach(), alpha.detach().contiguous(), rgb.detach().contiguous())
         if ws is None:
             ws = _wt.Workspace(spec, frags.count, device=pixel.device)
-        coeffs = spec.new_coeffs(device=pixel.device)
-        accum = spec.new_accum(device=pixel.device)
-        _wt.bin(spec, frags, ws)
-        _wt.build_binned(spec, coeffs, ws)
-        _wt.evaluate_binned(spec, coeffs, accum, ws)
-        out = _wt.resolve(spec, accum, bg)
+        dev = pixel.device
+        coeffs = torch.empty(spec.coeff_shape(), dtype=_wt.TORCH_DTYPES[spec.dtype], device=dev)
+        accum = torch.empty((spec.pixels, spec.accum_width), dtype=torch.float32, device=dev)
+        out = torch.empty((spec.pixels, 3), dtype=torch.float32, device=dev)
+        _wt.render_accum(spec, frags, bg, ws, out, coeffs, accum)
         ctx.save_for_backward(pixel, frags.depth, frags.alpha, frags.rgb, coeffs, accum)
         ctx.spec, ctx.bg, ctx.ws = spec, tuple(float(b) for b in bg), ws
         return out

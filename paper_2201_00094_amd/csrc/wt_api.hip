@@ -249,8 +249,8 @@ wt_status wt_resolve_chromatic(const wt_frame_desc* desc, const float* accum, co
   return WT_OK;
 }
 
-wt_status wt_render(const wt_frame_desc* desc, const wt_fragments* frags, const float* bg_rgb, void* coeffs,
-                    float* out, void* ws, size_t ws_bytes, hipStream_t stream) {
+static wt_status render_frame(const wt_frame_desc* desc, const wt_fragments* frags, const float* bg_rgb, void* coeffs,
+                              float* accum, float* out, void* ws, size_t ws_bytes, hipStream_t stream) {
   WT_TRY(check_desc(desc));
   WT_TRY(check_frags(frags));
   if (!bg_rgb || !out) return fail(WT_ERR_INVALID, "bg_rgb or out is NULL");
@@ -260,9 +260,21 @@ wt_status wt_render(const wt_frame_desc* desc, const wt_fragments* frags, const 
   WT_TRY(check_ws(g, ws, ws_bytes, frags->count, &l));
   hipError_t e = wt::launch_bin(g, *frags, ws, l, wt::GradOut{}, stream);
   if (e != hipSuccess) return hip_fail(e, "wt_render (bin)");
-  e = wt::launch_render(g, wt::binned_view(g, l, ws, false), bg_rgb, coeffs, out, stream);
+  e = wt::launch_render(g, wt::binned_view(g, l, ws, false), bg_rgb, coeffs, accum, out, stream);
   if (e != hipSuccess) return hip_fail(e, "wt_render");
   return WT_OK;
+}
+
+wt_status wt_render(const wt_frame_desc* desc, const wt_fragments* frags, const float* bg_rgb, void* coeffs,
+                    float* out, void* ws, size_t ws_bytes, hipStream_t stream) {
+  return render_frame(desc, frags, bg_rgb, coeffs, nullptr, out, ws, ws_bytes, stream);
+}
+
+wt_status wt_render_accum(const wt_frame_desc* desc, const wt_fragments* frags, const float* bg_rgb, void* coeffs,
+                          float* accum, float* out, void* ws, size_t ws_bytes, hipStream_t stream) {
+  WT_TRY(check_desc(desc));
+  if (!coeffs || !accum) return fail(WT_ERR_INVALID, "coeffs or accum is NULL");
+  return render_frame(desc, frags, bg_rgb, coeffs, accum, out, ws, ws_bytes, stream);
 }
 
 wt_status wt_render_noalloc(const wt_frame_desc* desc, const wt_fragments* frags, const float* bg_rgb, void* coeffs,
@@ -282,7 +294,7 @@ wt_status wt_render_noalloc(const wt_frame_desc* desc, const wt_fragments* frags
   WT_TRY(check_ws(g, ws, kScratchBytes, frags->count, &l));
   hipError_t e = wt::launch_bin(g, *frags, ws, l, wt::GradOut{}, stream);
   if (e != hipSuccess) return hip_fail(e, "wt_render_noalloc (bin)");
-  e = wt::launch_render(g, wt::binned_view(g, l, ws, false), bg_rgb, coeffs, out, stream);
+  e = wt::launch_render(g, wt::binned_view(g, l, ws, false), bg_rgb, coeffs, nullptr, out, stream);
   if (e != hipSuccess) return hip_fail(e, "wt_render_noalloc");
   return WT_OK;
 }
@@ -295,7 +307,7 @@ wt_status wt_render_binned(const wt_frame_desc* desc, const void* ws, size_t ws_
   WT_TRY(check_lds(g));
   wt::Layout l;
   WT_TRY(check_ws(g, ws, ws_bytes, 0, &l));
-  hipError_t e = wt::launch_render(g, wt::binned_view(g, l, ws, false), bg_rgb, coeffs, out, stream);
+  hipError_t e = wt::launch_render(g, wt::binned_view(g, l, ws, false), bg_rgb, coeffs, nullptr, out, stream);
   if (e != hipSuccess) return hip_fail(e, "wt_render_binned");
   return WT_OK;
 }

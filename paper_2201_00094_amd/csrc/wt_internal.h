@@ -267,7 +267,9 @@ hipError_t launch_bin_scatter(const Geom& g, const wt_fragments& f, void* ws, co
 hipError_t launch_build(const Geom& g, const Binned& b, void* coeffs, hipStream_t s);
 hipError_t launch_evaluate(const Geom& g, const Binned& b, const void* coeffs, float* accum, hipStream_t s);
 hipError_t launch_resolve(const Geom& g, const float* accum, const float* bg, float* out, hipStream_t s);
-hipError_t launch_render(const Geom& g, const Binned& b, const float* bg, void* coeffs, float* out, hipStream_t s);
+// coeffs and accum may be null (not stored).
+hipError_t launch_render(const Geom& g, const Binned& b, const float* bg, void* coeffs, float* accum, float* out,
+                         hipStream_t s);
 hipError_t launch_render_temporal(const Geom& g, const Binned& b, const float* bg, const void* prev,
                                   const uint32_t* map, void* coeffs, float* out, hipStream_t s);
 hipError_t launch_resolve_chromatic(const Geom& g, const float* accum, const float* bgimg, const float* offset,

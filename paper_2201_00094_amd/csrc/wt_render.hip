@@ -100,10 +100,26 @@ __device__ __forceinline__ void render_convert(const Geom& g, const TileRef& r, 
   });
 }
 
-// out = colour + bg exp(-sum a) of the tile's pixels, from the colour rows and the totals the conversion left.
+// One pixel's results: out = colour + bg exp(-sum a), and its accumulation where accum is not null.
+template <int C>
+__device__ __forceinline__ void put_pixel(uint64_t p, const float (&colour)[3], const float (&suma)[C],
+                                          const float (&bg)[3], float* __restrict__ accum, float* __restrict__ out) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) out[p * 3 + q] = colour[q] + bg[q] * __expf(-suma[C == 1 ? 0 : q]);
+  if (!accum) return;
+  float* a = accum + p * (C == 1 ? 4 : 8);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) a[q] = colour[q];
+  if constexpr (C == 3) a[3] = a[7] = 0.f;
+#pragma unroll
+  for (int c = 0; c < C; ++c) a[(C == 1 ? 3 : 4) + c] = suma[c];
+}
+
+// The results of the tile's pixels, from the colour rows and the totals the conversion left.
 template <int C>
 __device__ __forceinline__ void resolve_tile(const Geom& g, const TileRef& r, const acc_t* le, const acc_t* la,
-                                             const float (&bg)[3], float* __restrict__ out) {
+                                             const float (&bg)[3], float* __restrict__ accum,
+                                             float* __restrict__ out) {
   const uint32_t TP = g.tile_px;
   for (uint32_t lp = threadIdx.x; lp < TP; lp += blockDim.x) {
     uint64_t p;
@@ -111,8 +127,8 @@ __device__ __forceinline__ void resolve_tile(const Geom& g, const TileRef& r, co
     float suma[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) suma[c] = *(const float*)(le + (size_t)(c * (g.M + 1) + g.M / 2) * TP + lp);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) out[p * 3 + q] = (float)la[q * TP + lp] + bg[q] * __expf(-suma[C == 1 ? 0 : q]);
+    const float colour[3] = {(float)la[lp], (float)la[TP + lp], (float)la[2 * TP + lp]};
+    put_pixel<C>(p, colour, suma, bg, accum, out);
   }
 }
 
@@ -163,7 +179,8 @@ __device__ __forceinline__ void shade_record(const Binned& b, const Geom& g, uin
 // bounds [2][TP] (TIGHT).
 template <int C, typename TS, bool TIGHT>
 __global__ __launch_bounds__(kTileThreads) void k_render(Binned b, Geom g, TS* __restrict__ coeffs, float bg0,
-                                                         float bg1, float bg2, float* __restrict__ out) {
+                                                         float bg1, float bg2, float* __restrict__ accum,
+                                                         float* __restrict__ out) {
   extern __shared__ acc_t smem_d[];
   constexpr int K = kept<C, TIGHT>(), U = 4;
   constexpr bool kNT = last_read_nt<C>();
@@ -271,7 +288,7 @@ __global__ __launch_bounds__(kTileThreads) void k_render(Binned b, Geom g, TS* _
         });
   }
   __syncthreads();
-  resolve_tile<C>(g, r, le, la, bg, out);
+  resolve_tile<C>(g, r, le, la, bg, accum, out);
 }
 
 // ------------------------------------------------------------------------------------------- render, M > 32
@@ -280,7 +297,8 @@ __global__ __launch_bounds__(kTileThreads) void k_render(Binned b, Geom g, TS* _
 // coeffs is not null), accumulation rows [AL][TP] FP64, depth bounds.
 template <int C, typename TS>
 __global__ __launch_bounds__(kTileThreads) void k_render_direct(Binned b, Geom g, TS* __restrict__ coeffs, float bg0,
-                                                                float bg1, float bg2, float* __restrict__ out) {
+                                                                float bg1, float bg2, float* __restrict__ accum,
+                                                                float* __restrict__ out) {
   extern __shared__ acc_t smem_d[];
   const uint32_t TP = g.tile_px;
   uint32_t tile;
@@ -316,11 +334,11 @@ __global__ __launch_bounds__(kTileThreads) void k_render_direct(Binned b, Geom g
   for (uint32_t lp = threadIdx.x; lp < TP; lp += blockDim.x) {
     uint64_t p;
     if (!tile_pixel(g, r, lp, p)) continue;
+    float suma[C];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const float suma = (float)la[(3 + (C == 1 ? 0 : q)) * TP + lp];
-      out[p * 3 + q] = (float)la[q * TP + lp] + bg[q] * __expf(-suma);
-    }
+    for (int c = 0; c < C; ++c) suma[c] = (float)la[(3 + c) * TP + lp];
+    const float colour[3] = {(float)la[lp], (float)la[TP + lp], (float)la[2 * TP + lp]};
+    put_pixel<C>(p, colour, suma, bg, accum, out);
   }
 }
 
@@ -421,7 +439,7 @@ __global__ __launch_bounds__(kTileThreads) void k_render_temporal(Binned b, Geom
   __syncthreads();
   render_convert<C, TS>(g, r, le, coeffs);
   __syncthreads();
-  resolve_tile<C>(g, r, le, la, bg, out);
+  resolve_tile<C>(g, r, le, la, bg, nullptr, out);
 }
 
 // ------------------------------------------------------------------------------------------- launchers
@@ -438,7 +456,8 @@ size_t lds_temporal_bytes(const Geom& g) {
   return (size_t)g.tile_px * ((g.C * (g.M + 1) + 3) * sizeof(acc_t) + g.C * g.M * sizeof(float));
 }
 
-hipError_t launch_render(const Geom& g, const Binned& b, const float* bg, void* coeffs, float* out, hipStream_t s) {
+hipError_t launch_render(const Geom& g, const Binned& b, const float* bg, void* coeffs, float* accum, float* out,
+                         hipStream_t s) {
   const size_t lds = lds_tile_bytes(g, true);
   return dispatch(g, [&](auto cc, auto* tag) {
     constexpr int C = decltype(cc)::value;
@@ -449,7 +468,7 @@ hipError_t launch_render(const Geom& g, const Binned& b, const float* bg, void* 
     }
     hipError_t err = prep(k, lds);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(g.tthreads), lds, s, b, g, (TS*)coeffs, bg[0], bg[1], bg[2], out);
+    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(g.tthreads), lds, s, b, g, (TS*)coeffs, bg[0], bg[1], bg[2], accum, out);
     return hipGetLastError();
   });
 }

@@ -260,6 +260,20 @@ def render(spec: FrameSpec, frags: Fragments, bg, ws: Workspace, out: torch.Tens
     return out
 
 
+def render_accum(spec: FrameSpec, frags: Fragments, bg, ws: Workspace, out: torch.Tensor, coeffs: torch.Tensor,
+                 accum: torch.Tensor, stream=None) -> torch.Tensor:
+    """:func:`render` that also writes the accumulation, for a following :func:`backward` (all three overwritten)."""
+    _check(out, (torch.float32,), (spec.pixels, 3), "out")
+    _check(coeffs, (TORCH_DTYPES[spec.dtype],), spec.coeff_shape(), "coeffs")
+    _check(accum, (torch.float32,), (spec.pixels, spec.accum_width), "accum")
+    _binned_as(ws, None)
+    _lib.check(_lib.load().wt_render_accum(C.byref(spec.c_desc()), C.byref(frags.c_struct(spec.channels)),
+                                           _lib.bg3(bg), _ptr(coeffs), _ptr(accum), _ptr(out), ws.ptr, ws.nbytes,
+                                           _stream(stream)), "wt_render_accum")
+    _binned_as(ws, spec)
+    return out
+
+
 def render_noalloc(spec: FrameSpec, frags: Fragments, bg, out: torch.Tensor, coeffs: torch.Tensor = None,
                    stream=None) -> torch.Tensor:
     """:func:`render` without a workspace: the library bins into its own static per-GPU array (for callers that

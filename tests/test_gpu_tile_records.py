@@ -128,3 +128,33 @@ def test_gradient_counts(orc, channels, tight, rank, dtype):
             oa, og = orc.backward(W, H, rank, pixel, depth, alpha, rgb, g, bg=bg, channels=channels, tight=tight)
             scale = max(1.0, np.abs(oa).max())
             assert np.abs(ga - oa).max() <= 1e-3 * scale and np.abs(gr - og).max() <= 1e-4, F
+
+
+@pytest.mark.parametrize("channels,rank,dtype", [(1, 3, "f32"), (3, 3, "f16"), (3, 2, "e5b9g9r9"), (1, 5, "bf16")])
+def test_render_accum_matches_the_passes(orc, channels, rank, dtype):
+    """The accumulation written by the one-pass render against evaluate's from the same coefficients (FP32 sums of FP64
+    totals on both sides: 2e-6 relative), the padding words zero, composite and coefficients those of render."""
+    import torch
+    import paper_2201_00094_amd as wt
+    from paper_2201_00094_amd.wt import render_accum
+    W, H, bg, F = 53, 38, (0.2, 0.3, 0.4), 24000
+    say("case render accum", channels, rank, dtype)
+    rng = np.random.default_rng(rank)
+    fr = wt.Fragments.from_numpy(*_stream(rng, W * H, F, channels))
+    spec = wt.FrameSpec(W, H, rank, channels, dtype)
+    ws = wt.Workspace(spec, F)
+    nan = float("nan")
+    out = torch.full((spec.pixels, 3), nan, device="cuda")
+    accum = torch.full((spec.pixels, spec.accum_width), nan, device="cuda")
+    coeffs = torch.full_like(spec.new_coeffs(), 7)
+    render_accum(spec, fr, bg, ws, out, coeffs, accum)
+    c2 = spec.new_coeffs()
+    o2 = wt.render(spec, fr, bg, ws, coeffs=c2)
+    a2 = spec.new_accum()
+    wt.evaluate(spec, fr, coeffs, a2, ws)
+    torch.cuda.synchronize()
+    assert torch.allclose(coeffs.float(), c2.float(), rtol=1e-2 if dtype != "f32" else 1e-6, atol=1e-6)
+    assert (out - o2).abs().max() <= 1e-5
+    assert ((accum - a2).abs() <= 2e-6 * a2.abs().clamp(min=1e-3)).all()
+    if channels == 3:
+        assert (accum[:, 3] == 0).all() and (accum[:, 7] == 0).all()
