@@ -158,3 +158,21 @@ def test_render_accum_matches_the_passes(orc, channels, rank, dtype):
     assert ((accum - a2).abs() <= 2e-6 * a2.abs().clamp(min=1e-3)).all()
     if channels == 3:
         assert (accum[:, 3] == 0).all() and (accum[:, 7] == 0).all()
+
+
+@pytest.mark.parametrize("width,height,taps", [(1, 300, 5), (300, 1, 7), (1398102, 2, 5), (1398101, 2, 11), (129, 67, 3)])
+def test_chromatic_addressing(orc, width, height, taps):
+    """The composite's two addressing forms at their border (row pitch 12 x width at 2^24 bytes), one-pixel rows and
+    columns, offsets past every edge: within 1e-4 of the oracle (the contract of the chromatic tests)."""
+    import torch
+    import paper_2201_00094_amd as wt
+    say("case chromatic addressing", width, height, taps)
+    rng = np.random.default_rng(width)
+    P = width * height
+    spec = wt.FrameSpec(width, height, 3)
+    accum, image = rng.random((P, 4), dtype=np.float32), rng.random((P, 3), dtype=np.float32)
+    offset = rng.uniform(-40, 40, (P, 2)).astype(np.float32)
+    offset[:2] = (-1e6, 1e6), (3e9, -3e9)
+    out = wt.resolve_chromatic(spec, *(torch.from_numpy(a).cuda() for a in (accum, image, offset)), 0.5, taps)
+    ref = orc.resolve_chromatic(width, height, accum[:, :3], accum[:, 3:], image, offset, 0.5, taps)
+    assert np.abs(out.cpu().double().numpy() - ref).max() <= 1e-4
