@@ -1188,6 +1188,99 @@ __global__ __launch_bounds__(kSplitThreads) void k_split(Geom g, const uint32_t*
   }
 }
 
+// Small streams: the whole binning in one launch (after the header's reset), a workgroup per tile. Each reads every
+// pixel id, lists the fragments of its own tile in LDS and counts those of the tiles before it, which is where its
+// records start, and writes them there, consecutive lanes on consecutive records. The ids are read once per tile, from
+// L2, which costs less than the count, scan, scatter and seal one after the other (five launches that each wait for the
+// one before) up to kSmallReads ids in all; a list of 16-bit indices takes kSmallStream fragments at most.
+// 64x64 with 33,000 fragments: 29 -> 17 us a frame.
+constexpr uint32_t kSmallStream = 65536;
+constexpr uint64_t kSmallReads = 16u << 20;
+
+template <int C, bool IDX>
+__global__ __launch_bounds__(1024) void k_bin_small(wt_fragments f, Geom g, int vec, uint32_t* __restrict__ offsets,
+                                                    uint32_t* __restrict__ order, uint32_t* __restrict__ head,
+                                                    uint32_t* __restrict__ tail, WsHeader* hdr,
+                                                    unsigned long long stamp, GradOut go) {
+  constexpr uint32_t DH = head_dwords(C), DT = tail_dwords(IDX);
+  extern __shared__ uint16_t list[];
+  __shared__ uint32_t mine, before, lost;
+  const uint32_t F = (uint32_t)f.count, me = blockIdx.x;
+  if (threadIdx.x == 0) mine = before = lost = 0;
+  __syncthreads();
+  uint32_t below = 0, drops = 0;
+  auto take = [&](uint32_t i, uint32_t p) {
+    if (p >= g.P) {  // in no tile: the first workgroup accounts for it
+      if (me == 0) {
+        ++drops;
+        if constexpr (IDX) zero_gradient<C>(go, i);
+      }
+      return;
+    }
+    const uint32_t t = tile_of(g, p);
+    if (t < me) ++below;
+    if (t == me) list[atomicAdd(&mine, 1u)] = (uint16_t)i;
+  };
+  const uint32_t quads = vec ? F / 4 : 0;
+  for (uint32_t q0 = threadIdx.x; q0 < quads; q0 += 2048) {
+    const bool two = q0 + 1024 < quads;
+    const uint4 a = ((const uint4*)f.pixel)[q0], b = ((const uint4*)f.pixel)[two ? q0 + 1024 : q0];
+    const uint32_t pa[4] = {a.x, a.y, a.z, a.w}, pb[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) take(4 * q0 + k, pa[k]);
+    if (two) {
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k) take(4 * (q0 + 1024) + k, pb[k]);
+    }
+  }
+  for (uint32_t i = 4 * quads + threadIdx.x; i < F; i += 1024) take(i, f.pixel[i]);
+  below = wave_sum(below);
+  if ((threadIdx.x & 63) == 0 && below) atomicAdd(&before, below);
+  __syncthreads();
+  const uint32_t base = before, n = mine;
+  for (uint32_t k = threadIdx.x; k < n; k += 1024) {
+    const uint32_t i = list[k];
+    uint32_t w[DH + DT], tile;
+    tile_locate(g, f.pixel[i], tile, w[0]);
+    w[1] = __float_as_uint(f.depth[i]);
+    bool bad = isnan(f.depth[i]);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const float al = f.alpha[C * i + c];
+      bad |= isnan(al);
+      w[2 + c] = __float_as_uint(al);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) w[DH + q] = __float_as_uint(f.rgb[3 * i + q]);
+    if constexpr (IDX) w[DH + 3] = i;
+    if constexpr (!IDX) to_forward<C>(w + 2, w + DH);
+    drops += bad ? 1u : 0u;
+    Words<DH> h;
+#pragma unroll
+    for (uint32_t j = 0; j < DH; ++j) h.w[j] = w[j];
+    Words<DT> t;
+#pragma unroll
+    for (uint32_t j = 0; j < DT; ++j) t.w[j] = w[DH + j];
+    *(Words<DH>*)(head + (uint64_t)(base + k) * DH) = h;
+    *(Words<DT>*)(tail + (uint64_t)(base + k) * DT) = t;
+  }
+  drops = wave_sum(drops);
+  if ((threadIdx.x & 63) == 0 && drops) atomicAdd(&lost, drops);
+  // all of the tile's records are in its first class
+  if (threadIdx.x < g.NX) offsets[me * g.NX + threadIdx.x] = threadIdx.x ? base + n : base;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    order[me] = me;
+    if (lost) atomicAdd(&hdr->dropped, (unsigned long long)lost);
+    if (me == g.ntiles - 1) offsets[g.ntiles * g.NX] = base + n;
+    if (me == 0) hdr->binned = stamp;
+  }
+}
+
+static bool small_stream(const Geom& g, uint64_t F) {
+  return F > 0 && F <= kSmallStream && F * g.ntiles <= kSmallReads && g.lds_bins && !g.two && !g.serial;
+}
+
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 // Largest staging round with two workgroups per compute unit. A round's slots are reserved when it is staged and
@@ -1357,6 +1450,22 @@ hipError_t launch_bin_scatter(const Geom& g, const wt_fragments& f, void* ws, co
 
 hipError_t launch_bin(const Geom& g, const wt_fragments& f, void* ws, const Layout& l, const GradOut& go,
                       hipStream_t s) {
+  if (small_stream(g, f.count)) {
+    char* b = (char*)ws;
+    WsHeader* hdr = (WsHeader*)(b + l.header);
+    hipLaunchKernelGGL(k_count_reset, dim3(1), dim3(256), 0, s, hdr, nullptr, (uint64_t)0);
+    auto k = g.C == 1 ? (go.on ? k_bin_small<1, true> : k_bin_small<1, false>)
+                      : (go.on ? k_bin_small<3, true> : k_bin_small<3, false>);
+    const size_t lds = (2 * f.count + 3) & ~(size_t)3;
+    if (lds > 65536 - 1024) {
+      hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(1024), lds, s, f, g, aligned16(f.pixel) ? 1 : 0,
+                       (uint32_t*)(b + l.offsets), (uint32_t*)(b + l.order), (uint32_t*)(b + l.heads),
+                       (uint32_t*)(b + l.tails), hdr, layout_stamp(g, l, go.on), go);
+    return hipGetLastError();
+  }
   hipError_t e = launch_bin_count(g, f, ws, l, s);
   if (e != hipSuccess) return e;
   return launch_bin_scatter(g, f, ws, l, go, s);

@@ -176,3 +176,41 @@ def test_chromatic_addressing(orc, width, height, taps):
     out = wt.resolve_chromatic(spec, *(torch.from_numpy(a).cuda() for a in (accum, image, offset)), 0.5, taps)
     ref = orc.resolve_chromatic(width, height, accum[:, :3], accum[:, 3:], image, offset, 0.5, taps)
     assert np.abs(out.cpu().double().numpy() - ref).max() <= 1e-4
+
+
+@pytest.mark.parametrize("width,height,rank,channels", [(16, 12, 3, 1), (64, 64, 3, 3), (250, 130, 4, 1), (31, 700, 2, 3),
+                                                        (9, 9, 6, 1)])
+def test_small_streams_match_the_general_binning(width, height, rank, channels):
+    """Streams binned in one launch against count + scatter of the same stream (which always take the general way), on
+    both sides of the largest small stream, aligned and not, with fragments out of range and NaN: the same drop count,
+    composites within 1e-5 (the order of FP64 sums differs, then FP32 rounding), gradients within 1e-4 of each other."""
+    import torch
+    import paper_2201_00094_amd as wt
+    rng = np.random.default_rng(width + height)
+    bg, P = (0.2, 0.3, 0.4), width * height
+    spec = wt.FrameSpec(width, height, rank, channels)
+    for F, shift in [(1, 0), (3, 1), (7, 0), (2048, 0), (4099, 1), (16384, 0), (65535, 2), (65536, 0), (65537, 0)]:
+        say("case small streams", width, height, rank, channels, F, shift)
+        pixel, depth, alpha, rgb = _stream(rng, P, F, channels)
+        alpha *= np.float32(0.1)
+        if F > 100:
+            pixel[5], pixel[F - 1] = P, 0xffffffff
+            depth[17], alpha.reshape(F, -1)[40, 0] = np.nan, np.nan
+        t = [torch.from_numpy(a).cuda() for a in (pixel.view(np.int32), depth, alpha, rgb)]
+        if shift:  # arrays that start off a 16-byte boundary
+            t = [torch.cat([a.new_zeros((shift,) + a.shape[1:]), a])[shift:] for a in t]
+        fr = wt.Fragments(*t)
+        a, b = wt.Workspace(spec, F), wt.Workspace(spec, F)
+        ca, cb = spec.new_coeffs(), spec.new_coeffs()
+        oa = wt.render(spec, fr, bg, a, coeffs=ca)
+        ob = torch.empty_like(oa)
+        wt.bin_count(spec, fr, b)
+        wt.bin_scatter(spec, fr, b)
+        wt.render_binned(spec, b, bg, ob, coeffs=cb)
+        assert wt.dropped_count(a) == wt.dropped_count(b) == (4 if F > 100 else 0)
+        assert (oa - ob).abs().max() <= 1e-5 and torch.allclose(ca, cb, rtol=1e-5, atol=0)
+        oc = torch.empty_like(oa)
+        wt.render_binned(spec, a, bg, oc)  # the workspace serves later calls
+        assert (oa - oc).abs().max() <= 1e-5
+        with pytest.raises(ValueError):
+            wt.bin_scatter(spec, fr, a)
