@@ -16,13 +16,15 @@
 //                     present in a round just before the round is written record by record with consecutive lanes
 //                     on consecutive records (head array, then tail array), so each tile's run is written
 //                     coalesced.
+//   k_scatter_stream  the same with the whole chunk staged and one workgroup per compute unit that takes chunk after
+//                     chunk, the next one's loads in flight while it writes (wherever the tables fit).
 //   Frames with more than kTwoLevelTiles tiles: a chunk would touch most tiles about once, so the stream is
-//   binned into super-tiles of SW x SH tiles first (k_super_counts, k_scan and k_scatter_staged over the
-//   super-tile geometry), then k_split moves each super-tile's records into its tiles without atomics.
+//   binned into super-tiles of SW x SH tiles first (k_super_counts, k_scan and k_scatter_stream or k_scatter_staged
+//   over the super-tile geometry), then k_split moves each super-tile's records into its tiles without atomics.
 //   k_hist_global,    one global atomic per fragment (beyond kMaxLdsBins super-tiles).
 //   k_scatter_global
-// A chunk's class is chunk % NX in both the histogram and the scatter; with one chunk per scatter workgroup the
-// class is also the XCD the workgroup runs on, so each (bin, class) run is written from a single L2.
+// A chunk's class is chunk % NX in both the histogram and the scatter; a scatter workgroup takes chunks of one class,
+// which is also the XCD the workgroup runs on, so each (bin, class) run is written from a single L2.
 // NaN fragments are counted as dropped and still binned; the tile kernels skip them.
 
 #include <algorithm>
@@ -158,7 +160,8 @@ Geom make_geom(const wt_frame_desc& d, bool backward) {
   // that one workgroup's loads overlap the other's ranking, staging and writes: one channel, 1024 threads with 4
   // fragments each (64 registers, eight waves per SIMD); three channels, 512 threads with 8 fragments each (the
   // three-channel fragment needs about 110 registers: four waves per SIMD). Otherwise one workgroup of 1024 threads
-  // with 8 fragments each per compute unit. Chunks are powers of two.
+  // with 8 fragments each per compute unit. Chunks are powers of two. (Where its tables fit, k_scatter_stream takes the
+  // chunks of the former, see stream_scatter.)
   // (Glass 3840x2160: the three-channel form took the scatter phases from 7.86 to 7.22 ms. One channel, 50 M fragments:
   // 2,280 bins 0.718 ms with one workgroup per compute unit, 0.678 with two; 3,000 bins 0.725 and 0.692; at 4,080 one
   // is faster, smoke frame 2.10 -> 2.07 ms.)
@@ -812,6 +815,43 @@ __device__ __forceinline__ void block_scan_inplace(uint32_t* cnt, uint32_t nt, u
   }
 }
 
+// The same, returning the total to every thread and storing it behind the table. Ends with a barrier.
+template <int THREADS>
+__device__ __forceinline__ uint32_t block_scan_total(uint32_t* cnt, uint32_t nt, uint32_t* wsum) {
+  constexpr uint32_t NW = THREADS / 64;
+  const uint32_t per = (nt + THREADS - 1) / THREADS;
+  const uint32_t t0 = std::min(threadIdx.x * per, nt), t1 = std::min(t0 + per, nt);
+  uint32_t s = 0;
+  for (uint32_t t = t0; t < t1; ++t) s += cnt[t];
+  const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  uint32_t inc = s;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t v = __shfl_up(inc, o, 64);
+    if (lane >= (uint32_t)o) inc += v;
+  }
+  if (lane == 63) wsum[wv] = inc;
+  __syncthreads();
+  uint32_t before = 0, total = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < NW; ++w) {
+    const uint32_t v = wsum[w];
+    before += w < wv ? v : 0u;
+    total += v;
+  }
+  uint32_t run = before + inc - s;
+  for (uint32_t t = t0; t < t1; ++t) {
+    const uint32_t v = cnt[t];
+    cnt[t] = run;
+    run += v;
+  }
+  if (threadIdx.x == 0) cnt[nt] = total;
+  __syncthreads();
+  return total;
+}
+
+constexpr uint32_t kNoTile = 0xffffffffu;
+
 // A record as it is stored: N dwords, 4-byte aligned, so that one lane writes one record with one wide store and
 // consecutive lanes write consecutive records.
 template <uint32_t N>
@@ -997,13 +1037,158 @@ __global__ __launch_bounds__(THREADS, PER == 4 ? 8 : (THREADS == 512 ? 4 : 1)) v
   if ((threadIdx.x & 63) == 0 && nan_count) atomicAdd(&hdr->dropped, (unsigned long long)nan_count);
 }
 
+// Four consecutive fragments of each array from fragment i on, as they lie in memory (any 4-byte alignment), non-temporal
+// (each fragment is read once). No branch and no copy: the loads of one chunk stay in flight while another is written.
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+template <int C>
+struct Quad {
+  u32x4_any p, x, a[C], c[3];
+  __device__ __forceinline__ void load(const wt_fragments& f, uint64_t i) {
+    p = __builtin_nontemporal_load((const u32x4_any*)(f.pixel + i));
+    x = __builtin_nontemporal_load((const u32x4_any*)(f.depth + i));
+#pragma unroll
+    for (int q = 0; q < C; ++q) a[q] = __builtin_nontemporal_load((const u32x4_any*)(f.alpha + C * i) + q);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) c[q] = __builtin_nontemporal_load((const u32x4_any*)(f.rgb + 3 * i) + q);
+  }
+  __device__ __forceinline__ uint32_t alpha(int k, int q) const { return a[(C * k + q) / 4][(C * k + q) % 4]; }
+  __device__ __forceinline__ uint32_t colour(int k, int q) const { return c[(3 * k + q) / 4][(3 * k + q) % 4]; }
+};
+
+// The same with a workgroup that stays on its compute unit and takes every gridDim.x-th chunk (a multiple of the classes,
+// so its class is its XCD's). What bounds k_scatter_staged up to about a thousand bins is not memory but the chain of
+// each workgroup: load, rank, scan, then per round stage, reserve, write. Here the chunk is staged whole (every lane has a
+// record to stage, where a round stages with a quarter of the lanes); its runs are reserved as soon as it is ranked, and
+// the reservations come back while it is scanned and staged; the next chunk's loads are in flight while it is written; and
+// a wave that has written its records goes on to rank the next chunk. Slots are open from the ranking to the write-out.
+// Measured against k_scatter_staged (one channel; 48 bytes per fragment, a copy at 4.7 TB/s in brackets):
+// 1024x768 at 16 per pixel, 768 bins: 150 -> 130 us (127); 1280x720, 1000 bins: 180 -> 158 (149); 1280x720 rank 4,
+// 1,720 bins: 280 -> 249; smoke frame, 2,040 bins: 1.675 -> 1.66 ms; 1920x1080 at 24, 3,000 bins: 687 -> 667 us; glass
+// 3840x2160 (960 super-tiles, with its split): 6.94 -> 6.83 ms. Writing the last records with the wait for the next
+// chunk's loads counted apart from the stores (an unrolled write) gave 40 us on the glass frame and cost 8 on smoke.
+// Reservations awaited before the scan instead: 3% to 6% slower. Streams of at least four fragments.
 template <int C, bool IDX, int THREADS>
-__global__ __launch_bounds__(THREADS) void k_scatter_global(wt_fragments f, Geom g, int vec,
-                                                                    uint32_t* __restrict__ cursors,
-                                                                    uint32_t* __restrict__ head,
-                                                                    uint32_t* __restrict__ tail,
-                                                                    WsHeader* hdr, unsigned long long cstamp,
-                                                                    uint32_t cap, GradOut go) {
+__global__ __launch_bounds__(THREADS) void k_scatter_stream(wt_fragments f, Geom g, uint32_t nchunks,
+                                                            uint32_t* __restrict__ cursors, uint32_t* __restrict__ head,
+                                                            uint32_t* __restrict__ tail, WsHeader* hdr,
+                                                            unsigned long long cstamp, uint32_t cap, GradOut go) {
+  constexpr uint32_t PER = 4, DH = head_dwords(C), DT = tail_dwords(IDX), HW = DH + 1, CH = THREADS * PER;
+  constexpr uint32_t R = THREADS == 1024 ? 4 : 1;  // tiles per thread at most (kTwoWgBins, 512)
+  extern __shared__ uint4 sm4[];
+  uint32_t* sh = (uint32_t*)sm4;        // [CH][HW]: head words, then the tile
+  uint32_t* st = sh + CH * HW;          // [CH][DT]: tail words
+  uint32_t* cnt = st + CH * DT;         // [ntiles + 1]: counts, then first staged positions, the total last
+  uint32_t* cnt2 = cnt + g.ntiles + 1;  // the same of the next chunk
+  uint32_t* gb = cnt2 + g.ntiles + 1;   // [ntiles]: reserved base - first staged position
+  __shared__ uint32_t wsum[THREADS / 64];
+  __shared__ uint32_t refused;
+  const uint32_t F = (uint32_t)f.count, cls = blockIdx.x % g.NX;
+  if (threadIdx.x == 0) refused = 0;
+  uint32_t nan_count = 0, c = blockIdx.x;
+  // A thread's fragments are [first, first + 4) of the chunk; past the end of the stream it loads the last four, of
+  // which it takes those from `first` on.
+  uint32_t first = c * CH + threadIdx.x * PER;
+  Quad<C> r;
+  r.load(f, std::min(first, F - PER));
+  if (hdr->counted != cstamp) {
+    if (threadIdx.x == 0) scatter_refuse(hdr);
+    return;
+  }
+  for (uint32_t t = threadIdx.x; t < g.ntiles; t += THREADS) cnt[t] = 0;
+  __syncthreads();
+  while (true) {
+    const uint32_t from = std::min(first, F - PER);
+    uint32_t tile[PER], rank[PER], local[PER];
+#pragma unroll
+    for (uint32_t k = 0; k < PER; ++k) {
+      tile[k] = kNoTile;
+      if (from + k < first) continue;
+      if (r.p[k] < g.P) {
+        tile_locate(g, r.p[k], tile[k], local[k]);
+        rank[k] = atomicAdd(&cnt[tile[k]], 1u);
+      } else if constexpr (IDX) {
+        zero_gradient<C>(go, from + k);
+      }
+    }
+    __syncthreads();
+    uint32_t got[R], n[R];
+#pragma unroll
+    for (uint32_t u = 0; u < R; ++u) {
+      const uint32_t t = threadIdx.x + u * THREADS;
+      n[u] = t < g.ntiles ? cnt[t] : 0u;
+      if (n[u]) got[u] = atomicAdd(&cursors[(cls * g.ntiles + t) * kCursorPad], n[u]);
+    }
+    const uint32_t total = block_scan_total<THREADS>(cnt, g.ntiles, wsum);
+#pragma unroll
+    for (uint32_t k = 0; k < PER; ++k) {
+      if (tile[k] == kNoTile) continue;
+      uint32_t hw[HW], tw[DT];
+      hw[0] = local[k];
+      hw[1] = r.x[k];
+      bool bad = isnan(__uint_as_float(hw[1]));
+#pragma unroll
+      for (int q = 0; q < C; ++q) {
+        hw[2 + q] = r.alpha(k, q);
+        bad |= isnan(__uint_as_float(hw[2 + q]));
+      }
+      hw[DH] = tile[k];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) tw[q] = r.colour(k, q);
+      if constexpr (IDX) tw[3] = from + k;
+      nan_count += bad ? 1u : 0u;
+      const uint32_t sp = cnt[tile[k]] + rank[k];
+      lds_put<HW>(sh + sp * HW, hw);
+      lds_put<DT>(st + sp * DT, tw);
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < R; ++u) {
+      const uint32_t t = threadIdx.x + u * THREADS;
+      if (t < g.ntiles) cnt2[t] = 0;
+      if (!n[u]) continue;
+      gb[t] = got[u] - cnt[t];
+      // writes stay inside the record arrays whatever the cursors hold
+      if (got[u] > cap || cap - got[u] < n[u]) refused = 1;
+    }
+    c += gridDim.x;
+    const bool more = c < nchunks;
+    first = c * CH + threadIdx.x * PER;
+    if (more) r.load(f, std::min(first, F - PER));
+    __syncthreads();
+    if (refused) {
+      if (threadIdx.x == 0) scatter_refuse(hdr);
+      return;
+    }
+    for (uint32_t s = threadIdx.x; s < total; s += THREADS) {
+      uint32_t hw[HW], tw[DT];
+      lds_get<HW>(sh + s * HW, hw);
+      lds_get<DT>(st + s * DT, tw);
+      const uint64_t slot = (uint32_t)(gb[hw[DH]] + s);
+      if constexpr (!IDX) to_forward<C>(hw + 2, tw);
+      Words<DH> h;
+#pragma unroll
+      for (uint32_t j = 0; j < DH; ++j) h.w[j] = hw[j];
+      Words<DT> t;
+#pragma unroll
+      for (uint32_t j = 0; j < DT; ++j) t.w[j] = tw[j];
+      *(Words<DH>*)(head + slot * DH) = h;
+      *(Words<DT>*)(tail + slot * DT) = t;
+    }
+    if (!more) break;
+    // A wave goes on to rank the next chunk while others still write: the tables it counts in were cleared before the
+    // last barrier, and the barriers after its ranking keep the stage until all have written.
+    uint32_t* const x = cnt;
+    cnt = cnt2;
+    cnt2 = x;
+  }
+  nan_count = wave_sum(nan_count);
+  if ((threadIdx.x & 63) == 0 && nan_count) atomicAdd(&hdr->dropped, (unsigned long long)nan_count);
+}
+
+template <int C, bool IDX>
+__global__ __launch_bounds__(1024) void k_scatter_global(wt_fragments f, Geom g, int vec, uint32_t* __restrict__ cursors,
+                                                         uint32_t* __restrict__ head, uint32_t* __restrict__ tail,
+                                                         WsHeader* hdr, unsigned long long cstamp, uint32_t cap,
+                                                         GradOut go) {
   constexpr uint32_t DH = head_dwords(C), DT = tail_dwords(IDX);
   if (hdr->counted != cstamp) {
     if (threadIdx.x == 0) scatter_refuse(hdr);
@@ -1290,43 +1475,93 @@ static bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 constexpr uint32_t kStageTwoWg = 1024;
 
 template <int C, bool IDX, int PER, int THREADS>
-static hipError_t launch_scatter_t(const Geom& g, const wt_fragments& f, int vec, uint32_t* cursors,
-                                   uint32_t* head, uint32_t* tail, WsHeader* hdr,
-                                   unsigned long long cstamp, uint32_t cap, const GradOut& go, uint32_t nchunks, hipStream_t s) {
-  if (g.lds_bins) {
-    constexpr uint32_t RB = staged_record_bytes(C, IDX);
-    // largest power-of-two round beside the tile tables (1 KB left for static LDS), within half the LDS when two
-    // workgroups share a compute unit
-    constexpr bool kTwoWg = PER == 4 || THREADS == 512;
-    const size_t budget = (kTwoWg ? kLdsBytes / 2 : kLdsBytes) - 1024;
-    uint32_t stage = std::min<uint32_t>(g.chunk, kTwoWg ? kStageTwoWg : g.chunk);
-    while (stage > 256 && (size_t)stage * RB + 8ull * g.rb > budget) stage >>= 1;
-    const size_t lds = (size_t)stage * RB + 8ull * g.rb;
-    auto k = k_scatter_staged<C, IDX, THREADS, PER>;
-    if (lds > 65536) {
-      hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k, dim3(nchunks), dim3(THREADS), lds, s, f, g, vec, stage, cursors, head, tail, hdr, cstamp,
-                       cap, go);
-  } else {
-    hipLaunchKernelGGL((k_scatter_global<C, IDX, THREADS>), dim3(nchunks), dim3(THREADS), 0, s, f, g, vec, cursors,
-                       head, tail, hdr, cstamp, cap, go);
+static hipError_t launch_scatter_staged(const Geom& g, const wt_fragments& f, int vec, uint32_t* cursors,
+                                        uint32_t* head, uint32_t* tail, WsHeader* hdr, unsigned long long cstamp,
+                                        uint32_t cap, const GradOut& go, uint32_t nchunks, hipStream_t s) {
+  constexpr uint32_t RB = staged_record_bytes(C, IDX);
+  // largest power-of-two round beside the tile tables (1 KB left for static LDS), within half the LDS when two
+  // workgroups share a compute unit
+  constexpr bool kTwoWg = PER == 4 || THREADS == 512;
+  const size_t budget = (kTwoWg ? kLdsBytes / 2 : kLdsBytes) - 1024;
+  uint32_t stage = std::min<uint32_t>(g.chunk, kTwoWg ? kStageTwoWg : g.chunk);
+  while (stage > 256 && (size_t)stage * RB + 8ull * g.rb > budget) stage >>= 1;
+  const size_t lds = (size_t)stage * RB + 8ull * g.rb;
+  auto k = k_scatter_staged<C, IDX, THREADS, PER>;
+  if (lds > 65536) {
+    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
   }
+  hipLaunchKernelGGL(k, dim3(nchunks), dim3(THREADS), lds, s, f, g, vec, stage, cursors, head, tail, hdr, cstamp,
+                     cap, go);
   return hipGetLastError();
+}
+
+// k_scatter_stream takes every chunk geometry that k_scatter_staged would take two workgroups per compute unit for, with
+// at least four fragments, where its tables fit beside a chunk. It needs six chunks for each compute unit to pay for
+// three channels, whose k_scatter_staged has as many lanes to stage with (512x512 at 16 per pixel 75 us staged, 79 as a
+// stream; at 32 per pixel 151 and 137); with more bins than kTwoWgBins runs are one record long and writing is what counts
+// (3,840 bins, 1920x1080 rank 4: 1.51 ms staged, 1.53 as a stream).
+static size_t stream_lds(uint32_t chunk, uint32_t C, bool idx, uint32_t bins) {
+  return (size_t)chunk * staged_record_bytes(C, idx) + 4 * (3 * (size_t)bins + 2);
+}
+
+static bool stream_scatter(const Geom& g, uint64_t F, uint32_t bins, bool idx) {
+  if (!g.lds_bins || F < 4 || bins > kTwoWgBins || g.chunk > 4096) return false;
+  if (g.C == 3 && F < 6ull * kComputeUnits * 4096) return false;
+  return stream_lds(g.chunk, g.C, idx, bins) <= kLdsBytes - 1024;
+}
+
+// The chunk a stream of F fragments is counted and scattered in: that of the geometry, or half of it, with two workgroups
+// of k_scatter_stream per compute unit, for a one-channel stream of few chunks whose last round of them would leave a
+// tenth of the compute units or more idle (or several times that: a single round). (640x360 at 16 per pixel, 900 chunks:
+// 67 us and 62; 320x240, 300 chunks: 26.4 and 21.4. With full rounds, or with runs that the halved chunk makes short, it
+// loses: 512x512 at 8 per pixel, 512 chunks, 27.2 and 28.6; 800x600 at 64, 333 us staged, 301 whole, 416 halved.)
+constexpr uint32_t kSmallChunk = 2048;
+
+static Geom chunked(Geom g, uint64_t F) {
+  const uint64_t n = (F + 4095) / 4096, rounds = (n + kComputeUnits - 1) / kComputeUnits;
+  const uint32_t bins = g.two ? g.nsuper : g.ntiles;
+  if (g.C == 1 && g.lds_bins && g.chunk == 4096 && F >= 4 && rounds <= 4 && bins <= 512 &&
+      10 * n <= 9 * rounds * kComputeUnits)
+    g.chunk = kSmallChunk;
+  return g;
 }
 
 template <int C, bool IDX>
 static hipError_t launch_scatter(const Geom& g, const wt_fragments& f, int vec, uint32_t* cursors,
                                  uint32_t* head, uint32_t* tail, WsHeader* hdr,
                                  unsigned long long cstamp, uint32_t cap, const GradOut& go, uint32_t nchunks, hipStream_t s) {
-  auto run = g.kper == 4         ? launch_scatter_t<C, IDX, 4, 1024>
-             : g.sthreads == 512 ? launch_scatter_t<C, IDX, kPer, 512>
-                                 : launch_scatter_t<C, IDX, kPer, 1024>;
+  if constexpr (C == 1 || !IDX) {  // (a chunk of three-channel records with their indexes is all of the LDS)
+    if (stream_scatter(g, f.count, g.ntiles, IDX)) {
+      auto k = k_scatter_stream<C, IDX, 1024>;
+      if constexpr (C == 1)
+        if (g.chunk == kSmallChunk) k = k_scatter_stream<C, IDX, kSmallChunk / 4>;
+      const size_t lds = stream_lds(g.chunk, C, IDX, g.ntiles);
+      hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+      // one workgroup per compute unit, two of the small ones (multiples of the classes)
+      const uint32_t grid = std::min<uint32_t>(nchunks, g.chunk == kSmallChunk ? 2 * kComputeUnits : kComputeUnits);
+      hipLaunchKernelGGL(k, dim3(grid), dim3(g.chunk / 4), lds, s, f, g, nchunks, cursors, head, tail, hdr, cstamp, cap, go);
+      return hipGetLastError();
+    }
+  }
+  if (!g.lds_bins) {
+    hipLaunchKernelGGL((k_scatter_global<C, IDX>), dim3(nchunks), dim3(1024), 0, s, f, g, vec, cursors, head, tail, hdr,
+                       cstamp, cap, go);
+    return hipGetLastError();
+  }
+  // (without an index every one-channel stream of at least four fragments that has small chunks goes through above)
+  auto run = launch_scatter_staged<C, IDX, kPer, 1024>;
+  if constexpr (C == 1 && IDX) {
+    if (g.kper == 4) run = launch_scatter_staged<C, IDX, 4, 1024>;
+  } else if constexpr (C == 3) {
+    if (g.sthreads == 512) run = launch_scatter_staged<C, IDX, kPer, 512>;
+  }
   return run(g, f, vec, cursors, head, tail, hdr, cstamp, cap, go, nchunks, s);
 }
 
-hipError_t launch_bin_count(const Geom& g, const wt_fragments& f, void* ws, const Layout& l, hipStream_t s) {
+hipError_t launch_bin_count(const Geom& geom, const wt_fragments& f, void* ws, const Layout& l, hipStream_t s) {
+  const Geom g = chunked(geom, f.count);
   char* b = (char*)ws;
   uint32_t* counts = (uint32_t*)(b + l.counts);
   uint32_t* offsets = (uint32_t*)(b + l.offsets);
@@ -1388,8 +1623,9 @@ hipError_t launch_bin_count(const Geom& g, const wt_fragments& f, void* ws, cons
   return hipGetLastError();
 }
 
-hipError_t launch_bin_scatter(const Geom& g, const wt_fragments& f, void* ws, const Layout& l, const GradOut& go,
+hipError_t launch_bin_scatter(const Geom& geom, const wt_fragments& f, void* ws, const Layout& l, const GradOut& go,
                               hipStream_t s) {
+  const Geom g = chunked(geom, f.count);
   const bool record_index = go.on;
   char* b = (char*)ws;
   uint32_t* cursors = (uint32_t*)(b + l.cursors);

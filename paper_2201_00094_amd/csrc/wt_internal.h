@@ -154,7 +154,7 @@ struct Geom {
   uint32_t tthreads;     // workgroup size of the tile kernels
   uint32_t sthreads;     // scatter workgroup size
   uint32_t kper;         // fragments per scatter thread (4 or kPer)
-  uint32_t chunk;        // fragments per scatter workgroup = sthreads * kper (also the class granularity)
+  uint32_t chunk;        // fragments a scatter workgroup takes at a time (also the class granularity)
 };
 
 // Binned fragment records, two arrays of structures in the same order:

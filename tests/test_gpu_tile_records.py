@@ -214,3 +214,56 @@ def test_small_streams_match_the_general_binning(width, height, rank, channels):
         assert (oa - oc).abs().max() <= 1e-5
         with pytest.raises(ValueError):
             wt.bin_scatter(spec, fr, a)
+
+
+# Both sides of every edge of the scatter that stays on its compute unit: whole and halved chunks (2048, with at most 512
+# tiles), one or several of them per workgroup, a partial last chunk and a partial last group of four.
+@pytest.mark.parametrize("width,height,rank,channels,F,shift", [
+    (250, 130, 3, 1, 3, 0), (250, 130, 3, 1, 4, 1), (250, 130, 3, 1, 2047, 3), (250, 130, 3, 1, 2049, 1),
+    (400, 300, 3, 1, 70001, 2), (250, 130, 3, 1, 1048579, 3), (250, 130, 4, 1, 1048575, 1), (250, 130, 2, 1, 5300003, 1),
+    (1100, 900, 3, 1, 5, 1), (1100, 900, 3, 1, 4097, 2), (1100, 900, 4, 1, 300003, 3), (300, 200, 2, 3, 6291455, 1),
+    (300, 200, 2, 3, 6291458, 1)])
+def test_streamed_scatter(orc, width, height, rank, channels, F, shift):
+    """Coefficients of one binning against the sum of builds of pieces that are binned in one launch: FP32 sums of at most
+    106 pieces, each rounded once, so within 107 x 2^-24 < 1e-5 of each other; drop counts; gradients against the oracle
+    (one fragment per pixel or fewer, so the bounds of the two-level gradients)."""
+    import torch
+    import paper_2201_00094_amd as wt
+    say("case streamed scatter", width, height, rank, channels, F, shift)
+    rng = np.random.default_rng(F)
+    P = width * height
+    pixel, depth, alpha, rgb = _stream(rng, P, F, channels)
+    alpha *= np.float32(min(1.0, P / F))
+    if F > 100:
+        pixel[5], pixel[F - 1] = P, 0xffffffff
+        depth[17], alpha.reshape(F, -1)[40, 0] = np.nan, np.nan
+    t = [torch.from_numpy(a).cuda() for a in (pixel.view(np.int32), depth, alpha, rgb)]
+    if shift:  # arrays that start off a 16-byte boundary
+        t = [torch.cat([a.new_zeros((shift,) + a.shape[1:]), a])[shift:] for a in t]
+    spec = wt.FrameSpec(width, height, rank, channels)
+    fr = wt.Fragments(*t)
+    ws, small = wt.Workspace(spec, F), wt.Workspace(spec, F)
+    whole, parts = spec.new_coeffs(), spec.new_coeffs()
+    wt.bin_count(spec, fr, ws)
+    wt.bin_scatter(spec, fr, ws)
+    wt.build_binned(spec, whole, ws)
+    assert wt.dropped_count(ws) == (4 if F > 100 else 0)
+    piece = 50000 if P < 100000 else 16000
+    for i in range(0, F, piece):
+        wt.build(spec, wt.Fragments(*[a[i:i + piece] for a in t]), parts, small)
+    assert torch.allclose(whole, parts, rtol=1e-5, atol=0)
+    if F > P or F < 70001:
+        return
+    g = rng.standard_normal((P, 3)).astype(np.float32)
+    accum = spec.new_accum()
+    wt.evaluate(spec, fr, whole, accum, ws)
+    ga, gr = wt.backward(spec, fr, whole, accum, (0.1, 0.2, 0.3), torch.from_numpy(g).cuda(), ws)
+    torch.cuda.synchronize()
+    ga, gr = ga.cpu().double().numpy().reshape(F, channels), gr.cpu().double().numpy()
+    out = np.zeros(F, bool)
+    out[[5, 17, 40, F - 1]] = True
+    assert (ga[out] == 0).all() and (gr[out] == 0).all()
+    oa, og = orc.backward(width, height, rank, pixel[~out], depth[~out], alpha[~out], rgb[~out], g, bg=(0.1, 0.2, 0.3),
+                          channels=channels)
+    assert np.abs(ga[~out] - oa).max() <= 1e-3
+    assert np.abs(gr[~out] - og).max() <= 1e-4
