@@ -1512,16 +1512,17 @@ static bool stream_scatter(const Geom& g, uint64_t F, uint32_t bins, bool idx) {
 }
 
 // The chunk a stream of F fragments is counted and scattered in: that of the geometry, or half of it, with two workgroups
-// of k_scatter_stream per compute unit, for a one-channel stream of few chunks whose last round of them would leave a
-// tenth of the compute units or more idle (or several times that: a single round). (640x360 at 16 per pixel, 900 chunks:
-// 67 us and 62; 320x240, 300 chunks: 26.4 and 21.4. With full rounds, or with runs that the halved chunk makes short, it
-// loses: 512x512 at 8 per pixel, 512 chunks, 27.2 and 28.6; 800x600 at 64, 333 us staged, 301 whole, 416 halved.)
+// of k_scatter_stream per compute unit, for a one-channel stream of few chunks and bins whose last round of chunks would
+// leave a tenth of the compute units or more idle. (240 bins: 300 chunks 26.4 us whole, 21.4 halved; 900, 67 and 62; 1,800,
+// 82 and 79; 3,600, 144 and 151. 480 bins: 900 chunks 50.4 and 47.3, 1,800 chunks 83.3 and 85.3. With full rounds it loses:
+// 256 bins, 512 chunks, 27.2 and 28.6. With many more bins the halved chunk's runs are short: 800x600 at 64 per pixel,
+// 500 bins, 333 us staged, 301 whole, 416 halved.)
 constexpr uint32_t kSmallChunk = 2048;
 
 static Geom chunked(Geom g, uint64_t F) {
   const uint64_t n = (F + 4095) / 4096, rounds = (n + kComputeUnits - 1) / kComputeUnits;
   const uint32_t bins = g.two ? g.nsuper : g.ntiles;
-  if (g.C == 1 && g.lds_bins && g.chunk == 4096 && F >= 4 && rounds <= 4 && bins <= 512 &&
+  if (g.C == 1 && g.lds_bins && g.chunk == 4096 && F >= 4 && bins <= 512 && rounds * bins <= 2048 &&
       10 * n <= 9 * rounds * kComputeUnits)
     g.chunk = kSmallChunk;
   return g;
