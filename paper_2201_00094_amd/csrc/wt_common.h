@@ -49,10 +49,10 @@ struct is_e5<e5_t> {
 };
 
 // Shared-exponent encoding: clamp to [0, 511/512 * 2^16] (NaN and negatives to 0); exponent from the largest,
-// e = max(-16, floor(log2 max)) + 16, bumped by one if the largest rounds to 512 at e; each mantissa is
-// floor(v * 2^(24 - e) + 1/2). The scaled values are exact in FP32 (power-of-two scaling) and the rounding is
-// taken in FP64, where adding 1/2 is exact. (The same rounding done exactly in FP32, as trunc(x) plus
-// x - trunc(x) >= 1/2, made the glass frame's tile kernel slower: 3.25 -> 3.30 ms.)
+// e = max(-16, floor(log2 max)) + 16, bumped by one if the largest rounds to 512 at e, which is when it has at least
+// 511.5/256 of its power of two: the nine leading mantissa bits are ones, and 2^14 added to its bits carries into the
+// exponent. Each mantissa is floor(v * 2^(24 - e) + 1/2). The scaled values x are exact in FP32 (power-of-two scaling),
+// and so are trunc(x) and the x - trunc(x) that decides the rounding.
 __host__ __device__ __forceinline__ uint32_t e5_pack(float r, float g, float b) {
   float v[3] = {r, g, b};
   float mx = 0.f;
@@ -61,17 +61,15 @@ __host__ __device__ __forceinline__ uint32_t e5_pack(float r, float g, float b) 
     v[q] = v[q] > 0.f ? fminf(v[q], 65408.f) : 0.f;
     mx = fmaxf(mx, v[q]);
   }
-  int lead = -16;
-  if (mx >= 0x1p-16f) {
-    uint32_t u;
-    __builtin_memcpy(&u, &mx, 4);
-    lead = (int)((u >> 23) & 255u) - 127;
-  }
-  int es = lead + 16;
-  if (floor((double)ldexpf(mx, 24 - es) + 0.5) == 512.0) ++es;
+  uint32_t u;
+  __builtin_memcpy(&u, &mx, 4);
+  const int lead = (int)((u + 0x4000u) >> 23) - 111, es = lead > 0 ? lead : 0;
   uint32_t w = (uint32_t)es << 27;
 #pragma unroll
-  for (int q = 0; q < 3; ++q) w |= (uint32_t)floor((double)ldexpf(v[q], 24 - es) + 0.5) << (9 * q);
+  for (int q = 0; q < 3; ++q) {
+    const float x = ldexpf(v[q], 24 - es), t = truncf(x);
+    w |= ((uint32_t)t + (x - t >= 0.5f ? 1u : 0u)) << (9 * q);
+  }
   return w;
 }
 

@@ -267,3 +267,23 @@ def test_streamed_scatter(orc, width, height, rank, channels, F, shift):
                           channels=channels)
     assert np.abs(ga[~out] - oa).max() <= 1e-3
     assert np.abs(gr[~out] - og).max() <= 1e-4
+
+
+@pytest.mark.parametrize("rank", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("width,height", [(1, 1), (37, 53), (333, 201)])
+def test_packed_words_of_the_render(width, height, rank):
+    """The words that a render packs are those that a build packs: the same FP64 sums (one thread, stream order), rounded
+    to FP32 and packed by the same rule, so equal in every bit, for columns of every length and tiles cut by the frame;
+    and a render that stores no words shows the same frame."""
+    import torch
+    import paper_2201_00094_amd as wt
+    say("case packed words", width, height, rank)
+    rng = np.random.default_rng(width + rank)
+    F = 4 * width * height + 3
+    spec = wt.FrameSpec(width, height, rank, 3, "e5b9g9r9", deterministic=True)
+    fr = wt.Fragments.from_numpy(*_stream(rng, width * height, F, 3))
+    ws, a, b = wt.Workspace(spec, F), spec.new_coeffs(), spec.new_coeffs()
+    out = wt.render(spec, fr, (0.1, 0.2, 0.3), ws, coeffs=a)
+    wt.build(spec, fr, b, ws)
+    assert a.dtype == b.dtype and torch.equal(a, b) and bool((a != 0).any())
+    assert torch.equal(out, wt.render(spec, fr, (0.1, 0.2, 0.3), ws))
