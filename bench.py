@@ -34,8 +34,9 @@ LDS_F64_ATOMIC_CEILING = 3.0  # ds_add_f64 per compute unit per clock, random ad
 METRIC = "resolved fragments/s (build+eval) 1080p×64 frag/px; % HBM peak; p99 ms"
 CSRC = os.path.join(ROOT, "paper_2201_00094_amd", "csrc")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_smoke1080p.json")
-# short kernel names used in the JSON line -> prefix of the demangled name in rocprofv3's output
-KERNEL_PREFIX = {"k_scatter_staged": "void wt::k_scatter_staged<", "k_render": "void wt::k_render<",
+# short kernel names used in the JSON line -> prefix of the demangled name in rocprofv3's output (the scatter is
+# k_scatter_stream or k_scatter_staged)
+KERNEL_PREFIX = {"k_scatter": "void wt::k_scatter_st", "k_render": "void wt::k_render<",
                  "k_hist_lds": "void wt::k_hist_lds<", "k_render_temporal": "void wt::k_render_temporal<"}
 
 
@@ -305,7 +306,7 @@ def main():
     else:
         b_alg = algorithmic_bytes(F, P, C, coeff_px)
         models = {"k_render": (render_kernel_bytes(F, P, C, coeff_px), float(render_ms.mean()))}
-    models["k_scatter_staged"] = (scatter_kernel_bytes(F, C), float(scatter_ms.mean()))
+    models["k_scatter"] = (scatter_kernel_bytes(F, C), float(scatter_ms.mean()))
     dom = max(models, key=lambda k: models[k][1])
     dom_ms = models[dom][1]
     roof = roofline(b_alg, dom, dom_ms, None if glass else measured_traffic(dom, workload_key(args)))
@@ -343,7 +344,7 @@ def main():
         "path_hbm_frac": b_alg / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS,
         "roofline": roof,
         "kernel_rates": kernel_rates,
-        "binning_rate_frac": kernel_rates["k_scatter_staged"]["frac"],
+        "binning_rate_frac": kernel_rates["k_scatter"]["frac"],
     }
     # coefficient and colour updates of the tile kernel: LDS FP64 atomics, 2 per channel for the endpoint masses
     # and 3 for the colour sums per fragment (the clock and CU count are the published ones; the ceiling is what a
