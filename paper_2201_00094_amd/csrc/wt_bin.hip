@@ -11,7 +11,7 @@
 //                     ranges for very large frames); range drops counted.
 //   k_scan            exclusive scan of the counts, tile-major over (tile, class), into segment offsets and write
 //                     cursors; tile order for the tile kernels (heaviest first).
-//   k_scatter_staged  one chunk (4 or 8 fragments per thread) per workgroup: vector loads into registers, LDS
+//   k_scatter_staged  one chunk (8 fragments per thread) per workgroup: vector loads into registers, LDS
 //                     rank per tile, records placed in LDS in tile order in rounds, one cursor reservation per tile
 //                     present in a round just before the round is written record by record with consecutive lanes
 //                     on consecutive records (head array, then tail array), so each tile's run is written
@@ -155,26 +155,19 @@ Geom make_geom(const wt_frame_desc& d, bool backward) {
   g.sY = (g.tilesY + g.SH - 1) / g.SH;
   g.nsuper = g.sX * g.sY;
   g.NX = g.lds_bins ? kClasses : 1;
-  // Scatter: two workgroups per compute unit where the tile tables (of the binning level that scatters) and a
-  // 1024-record round fit half the LDS and a 4096-fragment chunk still holds more than one record per bin, so
-  // that one workgroup's loads overlap the other's ranking, staging and writes: one channel, 1024 threads with 4
-  // fragments each (64 registers, eight waves per SIMD); three channels, 512 threads with 8 fragments each (the
-  // three-channel fragment needs about 110 registers: four waves per SIMD). Otherwise one workgroup of 1024 threads
-  // with 8 fragments each per compute unit. Chunks are powers of two. (Where its tables fit, k_scatter_stream takes the
-  // chunks of the former, see stream_scatter.)
-  // (Glass 3840x2160: the three-channel form took the scatter phases from 7.86 to 7.22 ms. One channel, 50 M fragments:
-  // 2,280 bins 0.718 ms with one workgroup per compute unit, 0.678 with two; 3,000 bins 0.725 and 0.692; at 4,080 one
-  // is faster, smoke frame 2.10 -> 2.07 ms.)
-  // (a one-channel record stages in at most 32 bytes, index or not, a three-channel one in at most 40: 1024 of
-  // them take 32 or 40 KB)
-  g.sthreads = 1024;
-  g.kper = kPer;
+  // Scatter chunks (powers of two): 4096 fragments where a 1024-record round and the tile tables (of the binning level
+  // that scatters) fit half the LDS and a chunk still holds more than one record per bin, else 8192. k_scatter_stream
+  // takes the former (see stream_scatter); what it leaves of three channels, k_scatter_staged takes in two workgroups of
+  // 512 threads per compute unit, so that one loads while the other ranks, stages and writes (glass 3840x2160, scatter
+  // phases: 7.86 ms with one workgroup of 1024 threads, 7.22 with two).
+  // (One channel, 50 M fragments, 4096 against 8192: 2,280 bins 0.678 ms and 0.718; 3,000 bins 0.692 and 0.725; at 4,080
+  // the longer chunk is faster, smoke frame 2.07 ms and 2.10. A one-channel record stages in at most 32 bytes, index or
+  // not, a three-channel one in at most 40: 1024 of them take 32 or 40 KB.)
   const uint32_t bins = g.two ? g.nsuper : g.rb;
-  const bool two_wg = g.lds_bins && bins <= kTwoWgBins &&
-                      8ull * bins + 1024ull * (g.C == 1 ? 32 : 40) <= kLdsBytes / 2 - 1024;
-  if (two_wg && g.C == 1) g.kper = 4;
-  if (two_wg && g.C == 3) g.sthreads = 512;
-  g.chunk = g.sthreads * g.kper;
+  const bool short_chunk = g.lds_bins && bins <= kTwoWgBins &&
+                           8ull * bins + 1024ull * (g.C == 1 ? 32 : 40) <= kLdsBytes / 2 - 1024;
+  g.sthreads = short_chunk && g.C == 3 ? 512 : 1024;
+  g.chunk = short_chunk ? 4096 : 1024 * kPer;
   return g;
 }
 
@@ -195,7 +188,7 @@ Geom super_geom(const Geom& g) {
   s.lSW = 0;
   s.sX = s.tilesX;
   s.sY = s.tilesY;
-  return s;  // NX, kper and chunk stay those of g: the first level uses the classes the histogram counted
+  return s;  // NX and chunk stay those of g: the first level uses the classes the histogram counted
 }
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -712,23 +705,23 @@ __device__ __forceinline__ void load_chunk(const wt_fragments& f, uint32_t base,
     // pixel ids first: the tile count needs only them, and the other loads stay in flight meanwhile
 #pragma unroll
     for (uint32_t v = 0; v < kPer / 4; ++v) {
-      const uint4 p4 = load_stream_u4<PER == 4>(f.pixel + (uint64_t)base + i0 + 4 * v);
+      const uint4 p4 = load_stream_u4<false>(f.pixel + (uint64_t)base + i0 + 4 * v);
       r.p[4 * v + 0] = p4.x; r.p[4 * v + 1] = p4.y; r.p[4 * v + 2] = p4.z; r.p[4 * v + 3] = p4.w;
     }
 #pragma unroll
     for (uint32_t v = 0; v < kPer / 4; ++v) {
       const uint64_t i = (uint64_t)base + i0 + 4 * v;
-      const float4 x4 = load_stream_f4<PER == 4>(f.depth + i);
+      const float4 x4 = load_stream_f4<false>(f.depth + i);
       r.x[4 * v + 0] = x4.x; r.x[4 * v + 1] = x4.y; r.x[4 * v + 2] = x4.z; r.x[4 * v + 3] = x4.w;
 #pragma unroll
       for (int q = 0; q < C; ++q) {
-        const float4 a4 = load_stream_f4<PER == 4>(f.alpha + C * i + 4 * q);
+        const float4 a4 = load_stream_f4<false>(f.alpha + C * i + 4 * q);
         r.a[4 * C * v + 4 * q + 0] = a4.x; r.a[4 * C * v + 4 * q + 1] = a4.y;
         r.a[4 * C * v + 4 * q + 2] = a4.z; r.a[4 * C * v + 4 * q + 3] = a4.w;
       }
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
-        const float4 c4 = load_stream_f4<PER == 4>(f.rgb + 3 * i + 4 * q);
+        const float4 c4 = load_stream_f4<false>(f.rgb + 3 * i + 4 * q);
         r.c[12 * v + 4 * q + 0] = c4.x; r.c[12 * v + 4 * q + 1] = c4.y;
         r.c[12 * v + 4 * q + 2] = c4.z; r.c[12 * v + 4 * q + 3] = c4.w;
       }
@@ -815,9 +808,9 @@ __device__ __forceinline__ void block_scan_inplace(uint32_t* cnt, uint32_t nt, u
   }
 }
 
-// The same, returning the total to every thread and storing it behind the table. Ends with a barrier.
+// The same over 16-bit counts, returning the total to every thread and storing it behind the table. Ends with a barrier.
 template <int THREADS>
-__device__ __forceinline__ uint32_t block_scan_total(uint32_t* cnt, uint32_t nt, uint32_t* wsum) {
+__device__ __forceinline__ uint32_t block_scan_total(uint16_t* cnt, uint32_t nt, uint32_t* wsum) {
   constexpr uint32_t NW = THREADS / 64;
   const uint32_t per = (nt + THREADS - 1) / THREADS;
   const uint32_t t0 = std::min(threadIdx.x * per, nt), t1 = std::min(t0 + per, nt);
@@ -842,10 +835,10 @@ __device__ __forceinline__ uint32_t block_scan_total(uint32_t* cnt, uint32_t nt,
   uint32_t run = before + inc - s;
   for (uint32_t t = t0; t < t1; ++t) {
     const uint32_t v = cnt[t];
-    cnt[t] = run;
+    cnt[t] = (uint16_t)run;
     run += v;
   }
-  if (threadIdx.x == 0) cnt[nt] = total;
+  if (threadIdx.x == 0) cnt[nt] = (uint16_t)total;
   __syncthreads();
   return total;
 }
@@ -922,8 +915,8 @@ __device__ __forceinline__ void scatter_refuse(WsHeader* hdr) {
   ws_raise(hdr, kWsErrScatter);
 }
 
-template <int C, bool IDX, int THREADS, int PER>
-__global__ __launch_bounds__(THREADS, PER == 4 ? 8 : (THREADS == 512 ? 4 : 1)) void k_scatter_staged(wt_fragments f, Geom g, int vec,
+template <int C, bool IDX, int THREADS>
+__global__ __launch_bounds__(THREADS, THREADS == 512 ? 4 : 1) void k_scatter_staged(wt_fragments f, Geom g, int vec,
                                                                     uint32_t stage,
                                                                     uint32_t* __restrict__ cursors,
                                                                     uint32_t* __restrict__ head,
@@ -944,9 +937,9 @@ __global__ __launch_bounds__(THREADS, PER == 4 ? 8 : (THREADS == 512 ? 4 : 1)) v
   const uint32_t n = std::min<uint32_t>(g.chunk, F - base);
   for (uint32_t t = threadIdx.x; t < g.ntiles; t += blockDim.x) cnt[t] = 0;
   if (threadIdx.x == 0) nvalid = refused = 0;
-  ChunkRegs<C, PER> r;
-  const uint32_t i0 = threadIdx.x * PER;
-  load_chunk<C, PER>(f, base, i0, n, vec, r);
+  ChunkRegs<C, kPer> r;
+  const uint32_t i0 = threadIdx.x * kPer;
+  load_chunk<C, kPer>(f, base, i0, n, vec, r);
   // only the stream the preceding count counted, under the same layout, is scattered into its segments (the
   // stamp is loaded behind the chunk, so the check adds no wait of its own)
   if (hdr->counted != cstamp) {
@@ -954,15 +947,15 @@ __global__ __launch_bounds__(THREADS, PER == 4 ? 8 : (THREADS == 512 ? 4 : 1)) v
     return;
   }
   __syncthreads();
-  uint32_t tile[PER], rank[PER], local[PER];
+  uint32_t tile[kPer], rank[kPer], local[kPer];
   uint32_t nan_count = 0, mine = 0;
 #pragma unroll
-  for (uint32_t k = 0; k < PER; ++k) {
+  for (uint32_t k = 0; k < kPer; ++k) {
     tile[k] = 0xffffffffu;
     if (r.p[k] < g.P) {
       tile_locate(g, r.p[k], tile[k], local[k]);
       rank[k] = atomicAdd(&cnt[tile[k]], 1u);
-      nan_count += has_nan<C, PER>(r, k) ? 1u : 0u;
+      nan_count += has_nan<C, kPer>(r, k) ? 1u : 0u;
       ++mine;
     } else if constexpr (IDX) {
       if (i0 + k < n) zero_gradient<C>(go, (uint64_t)base + i0 + k);
@@ -974,19 +967,19 @@ __global__ __launch_bounds__(THREADS, PER == 4 ? 8 : (THREADS == 512 ? 4 : 1)) v
   block_scan_inplace<THREADS>(cnt, g.ntiles, wsum);
   __syncthreads();
   // cnt[t] is now the chunk's first staged position of tile t (tile-major order)
-  uint32_t sp[PER];
+  uint32_t sp[kPer];
 #pragma unroll
-  for (uint32_t k = 0; k < PER; ++k) sp[k] = (tile[k] == 0xffffffffu) ? 0xffffffffu : cnt[tile[k]] + rank[k];
+  for (uint32_t k = 0; k < kPer; ++k) sp[k] = (tile[k] == 0xffffffffu) ? 0xffffffffu : cnt[tile[k]] + rank[k];
   const uint32_t total = nvalid;
   for (uint32_t r0 = 0; r0 < total; r0 += stage) {
 #pragma unroll
-    for (uint32_t k = 0; k < PER; ++k) {
+    for (uint32_t k = 0; k < kPer; ++k) {
       if (sp[k] < r0 || sp[k] >= r0 + stage) continue;  // also skips invalid slots (0xffffffff)
       uint32_t hw[HW], tw[DT];
 #pragma unroll
-      for (uint32_t j = 0; j < HW; ++j) hw[j] = j < DH ? record_word<C, PER>(r, k, local[k], base + i0 + k, j) : tile[k];
+      for (uint32_t j = 0; j < HW; ++j) hw[j] = j < DH ? record_word<C, kPer>(r, k, local[k], base + i0 + k, j) : tile[k];
 #pragma unroll
-      for (uint32_t j = 0; j < DT; ++j) tw[j] = record_word<C, PER>(r, k, local[k], base + i0 + k, DH + j);
+      for (uint32_t j = 0; j < DT; ++j) tw[j] = record_word<C, kPer>(r, k, local[k], base + i0 + k, DH + j);
       lds_put<HW>(sh + (size_t)(sp[k] - r0) * HW, hw);
       lds_put<DT>(st + (size_t)(sp[k] - r0) * DT, tw);
     }
@@ -1067,6 +1060,10 @@ struct Quad {
 // 3840x2160 (960 super-tiles, with its split): 6.94 -> 6.83 ms. Writing the last records with the wait for the next
 // chunk's loads counted apart from the stores (an unrolled write) gave 40 us on the glass frame and cost 8 on smoke.
 // Reservations awaited before the scan instead: 3% to 6% slower. Streams of at least four fragments.
+// Three channels stage a record in eight words (the tile above the pixel's 18 bits: a super-tile has at most 64 x 2048
+// pixels, and there are at most kTwoWgBins bins), and the counts are 16-bit (a chunk's), so that a chunk and the tables
+// of kTwoWgBins bins fit: glass 1366x768, 3,182 bins: 594 us staged in rounds, 542 here; 1024x768 at 27, 2,496 bins, 426
+// and 388; 1920x1080 rank 2, 3,240 bins, 1.20 ms and 1.12. At few bins neither changes the time.
 template <int C, bool IDX, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_scatter_stream(wt_fragments f, Geom g, uint32_t nchunks,
                                                             uint32_t* __restrict__ cursors, uint32_t* __restrict__ head,
@@ -1074,12 +1071,14 @@ __global__ __launch_bounds__(THREADS) void k_scatter_stream(wt_fragments f, Geom
                                                             unsigned long long cstamp, uint32_t cap, GradOut go) {
   constexpr uint32_t PER = 4, DH = head_dwords(C), DT = tail_dwords(IDX), HW = DH + 1, CH = THREADS * PER;
   constexpr uint32_t R = THREADS == 1024 ? 4 : 1;  // tiles per thread at most (kTwoWgBins, 512)
+  constexpr bool kPacked = C == 3;  // eight words: pixel | tile << 18, depth, absorbances, colour
   extern __shared__ uint4 sm4[];
-  uint32_t* sh = (uint32_t*)sm4;        // [CH][HW]: head words, then the tile
-  uint32_t* st = sh + CH * HW;          // [CH][DT]: tail words
-  uint32_t* cnt = st + CH * DT;         // [ntiles + 1]: counts, then first staged positions, the total last
-  uint32_t* cnt2 = cnt + g.ntiles + 1;  // the same of the next chunk
-  uint32_t* gb = cnt2 + g.ntiles + 1;   // [ntiles]: reserved base - first staged position
+  const uint32_t half = (g.ntiles + 2) / 2;
+  uint32_t* sh = (uint32_t*)sm4;  // [CH][HW]: head words, then the tile; [CH][8] packed
+  uint32_t* st = sh + CH * HW;    // [CH][DT]: tail words
+  uint32_t* gb = kPacked ? sh + CH * 8 : st + CH * DT;  // [ntiles]: reserved base - first staged position
+  uint32_t* cnt = gb + g.ntiles;  // [ntiles + 1] 16-bit counts, then first staged positions, the total last
+  uint32_t* cnt2 = cnt + half;    // the same of the next chunk
   __shared__ uint32_t wsum[THREADS / 64];
   __shared__ uint32_t refused;
   const uint32_t F = (uint32_t)f.count, cls = blockIdx.x % g.NX;
@@ -1094,7 +1093,7 @@ __global__ __launch_bounds__(THREADS) void k_scatter_stream(wt_fragments f, Geom
     if (threadIdx.x == 0) scatter_refuse(hdr);
     return;
   }
-  for (uint32_t t = threadIdx.x; t < g.ntiles; t += THREADS) cnt[t] = 0;
+  for (uint32_t t = threadIdx.x; t < half; t += THREADS) cnt[t] = cnt2[t] = 0;
   __syncthreads();
   while (true) {
     const uint32_t from = std::min(first, F - PER);
@@ -1105,20 +1104,22 @@ __global__ __launch_bounds__(THREADS) void k_scatter_stream(wt_fragments f, Geom
       if (from + k < first) continue;
       if (r.p[k] < g.P) {
         tile_locate(g, r.p[k], tile[k], local[k]);
-        rank[k] = atomicAdd(&cnt[tile[k]], 1u);
+        const uint32_t sh16 = 16 * (tile[k] & 1);  // (a count is at most the chunk: no carry into the other half)
+        rank[k] = atomicAdd(&cnt[tile[k] >> 1], 1u << sh16) >> sh16 & 0xffffu;
       } else if constexpr (IDX) {
         zero_gradient<C>(go, from + k);
       }
     }
     __syncthreads();
+    uint16_t* const pos = (uint16_t*)cnt;
     uint32_t got[R], n[R];
 #pragma unroll
     for (uint32_t u = 0; u < R; ++u) {
       const uint32_t t = threadIdx.x + u * THREADS;
-      n[u] = t < g.ntiles ? cnt[t] : 0u;
+      n[u] = t < g.ntiles ? pos[t] : 0u;
       if (n[u]) got[u] = atomicAdd(&cursors[(cls * g.ntiles + t) * kCursorPad], n[u]);
     }
-    const uint32_t total = block_scan_total<THREADS>(cnt, g.ntiles, wsum);
+    const uint32_t total = block_scan_total<THREADS>(pos, g.ntiles, wsum);
 #pragma unroll
     for (uint32_t k = 0; k < PER; ++k) {
       if (tile[k] == kNoTile) continue;
@@ -1132,20 +1133,26 @@ __global__ __launch_bounds__(THREADS) void k_scatter_stream(wt_fragments f, Geom
         bad |= isnan(__uint_as_float(hw[2 + q]));
       }
       hw[DH] = tile[k];
+      if constexpr (kPacked) hw[0] |= tile[k] << 18;
 #pragma unroll
       for (int q = 0; q < 3; ++q) tw[q] = r.colour(k, q);
       if constexpr (IDX) tw[3] = from + k;
       nan_count += bad ? 1u : 0u;
-      const uint32_t sp = cnt[tile[k]] + rank[k];
-      lds_put<HW>(sh + sp * HW, hw);
-      lds_put<DT>(st + sp * DT, tw);
+      const uint32_t sp = pos[tile[k]] + rank[k];
+      if constexpr (kPacked) {
+        sm4[2 * sp] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+        sm4[2 * sp + 1] = make_uint4(hw[4], tw[0], tw[1], tw[2]);
+      } else {
+        lds_put<HW>(sh + sp * HW, hw);
+        lds_put<DT>(st + sp * DT, tw);
+      }
     }
 #pragma unroll
     for (uint32_t u = 0; u < R; ++u) {
       const uint32_t t = threadIdx.x + u * THREADS;
-      if (t < g.ntiles) cnt2[t] = 0;
+      if (t < half) cnt2[t] = 0;
       if (!n[u]) continue;
-      gb[t] = got[u] - cnt[t];
+      gb[t] = got[u] - pos[t];
       // writes stay inside the record arrays whatever the cursors hold
       if (got[u] > cap || cap - got[u] < n[u]) refused = 1;
     }
@@ -1160,8 +1167,15 @@ __global__ __launch_bounds__(THREADS) void k_scatter_stream(wt_fragments f, Geom
     }
     for (uint32_t s = threadIdx.x; s < total; s += THREADS) {
       uint32_t hw[HW], tw[DT];
-      lds_get<HW>(sh + s * HW, hw);
-      lds_get<DT>(st + s * DT, tw);
+      if constexpr (kPacked) {
+        const uint4 a = sm4[2 * s], b = sm4[2 * s + 1];
+        hw[0] = a.x & 0x3ffffu; hw[1] = a.y; hw[2] = a.z; hw[3] = a.w; hw[4] = b.x;
+        tw[0] = b.y; tw[1] = b.z; tw[2] = b.w;
+        hw[DH] = a.x >> 18;
+      } else {
+        lds_get<HW>(sh + s * HW, hw);
+        lds_get<DT>(st + s * DT, tw);
+      }
       const uint64_t slot = (uint32_t)(gb[hw[DH]] + s);
       if constexpr (!IDX) to_forward<C>(hw + 2, tw);
       Words<DH> h;
@@ -1474,19 +1488,19 @@ static bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // more often: 512, 2.07 ms).
 constexpr uint32_t kStageTwoWg = 1024;
 
-template <int C, bool IDX, int PER, int THREADS>
+template <int C, bool IDX, int THREADS>
 static hipError_t launch_scatter_staged(const Geom& g, const wt_fragments& f, int vec, uint32_t* cursors,
                                         uint32_t* head, uint32_t* tail, WsHeader* hdr, unsigned long long cstamp,
                                         uint32_t cap, const GradOut& go, uint32_t nchunks, hipStream_t s) {
   constexpr uint32_t RB = staged_record_bytes(C, IDX);
   // largest power-of-two round beside the tile tables (1 KB left for static LDS), within half the LDS when two
   // workgroups share a compute unit
-  constexpr bool kTwoWg = PER == 4 || THREADS == 512;
+  constexpr bool kTwoWg = THREADS == 512;
   const size_t budget = (kTwoWg ? kLdsBytes / 2 : kLdsBytes) - 1024;
   uint32_t stage = std::min<uint32_t>(g.chunk, kTwoWg ? kStageTwoWg : g.chunk);
   while (stage > 256 && (size_t)stage * RB + 8ull * g.rb > budget) stage >>= 1;
   const size_t lds = (size_t)stage * RB + 8ull * g.rb;
-  auto k = k_scatter_staged<C, IDX, THREADS, PER>;
+  auto k = k_scatter_staged<C, IDX, THREADS>;
   if (lds > 65536) {
     hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -1496,20 +1510,23 @@ static hipError_t launch_scatter_staged(const Geom& g, const wt_fragments& f, in
   return hipGetLastError();
 }
 
-// k_scatter_stream takes every chunk geometry that k_scatter_staged would take two workgroups per compute unit for, with
-// at least four fragments, where its tables fit beside a chunk. It needs six chunks for each compute unit to pay for
-// three channels, whose k_scatter_staged has as many lanes to stage with (512x512 at 16 per pixel 75 us staged, 79 as a
-// stream; at 32 per pixel 151 and 137); with more bins than kTwoWgBins runs are one record long and writing is what counts
+// k_scatter_stream takes every stream in short chunks that has at least four fragments; the tables of kTwoWgBins bins fit
+// beside a chunk. Three channels need six chunks for each compute unit to pay for themselves: k_scatter_staged has as many
+// lanes to stage with there (512x512 at 16 per pixel 75 us staged, 79 as a stream; at 32 per pixel 151 and 137). With
+// their indexes they do not fit. With more bins than kTwoWgBins runs are one record long and writing is what counts
 // (3,840 bins, 1920x1080 rank 4: 1.51 ms staged, 1.53 as a stream).
 static size_t stream_lds(uint32_t chunk, uint32_t C, bool idx, uint32_t bins) {
-  return (size_t)chunk * staged_record_bytes(C, idx) + 4 * (3 * (size_t)bins + 2);
+  return (size_t)chunk * (C == 3 ? 32 : staged_record_bytes(C, idx)) + 4 * (bins + 2 * (size_t)((bins + 2) / 2));
 }
 
-static bool stream_scatter(const Geom& g, uint64_t F, uint32_t bins, bool idx) {
-  if (!g.lds_bins || F < 4 || bins > kTwoWgBins || g.chunk > 4096) return false;
-  if (g.C == 3 && F < 6ull * kComputeUnits * 4096) return false;
-  return stream_lds(g.chunk, g.C, idx, bins) <= kLdsBytes - 1024;
+static bool stream_scatter(const Geom& g, uint64_t F, bool idx) {
+  if (!g.lds_bins || F < 4 || g.chunk > 4096) return false;
+  return g.C == 1 || (!idx && F >= 6ull * kComputeUnits * 4096);
 }
+static_assert(4096 * 32 + 4 * (kTwoWgBins + 2 * ((kTwoWgBins + 2) / 2)) <= kLdsBytes - 1024 && kTwoWgBins < 4096 &&
+                  kMaxSub * kMaxTilePx <= 1u << 18 && staged_record_bytes(1, true) <= 32,
+              "a short chunk and the tables of its bins fit the LDS, and a packed word its tile and pixel");
+
 
 // The chunk a stream of F fragments is counted and scattered in: that of the geometry, or half of it, with two workgroups
 // of k_scatter_stream per compute unit, for a one-channel stream of few chunks and bins whose last round of chunks would
@@ -1533,7 +1550,7 @@ static hipError_t launch_scatter(const Geom& g, const wt_fragments& f, int vec, 
                                  uint32_t* head, uint32_t* tail, WsHeader* hdr,
                                  unsigned long long cstamp, uint32_t cap, const GradOut& go, uint32_t nchunks, hipStream_t s) {
   if constexpr (C == 1 || !IDX) {  // (a chunk of three-channel records with their indexes is all of the LDS)
-    if (stream_scatter(g, f.count, g.ntiles, IDX)) {
+    if (stream_scatter(g, f.count, IDX)) {
       auto k = k_scatter_stream<C, IDX, 1024>;
       if constexpr (C == 1)
         if (g.chunk == kSmallChunk) k = k_scatter_stream<C, IDX, kSmallChunk / 4>;
@@ -1551,13 +1568,10 @@ static hipError_t launch_scatter(const Geom& g, const wt_fragments& f, int vec, 
                        cstamp, cap, go);
     return hipGetLastError();
   }
-  // (without an index every one-channel stream of at least four fragments that has small chunks goes through above)
-  auto run = launch_scatter_staged<C, IDX, kPer, 1024>;
-  if constexpr (C == 1 && IDX) {
-    if (g.kper == 4) run = launch_scatter_staged<C, IDX, 4, 1024>;
-  } else if constexpr (C == 3) {
-    if (g.sthreads == 512) run = launch_scatter_staged<C, IDX, kPer, 512>;
-  }
+  // (a one-channel stream in short chunks comes here only with fewer than four fragments)
+  auto run = launch_scatter_staged<C, IDX, 1024>;
+  if constexpr (C == 3)
+    if (g.sthreads == 512) run = launch_scatter_staged<C, IDX, 512>;
   return run(g, f, vec, cursors, head, tail, hdr, cstamp, cap, go, nchunks, s);
 }
 

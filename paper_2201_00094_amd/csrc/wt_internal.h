@@ -152,8 +152,7 @@ struct Geom {
   uint32_t serial;       // 1: WT_DETERMINISTIC (stream-order binning by one thread, one thread per tile's records)
   uint32_t ntiles_large; // tiles of the frame if they were the largest power-of-two tiles
   uint32_t tthreads;     // workgroup size of the tile kernels
-  uint32_t sthreads;     // scatter workgroup size
-  uint32_t kper;         // fragments per scatter thread (4 or kPer)
+  uint32_t sthreads;     // workgroup size of k_scatter_staged
   uint32_t chunk;        // fragments a scatter workgroup takes at a time (also the class granularity)
 };
 
