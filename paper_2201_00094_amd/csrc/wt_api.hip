@@ -34,6 +34,12 @@ wt_status hip_fail(hipError_t e, const char* where) {
   return fail(WT_ERR_HIP, "%s: HIP error %d (%s)", where, (int)e, hipGetErrorString(e));
 }
 
+#define WT_TRY(expr)                 \
+  do {                               \
+    wt_status st_ = (expr);          \
+    if (st_ != WT_OK) return st_;    \
+  } while (0)
+
 wt_status check_desc(const wt_frame_desc* d) {
   if (!d) return fail(WT_ERR_INVALID, "desc is NULL");
   if (d->width == 0 || d->height == 0) return fail(WT_ERR_INVALID, "frame size %ux%u is empty", d->width, d->height);
@@ -86,17 +92,18 @@ wt_status check_ws(const wt::Geom& g, const void* ws, size_t ws_bytes, uint64_t 
   return WT_OK;
 }
 
+// (Only columns of a pixel or two, nearly 2^32 pixels high, at rank 10 with three channels have so many tiles.)
+wt_status check_tiles(const wt::Geom& g) {
+  if (g.ntiles > wt::kMaxTiles) return fail(WT_ERR_UNSUPPORTED, "%u tiles are above the limit of %u", g.ntiles, wt::kMaxTiles);
+  return WT_OK;
+}
+
 wt_status check_lds(const wt::Geom& g) {
+  WT_TRY(check_tiles(g));
   if (wt::lds_tile_bytes(g, true) > wt::kLdsBytes)
     return fail(WT_ERR_UNSUPPORTED, "tile of %u pixels needs %zu bytes of LDS", g.tile_px, wt::lds_tile_bytes(g, true));
   return WT_OK;
 }
-
-#define WT_TRY(expr)                 \
-  do {                               \
-    wt_status st_ = (expr);          \
-    if (st_ != WT_OK) return st_;    \
-  } while (0)
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -347,6 +354,7 @@ wt_status wt_backward(const wt_frame_desc* desc, const wt_fragments* frags, cons
   if (!coeffs || !accum || !bg_rgb || !grad_out || (frags->count && (!grad_alpha || !grad_rgb)))
     return fail(WT_ERR_INVALID, "a backward array pointer is NULL");
   const wt::Geom g = wt::make_geom(*desc, true);
+  WT_TRY(check_tiles(g));
   if (wt::lds_backward_bytes(g) > wt::kLdsBytes)
     return fail(WT_ERR_UNSUPPORTED, "gradient tile of %u pixels needs %zu bytes of LDS", g.tile_px,
                 wt::lds_backward_bytes(g));

@@ -40,7 +40,7 @@ static uint64_t pick_supers(uint32_t tx, uint32_t ty, uint32_t& lSW, uint32_t& S
   uint64_t best = ~0ull, fewest = ~0ull;
   for (uint32_t l = 1; l <= 3; ++l) {
     for (uint32_t sh = 2; (sh << l) <= kMaxSub; ++sh) {
-      const uint64_t n = ((uint64_t)(tx + (1u << l) - 1) >> l) * ((ty + sh - 1) / sh);
+      const uint64_t n = (uint64_t)(((tx - 1) >> l) + 1) * ((ty - 1) / sh + 1);
       const uint64_t cost = n <= kMaxSupers ? (n + kComputeUnits - 1) / kComputeUnits * (sh << l) : ~0ull;
       if (cost < best || (best == ~0ull && n < fewest)) {
         best = cost;
@@ -135,8 +135,8 @@ Geom make_geom(const wt_frame_desc& d, bool backward) {
   // One LDS tile table for the scatter (up to kTwoLevelTiles tiles; beyond, two levels below)
   g.lds_bins = g.ntiles <= kTwoLevelTiles ? 1 : 0;
   g.rb = g.ntiles;
-  const uint32_t hnr = (g.ntiles + kMaxHistBins - 1) / kMaxHistBins;
-  g.hrb = (g.ntiles + hnr - 1) / hnr;
+  const uint32_t hnr = (g.ntiles - 1) / kMaxHistBins + 1;
+  g.hrb = (g.ntiles - 1) / hnr + 1;
   // Many tiles: a chunk of the stream touches each tile about chunk / ntiles times, too few for whole runs. Bin
   // into at most kMaxSupers super-tiles of SW x SH tiles first (runs as long as for a small frame), then split
   // each super-tile's records into its tiles (runs of hundreds of records, no atomics).
@@ -151,8 +151,8 @@ Geom make_geom(const wt_frame_desc& d, bool backward) {
     g.two = (uint64_t)((g.tilesX - 1) / g.SW + 1) * ((g.tilesY - 1) / g.SH + 1) <= kMaxLdsBins ? 1 : 0;
     g.lds_bins = g.two;
   }
-  g.sX = (g.tilesX + g.SW - 1) / g.SW;
-  g.sY = (g.tilesY + g.SH - 1) / g.SH;
+  g.sX = (g.tilesX - 1) / g.SW + 1;
+  g.sY = (g.tilesY - 1) / g.SH + 1;
   g.nsuper = g.sX * g.sY;
   g.NX = g.lds_bins ? kClasses : 1;
   // Scatter chunks (powers of two): 4096 fragments where a 1024-record round and the tile tables (of the binning level

@@ -31,6 +31,7 @@ constexpr uint32_t kMinTilePx = 64;
 constexpr uint32_t kTileFixedPx = 160;     // what a tile costs by itself, in pixels (pick_tile)
 constexpr uint32_t kTileThreads = 1024;    // largest workgroup of the per-tile kernels
 constexpr uint32_t kScanRange = 16384;     // segments one scan workgroup covers (a multiple of kClasses)
+constexpr uint32_t kMaxTiles = 0xffffffffu - kScanRange;  // tile numbers of a whole scan range stay below 2^32
 constexpr float kAlphaMax = 0.99999994f;   // 1 - 2^-24
 
 // Division of 32-bit values by a divisor fixed per frame, without a hardware divide (Granlund and Montgomery,

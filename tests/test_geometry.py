@@ -1,0 +1,44 @@
+"""Frame geometry on the host (no GPU): the tiles, levels and tables that the library chooses for a description, compiled
+for the host from its own sources."""
+import ctypes as C
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2201_00094_amd import _lib
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+@pytest.fixture(scope="module")
+def check(tmp_path_factory):
+    if not os.path.exists(HIPCC) and shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    exe = tmp_path_factory.mktemp("geom") / "geom_check"
+    subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"),
+                           "-I", os.path.join(ROOT, "paper_2201_00094_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "host", "geom_check.cpp"), "-o", str(exe)],
+                          stderr=subprocess.DEVNULL)
+
+    def run(name):
+        res = subprocess.run([str(exe), name], capture_output=True, text=True, timeout=300)
+        assert res.returncode == 0 and "bad 0" in res.stdout, res.stdout
+        return res.stdout
+    return run
+
+
+def test_frames_at_the_size_limits(check):
+    """Descriptions of nearly 2^32 pixels in one row or column get tables for all their tiles; the few whose tiles cannot
+    be numbered are refused (they ended the process with a division by zero)."""
+    check("limits")
+    lib = _lib.load()
+    d = _lib.desc(1, (1 << 32) - 1, 10, 3)
+    assert lib.wt_workspace_bytes(C.byref(d), 10) > 4 * ((1 << 32) - 1)
+    frags, ws, bg = _lib.Fragments(10, 8, 8, 8, 8), C.c_void_p(0x1000), _lib.bg3((0, 0, 0))  # never dereferenced
+    assert lib.wt_bin(C.byref(d), C.byref(frags), ws, 16, None) == _lib.WT_ERR_UNSUPPORTED
+    assert lib.wt_backward(C.byref(d), C.byref(frags), ws, ws, bg, ws, ws, ws, ws, 16, None) == _lib.WT_ERR_UNSUPPORTED
+    d = _lib.desc(1, (1 << 32) - 1, 9, 3)
+    assert lib.wt_bin(C.byref(d), C.byref(frags), ws, 16, None) == _lib.WT_ERR_RANGE
