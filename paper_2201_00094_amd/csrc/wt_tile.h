@@ -38,13 +38,13 @@ __device__ __forceinline__ TileRef tile_ref(const Geom& g, const Binned& b, uint
   return r;
 }
 
-// Frame pixel of tile-local pixel lp, or false when it lies outside the frame.
-__device__ __forceinline__ bool tile_pixel(const Geom& g, const TileRef& r, uint32_t lp, uint64_t& p) {
+// Frame pixel of tile-local pixel lp, or false when it lies outside the frame. The row is tested inside the tile: the last
+// tile of a frame nearly 2^32 rows high has rows past 2^32, whose 32-bit frame row would be one of the first.
+__host__ __device__ __forceinline__ bool tile_pixel(const Geom& g, const TileRef& r, uint32_t lp, uint64_t& p) {
   p = 0;
-  const uint32_t px = r.x0 + (lp & (g.TW - 1));
-  const uint32_t py = r.y0 + (lp >> g.lTW);
-  if (px >= g.W || py >= g.H) return false;
-  p = (uint64_t)py * g.W + px;
+  const uint32_t px = r.x0 + (lp & (g.TW - 1)), row = lp >> g.lTW;
+  if (px >= g.W || row >= g.H - r.y0) return false;
+  p = (uint64_t)(r.y0 + row) * g.W + px;
   return true;
 }
 

@@ -1,10 +1,11 @@
-// Host checks of the frame geometry (wt_bin.hip: make_geom, make_layout). One check per
+// Host checks of the frame geometry (wt_bin.hip: make_geom, make_layout; wt_tile.h: tile addressing). One check per
 // argument; prints "bad 0" when it holds.
 #include <cstdio>
 #include <cstring>
-#include <utility>
+#include <vector>
 
 #include "wt_bin.hip"
+#include "wt_tile.h"
 
 static int bad = 0;
 
@@ -27,6 +28,26 @@ static void each_form(uint32_t w, uint32_t h, F&& f) {
         }
 }
 
+// The last tile's pixels are those of the frame and no others, also where its rows end at 2^32.
+static void last_tile() {
+  const uint32_t top = 0xffffffffu;
+  std::vector<std::pair<uint32_t, uint32_t>> sizes = {{top, 1}, {top - 7, 1}, {1920, 1080}, {65535, 65537}, {3, 1431655765}};
+  for (uint32_t k : {0u, 1u, 4u, 5u, 31u, 58u, 59u, 60u, 63u, 64u, 1000u}) sizes.push_back({1, top - k});
+  for (auto [w, h] : sizes)
+    each_form(w, h, [&](const wt_frame_desc& d, bool bwd) {
+      const wt::Geom g = wt::make_geom(d, bwd);
+      const wt::TileRef r{(g.tilesX - 1) * g.TW, (g.tilesY - 1) * g.TH, 0, 0};
+      bool ok = g.W - r.x0 <= g.TW && g.H - r.y0 <= g.TH;
+      for (uint32_t lp = 0; lp < g.tile_px; ++lp) {
+        const uint64_t x = (uint64_t)r.x0 + (lp & (g.TW - 1)), y = (uint64_t)r.y0 + (lp >> g.lTW);
+        const bool want = x < g.W && y < g.H;
+        uint64_t p;
+        ok &= wt::tile_pixel(g, r, lp, p) == want && (!want || p == y * g.W + x);
+      }
+      expect(ok, "pixels of the last tile", d, bwd);
+    });
+}
+
 // Frames at the limits of every size still get tables that cover all their tiles.
 static void limits() {
   const uint32_t top = 0xffffffffu;
@@ -43,7 +64,8 @@ static void limits() {
 
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
-  if (!strcmp(what, "limits")) limits();
+  if (!strcmp(what, "last_tile")) last_tile();
+  else if (!strcmp(what, "limits")) limits();
   else return 2;
   printf("bad %d\n", bad);
   return bad != 0;

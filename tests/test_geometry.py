@@ -42,3 +42,8 @@ def test_frames_at_the_size_limits(check):
     assert lib.wt_backward(C.byref(d), C.byref(frags), ws, ws, bg, ws, ws, ws, ws, 16, None) == _lib.WT_ERR_UNSUPPORTED
     d = _lib.desc(1, (1 << 32) - 1, 9, 3)
     assert lib.wt_bin(C.byref(d), C.byref(frags), ws, 16, None) == _lib.WT_ERR_RANGE
+
+
+def test_last_tile_of_any_frame(check):
+    """A tile's rows past the frame stay outside it, also where row numbers would wrap at 2^32."""
+    check("last_tile")
