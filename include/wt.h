@@ -188,18 +188,22 @@ wt_status wt_render(const wt_frame_desc* desc, const wt_fragments* frags, const 
 wt_status wt_render_accum(const wt_frame_desc* desc, const wt_fragments* frags, const float* bg_rgb, void* coeffs,
                           float* accum, float* out, void* ws, size_t ws_bytes, hipStream_t stream);
 
-/* Bytes of the per-GPU device array that wt_render_noalloc bins into (256 MiB). */
+/* Bytes that a frame of wt_render_noalloc may take of the per-GPU device array it is binned into (256 MiB; the array
+ * itself is 32 MiB larger, see the limit below). */
 #define WT_SCRATCH_BYTES ((size_t)256 << 20)
 
 /* wt_render for callers that cannot allocate device memory: code under HIP graph capture, tight serving loops and
  * harnesses that forbid hipMalloc. Same arguments, kernels and results as wt_render, without the workspace: the
- * binned stream and the tile tables go to a static device array of WT_SCRATCH_BYTES that the library holds on every
+ * binned stream and the tile tables go to a static device array that the library holds on every
  * GPU it runs on until the process ends (its address is looked up once per device, on the first call with that
  * device current). Nothing is allocated or freed, by the library or by any routine it calls.
- *   Limit: a frame whose workspace (wt_workspace_bytes(desc, frags->count) without the gradient's layout) exceeds
- *   WT_SCRATCH_BYTES is refused with WT_ERR_RANGE before anything is enqueued: about 9.5 million fragments at one
- *   channel (28 bytes per binned fragment) and 7.4 million at three (36 bytes), half as many for frames of more than
- *   8192 screen tiles (binned in two levels, each with its own copy).
+ *   Limit: a frame is refused with WT_ERR_RANGE before anything is enqueued when its workspace exceeds
+ *   WT_SCRATCH_BYTES. Counted are the binned records and the tables of the largest power-of-two tiles that the frame
+ *   could be cut into (about 100 bytes each); the tables of smaller tiles and of super-tiles have 32 MiB of their own.
+ *   That is about 9.5 million fragments at one channel (28 bytes per binned fragment) and 7.4 million at three (36
+ *   bytes), half as many for frames of more than 8192 screen tiles (binned in two levels, each with its own copy).
+ *   Frames past half a million of the largest power-of-two tiles take the whole number: what does not fit twice is
+ *   binned in one level, with an atomic per fragment (slower).
  *   Sharing: every call on one GPU uses that GPU's one array, which keeps the last call's contents (each call clears
  *   what it needs zeroed with its own fill kernels). Calls that overlap in time on one GPU (on different streams, or
  *   from different threads without ordering) race on the array: the caller serialises them, for example on one

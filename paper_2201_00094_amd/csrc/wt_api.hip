@@ -3,18 +3,15 @@
 #include <stdarg.h>
 #include <stdio.h>
 
-#include <algorithm>
 #include <cmath>
 #include <mutex>
 #include <string>
 
 #include "wt_internal.h"
 
-// Workspace of wt_render_noalloc: one copy per GPU, held until the process ends. The room beyond WT_SCRATCH_BYTES is for
-// the tables of the smaller tiles that some frames are cut into (scratch_limit below). Host code reaches it only through
-// the device address that hipGetSymbolAddress returns for the current device (scratch_here below).
-constexpr size_t kScratchBytes = WT_SCRATCH_BYTES + (256u << 10);
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+// Workspace of wt_render_noalloc: one copy per GPU, held until the process ends. Host code reaches it only through the
+// device address that hipGetSymbolAddress returns for the current device (scratch_here below).
+static __device__ __align__(256) unsigned char scratch[wt::kScratchBytes];
 
 namespace {
 
@@ -108,15 +105,6 @@ wt_status check_lds(const wt::Geom& g) {
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_at[kMaxDevices];  // device address of scratch on device d, once looked up
-
-// Bytes of the scratch array that a frame may take: WT_SCRATCH_BYTES, and what its tile tables hold beyond those of the
-// largest tiles, so that the fragments it takes do not depend on the tiles chosen for it.
-size_t scratch_limit(const wt::Geom& g) {
-  wt::Geom few = g;
-  few.ntiles = std::min(g.ntiles, g.ntiles_large);
-  const size_t extra = wt::make_layout(g, 0).total - wt::make_layout(few, 0).total;
-  return std::min(kScratchBytes, WT_SCRATCH_BYTES + extra);
-}
 
 // Device address of the current device's scratch array, looked up with hipGetSymbolAddress on the first call per
 // device (with that device current) and kept.
@@ -289,16 +277,17 @@ wt_status wt_render_noalloc(const wt_frame_desc* desc, const wt_fragments* frags
   WT_TRY(check_desc(desc));
   WT_TRY(check_frags(frags));
   if (!bg_rgb || !out) return fail(WT_ERR_INVALID, "bg_rgb or out is NULL");
-  const wt::Geom g = wt::make_geom(*desc);
+  wt::Geom g;
+  size_t need, limit;
+  const bool fits = wt::scratch_geom(*desc, frags->count, g, need, limit);
   WT_TRY(check_lds(g));
-  const size_t need = wt::make_layout(g, frags->count).total, limit = scratch_limit(g);
-  if (need > limit)
+  if (!fits)
     return fail(WT_ERR_RANGE, "wt_render_noalloc: %llu fragments need %zu bytes of scratch, the static array holds %zu",
                 (unsigned long long)frags->count, need, limit);
   void* ws = nullptr;
   WT_TRY(scratch_here(&ws));
   wt::Layout l;
-  WT_TRY(check_ws(g, ws, kScratchBytes, frags->count, &l));
+  WT_TRY(check_ws(g, ws, wt::kScratchBytes, frags->count, &l));
   hipError_t e = wt::launch_bin(g, *frags, ws, l, wt::GradOut{}, stream);
   if (e != hipSuccess) return hip_fail(e, "wt_render_noalloc (bin)");
   e = wt::launch_render(g, wt::binned_view(g, l, ws, false), bg_rgb, coeffs, nullptr, out, stream);

@@ -53,6 +53,18 @@ static uint64_t pick_supers(uint32_t tx, uint32_t ty, uint32_t& lSW, uint32_t& S
   return best == ~0ull ? (fewest + kComputeUnits - 1) / kComputeUnits * (SH << lSW) : best;
 }
 
+// LDS of a tile's pixel. Forward: FP64 endpoint masses (M + 1 per channel) and three FP64 colour sums, or, for M > 32, FP64
+// coefficient sums plus FP64 accumulations; the one-pass render adds the previous frame's FP32 cells (M <= 32 and no depth
+// bounds are checked by the API). Backward: FP32 cells, FP64 cell adjoints and per-pixel gradient data. Depth bounds are
+// two FP32.
+static uint32_t tile_px_bytes(const Geom& g, bool backward) {
+  return (backward ? 12 * g.C * g.M + 4 * (3 + g.C)
+          : g.ep   ? 8 * g.C * (g.M + 1) + 24 + (g.temporal ? 4 * g.C * g.M : 0)
+                   : 8 * (g.C * g.M + g.AL)) + (g.tight ? 8 : 0);
+}
+
+static uint32_t log2_floor(uint32_t v) { return 31 - __builtin_clz(v); }
+
 // Tile of a frame, from the LDS bytes per pixel: TW a power of two, TH any height in [TW/2, 2 TW), and the workgroup size
 // of the tile kernels.
 //
@@ -65,8 +77,7 @@ static uint64_t pick_supers(uint32_t tx, uint32_t ty, uint32_t& lSW, uint32_t& S
 // unit for a small one. M > 32 keeps power-of-two tiles: there the tile is a few dozen pixels or less.
 static void pick_tile(Geom& g, uint32_t per_px) {
   uint32_t most = std::min<uint32_t>(std::max<uint32_t>(1, kLdsBytes / per_px), kMaxTilePx);
-  uint32_t e = 0;  // the largest power-of-two tile
-  while ((2u << e) <= most) ++e;
+  const uint32_t e = log2_floor(most);  // the largest power-of-two tile
   g.lTW = (e + 1) / 2;
   g.TH = 1u << (e / 2);
   g.ntiles_large = (((g.W - 1) >> g.lTW) + 1) * ((g.H - 1) / g.TH + 1);
@@ -119,18 +130,11 @@ Geom make_geom(const wt_frame_desc& d, bool backward) {
   g.AW = (d.channels == 3) ? 8 : 4;
   g.AL = (d.channels == 3) ? 6 : 4;
   g.dtype = d.coeff_dtype;
-  // LDS of a tile's pixel. Forward: FP64 endpoint masses (M + 1 per channel) and three FP64 colour sums, or, for
-  // M > 32, FP64 coefficient sums plus FP64 accumulations; the one-pass render adds the previous frame's FP32 cells
-  // (M <= 32 and no depth bounds are checked by the API). Backward: FP32 cells, FP64 cell adjoints and per-pixel
-  // gradient data. Depth bounds are two FP32.
   g.tight = (d.flags & WT_TIGHT_DEPTH) ? 1 : 0;
   g.serial = (d.flags & WT_DETERMINISTIC) ? 1 : 0;
   g.temporal = !backward && (d.flags & WT_TEMPORAL) ? 1 : 0;
   g.ep = !backward && g.M <= 32 ? 1 : 0;
-  const uint32_t per_px = (backward ? 12 * g.C * g.M + 4 * (3 + g.C)
-                           : g.ep   ? 8 * g.C * (g.M + 1) + 24 + (g.temporal ? 4 * g.C * g.M : 0)
-                                    : 8 * (g.C * g.M + g.AL)) + (g.tight ? 8 : 0);
-  pick_tile(g, per_px);
+  pick_tile(g, tile_px_bytes(g, backward));
   g.divW = make_fastdiv(g.W);
   // One LDS tile table for the scatter (up to kTwoLevelTiles tiles; beyond, two levels below)
   g.lds_bins = g.ntiles <= kTwoLevelTiles ? 1 : 0;
@@ -239,6 +243,39 @@ uint64_t capacity_for(const Geom& g, size_t ws_bytes) {
   uint64_t cap = (ws_bytes - fixed) / per;
   while (cap > 0 && make_layout(g, cap).total > ws_bytes) --cap;
   return cap;
+}
+
+// Whether a frame in the largest power-of-two tiles (no more of them than hold a column per thread, for packed storage and
+// the one-pass render) has more super-tiles of 8 x 8 of them than two levels bin.
+static bool past_two_levels(const Geom& g) {
+  uint32_t e = log2_floor(std::min(kLdsBytes / tile_px_bytes(g, false), kMaxTilePx));
+  if (g.dtype == WT_E5B9G9R9 || g.temporal) e = std::min(e, log2_floor(kTileThreads / g.C));
+  const uint32_t lw = (e + 1) / 2 + 3, lh = e / 2 + 3;
+  return (uint64_t)(((g.W - 1) >> lw) + 1) * (((g.H - 1) >> lh) + 1) > kMaxLdsBins;
+}
+
+bool scratch_geom(const wt_frame_desc& d, uint64_t count, Geom& g, size_t& need, size_t& limit) {
+  auto fits = [&] {
+    need = make_layout(g, count).total;
+    Geom few = g;
+    few.ntiles = std::min(g.ntiles, g.ntiles_large);
+    few.nsuper = 1;
+    limit = std::min(kScratchBytes, WT_SCRATCH_BYTES + make_layout(g, 0).total - make_layout(few, 0).total);
+    return need <= limit;
+  };
+  g = make_geom(d);
+  if (fits()) return true;
+  if (!g.two || !past_two_levels(g)) return false;
+  g.two = g.lds_bins = 0;
+  g.NX = 1;
+  g.SW = g.SH = 1;
+  g.lSW = 0;
+  g.sX = g.tilesX;
+  g.sY = g.tilesY;
+  g.nsuper = g.ntiles;
+  g.sthreads = 1024;
+  g.chunk = 1024 * kPer;
+  return fits();
 }
 
 Binned binned_view(const Geom& g, const Layout& l, const void* ws, bool with_index) {

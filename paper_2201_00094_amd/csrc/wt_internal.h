@@ -32,6 +32,10 @@ constexpr uint32_t kTileFixedPx = 160;     // what a tile costs by itself, in pi
 constexpr uint32_t kTileThreads = 1024;    // largest workgroup of the per-tile kernels
 constexpr uint32_t kScanRange = 16384;     // segments one scan workgroup covers (a multiple of kClasses)
 constexpr uint32_t kMaxTiles = 0xffffffffu - kScanRange;  // tile numbers of a whole scan range stay below 2^32
+// Bytes of the static array of wt_render_noalloc: what a frame may take, and room for the tables of smaller tiles and of
+// super-tiles (100 bytes each: a two-level frame has up to half a million tiles, at most about twice as many as the
+// largest ones would be).
+constexpr size_t kScratchBytes = WT_SCRATCH_BYTES + ((size_t)32 << 20);
 constexpr float kAlphaMax = 0.99999994f;   // 1 - 2^-24
 
 // Division of 32-bit values by a divisor fixed per frame, without a hardware divide (Granlund and Montgomery,
@@ -240,6 +244,12 @@ Geom make_geom(const wt_frame_desc& d, bool backward = false);
 // Geometry of the first binning level: super-tiles of g.SW x g.SH tiles as the bins, same chunking as g.
 Geom super_geom(const Geom& g);
 Layout make_layout(const Geom& g, uint64_t cap);
+// Geometry in which wt_render_noalloc renders a frame of `count` fragments, the bytes of its layout and those it may take:
+// WT_SCRATCH_BYTES, besides its super-tiles' tables and what its tile tables hold beyond those of the largest tiles, so
+// that the fragments a frame takes do not depend on the tiles chosen for it. A frame so large that the largest
+// power-of-two tiles would not be binned in two levels, whose tiles are, goes in one level (an atomic per fragment) when
+// the two copies of its records do not fit. False when the frame is refused.
+bool scratch_geom(const wt_frame_desc& d, uint64_t count, Geom& g, size_t& need, size_t& limit);
 uint64_t capacity_for(const Geom& g, size_t ws_bytes);
 size_t lds_tile_bytes(const Geom& g, bool with_accum);
 size_t lds_backward_bytes(const Geom& g);

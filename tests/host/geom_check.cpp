@@ -62,10 +62,72 @@ static void limits() {
     });
 }
 
+// Fragments of a frame in WT_SCRATCH_BYTES when it is cut into the largest power-of-two tiles (a column per thread for
+// packed storage and the one-pass render), one level up to 4,096 tiles, then super-tiles doubled up to 8 x 8 tiles until
+// there are at most 1,024, and one class without tables per super-tile past 8,192 of them.
+static uint64_t fragments_of_largest_tiles(const wt_frame_desc& d) {
+  const uint64_t C = d.channels, M = 2ull << d.rank, AL = C + 3;
+  const bool temporal = d.flags & WT_TEMPORAL;
+  const uint64_t per_px = 8 * (C * M + AL) + (temporal ? 4 * C * M : 0) + (d.flags & WT_TIGHT_DEPTH ? 8 : 0);
+  uint32_t e = 0;
+  while ((2ull << e) <= std::min<uint64_t>(163840 / per_px, 2048)) ++e;
+  if (temporal || d.coeff_dtype == WT_E5B9G9R9) e = std::min(e, C == 1 ? 10u : 8u);
+  auto up = [](uint64_t n, uint64_t by) { return (n + by - 1) / by; };
+  const uint64_t tx = up(d.width, 1ull << (e + 1) / 2), ty = up(d.height, 1ull << e / 2), nt = tx * ty;
+  uint64_t sw = 1, sh = 1, NX = 8, copies = 1, supers = 0;
+  if (nt > 4096) {
+    while (up(tx, sw) * up(ty, sh) > 1024 && sw * sh < 64) (sw <= sh ? sw : sh) *= 2;
+    supers = up(tx, sw) * up(ty, sh);
+    if (supers <= 8192) copies = 2;
+    else supers = 0, NX = 1;
+  }
+  auto a = [&](uint64_t bytes) { return up(bytes, 256) * 256; };
+  auto tables = [&](uint64_t n) { return 2 * a(4 * NX * n) + a(4 * (NX * n + 1)) + a(4 * n); };
+  auto bytes = [&](uint64_t F) {
+    return 256 + tables(nt) + a(4 * 257 * up(NX * nt, 16384)) + copies * (a(4 * (2 + C) * F) + a(16 * F)) +
+           (copies == 2 ? tables(supers) : 0);
+  };
+  if (bytes(0) > WT_SCRATCH_BYTES) return 0;
+  uint64_t F = (WT_SCRATCH_BYTES - bytes(0)) / (copies * 4 * (6 + C));
+  while (F && bytes(F) > WT_SCRATCH_BYTES) --F;
+  return F;
+}
+
+// wt_render_noalloc takes as many fragments of any frame as fit its limit with the largest tiles.
+static void scratch() {
+  uint32_t seed = 12345;
+  auto rnd = [&](uint32_t n) {
+    seed = seed * 1664525u + 1013904223u;
+    return (uint32_t)((uint64_t)(seed >> 8) * n >> 24);
+  };
+  std::vector<wt_frame_desc> ds = {{961, 1255, 7, 1, WT_F32, 0},   {15, 2879, 10, 3, WT_F32, 0},
+                                   {398, 38445, 6, 3, WT_F32, 0},  {3358, 48264, 3, 3, WT_F32, 0},
+                                   {16384, 16385, 3, 1, WT_F32, 0}, {62633, 9101, 0, 1, WT_F32, 0},
+                                   {20199, 7480, 4, 1, WT_F32, WT_TEMPORAL}, {19906, 19238, 1, 3, WT_E5B9G9R9, WT_TEMPORAL}};
+  while (ds.size() < 40000) {
+    const uint32_t w = 1 + rnd(1u << (1 + rnd(17))), h = 1 + rnd(1u << (1 + rnd(17)));
+    wt_frame_desc d{w, h, rnd(11), rnd(2) ? 3u : 1u, WT_F32, rnd(3)};
+    if ((uint64_t)w * h >> 32 || (d.flags == WT_TEMPORAL && d.rank > 4)) continue;
+    if (d.channels == 3 && d.rank <= 4 && rnd(2)) d.coeff_dtype = WT_E5B9G9R9;
+    ds.push_back(d);
+  }
+  for (const wt_frame_desc& d : ds) {
+    wt::Geom g;
+    size_t need, limit;
+    const uint64_t F = fragments_of_largest_tiles(d);
+    const bool ok = wt::scratch_geom(d, F, g, need, limit);
+    expect(!F || (ok && need <= limit && limit <= wt::kScratchBytes), "fragments of the scratch array", d, false);
+    // and no more than twice that, where the frame's own tiles are binned in one level instead of two
+    expect(!wt::scratch_geom(d, WT_SCRATCH_BYTES / (4 * (6 + d.channels)) + (1u << 20), g, need, limit),
+           "limit of the scratch array", d, false);
+  }
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "last_tile")) last_tile();
   else if (!strcmp(what, "limits")) limits();
+  else if (!strcmp(what, "scratch")) scratch();
   else return 2;
   printf("bad %d\n", bad);
   return bad != 0;

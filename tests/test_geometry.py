@@ -47,3 +47,8 @@ def test_frames_at_the_size_limits(check):
 def test_last_tile_of_any_frame(check):
     """A tile's rows past the frame stay outside it, also where row numbers would wrap at 2^32."""
     check("last_tile")
+
+
+def test_scratch_takes_what_the_largest_tiles_take(check):
+    """The fragments that wt_render_noalloc takes do not become fewer by the choice of tiles and binning levels."""
+    check("scratch")
