@@ -1,5 +1,6 @@
 // Host checks of the frame geometry (wt_bin.hip: make_geom, make_layout; wt_tile.h: tile addressing). One check per
 // argument; prints "bad 0" when it holds.
+#include <chrono>
 #include <cstdio>
 #include <cstring>
 #include <vector>
@@ -123,11 +124,67 @@ static void scratch() {
   }
 }
 
+// The least cost of all tile shapes of a frame at M <= 32, without the search's bounds: the larger of equals, the narrower
+// of those.
+static void all_shapes(const wt::Geom& g, uint32_t per_px, uint32_t& lTW, uint32_t& TH) {
+  uint32_t most = std::min(wt::kLdsBytes / per_px, wt::kMaxTilePx);
+  if (g.M >= 16) most = std::min(most, wt::kTileThreads / g.C);
+  uint64_t best = ~0ull;
+  for (uint32_t l = 3; l <= 6; ++l)
+    for (uint32_t tw = 1u << l, th = std::min(2 * tw - 1, most / tw); th >= tw / 2 && tw * th >= wt::kMinTilePx; --th) {
+      const uint32_t px = tw * th, tx = (g.W - 1) / tw + 1, ty = (g.H - 1) / th + 1;
+      const uint64_t nt = (uint64_t)tx * ty;
+      uint64_t cost = (nt + 255) / 256 * (px + wt::kTileFixedPx);
+      uint32_t lsw, sh;
+      if (nt > wt::kTwoLevelTiles) cost += wt::pick_supers(tx, ty, lsw, sh) * px;
+      if (nt > wt::kMaxLdsBins * wt::kMaxSub) cost = nt << 24;
+      if (cost < best || (cost == best && px > TH << lTW)) best = cost, lTW = l, TH = th;
+    }
+}
+
+// The bounded search of the tile shape finds what the search of all shapes finds, in less than half of its time on frames
+// that have thousands of tiles.
+static void shapes() {
+  uint32_t seed = 99;
+  auto rnd = [&](uint32_t n) {
+    seed = seed * 1664525u + 1013904223u;
+    return (uint32_t)((uint64_t)(seed >> 8) * n >> 24);
+  };
+  for (int i = 0; i < 60000; ++i) {
+    const uint32_t w = 1 + rnd(1u << (1 + rnd(17))), h = 1 + rnd(1u << (1 + rnd(17)));
+    const bool bwd = rnd(2);
+    const wt_frame_desc d{w, h, rnd(5), rnd(2) ? 3u : 1u, WT_F32, rnd(3)};
+    if ((uint64_t)w * h >> 32) continue;
+    const wt::Geom g = wt::make_geom(d, bwd);
+    uint32_t l = 0, th = 0;
+    all_shapes(g, wt::tile_px_bytes(g, bwd), l, th);
+    expect(l == g.lTW && th == g.TH, "tile shape", d, bwd);
+  }
+  double all = 0, bounded = 0;
+  volatile uint32_t sink = 0;
+  auto now = [] { return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count(); };
+  const std::pair<uint32_t, uint32_t> sizes[] = {{1920, 1080}, {3840, 2160}, {7680, 4320}, {16001, 16003}, {65535, 65537}};
+  for (auto [w, h] : sizes) {
+    const wt_frame_desc d{w, h, 3, 1, WT_F32, 0};
+    const wt::Geom g = wt::make_geom(d);
+    uint32_t l = 0, th = 0;
+    double t = now();
+    for (int i = 0; i < 500; ++i) sink = sink + wt::make_geom(d).TH;
+    bounded += now() - t;
+    t = now();
+    for (int i = 0; i < 500; ++i) all_shapes(g, wt::tile_px_bytes(g, false), l, th), sink = sink + th;
+    all += now() - t;
+  }
+  printf("all shapes %.2f us a frame, bounded %.2f\n", all / 2500 * 1e6, bounded / 2500 * 1e6);
+  expect(bounded < 0.5 * all, "time of the search", {0, 0, 3, 1, WT_F32, 0}, false);
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "last_tile")) last_tile();
   else if (!strcmp(what, "limits")) limits();
   else if (!strcmp(what, "scratch")) scratch();
+  else if (!strcmp(what, "shapes")) shapes();
   else return 2;
   printf("bad %d\n", bad);
   return bad != 0;

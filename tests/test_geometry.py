@@ -52,3 +52,8 @@ def test_last_tile_of_any_frame(check):
 def test_scratch_takes_what_the_largest_tiles_take(check):
     """The fragments that wt_render_noalloc takes do not become fewer by the choice of tiles and binning levels."""
     check("scratch")
+
+
+def test_tile_shape_search(check):
+    """Every call makes its geometry anew, so the search of the tile shape is bounded; it finds what the full one finds."""
+    check("shapes")
