@@ -311,7 +311,9 @@ __global__ __launch_bounds__(kTileThreads) void k_render(Binned b, Geom g, TS* _
 // ------------------------------------------------------------------------------------------- render, M > 32
 
 // The direct N + 2 updates: coefficients [C * M][TP] FP64, rounded to storage precision in place (and stored when
-// coeffs is not null), accumulation rows [AL][TP] FP64, depth bounds.
+// coeffs is not null), accumulation rows [AL][TP] FP64, depth bounds. Bound by its LDS atomics and reads (2 (N + 2) of a
+// fragment) and by the clearing and rounding of M sums per pixel. (512x512 at 8 per pixel: rank 8 with 256 threads and one
+// record in flight 0.77 ms, with 1024 and four 0.72; rank 10, three channels, 7.2 and 5.8.)
 template <int C, typename TS>
 __global__ __launch_bounds__(kTileThreads) void k_render_direct(Binned b, Geom g, TS* __restrict__ coeffs, float bg0,
                                                                 float bg1, float bg2, float* __restrict__ accum,
@@ -332,11 +334,7 @@ __global__ __launch_bounds__(kTileThreads) void k_render_direct(Binned b, Geom g
   __syncthreads();
   coeff_tile_io<C, TS, 2>(g, r, lc, coeffs);
   __syncthreads();
-  auto shade = [&](uint32_t i) {
-    Head<C> f;
-    float w[3];
-    load_tail<false>(b, i, w);
-    if (!load_head<C>(b, i, f)) return;
+  auto shade = [&](const Head<C>& f, const float (&w)[3]) {
     uint32_t j;
     float t, omt;
     cell_coord(f.x, lb, TP, f.lp, g.M, j, t, omt);
@@ -345,8 +343,24 @@ __global__ __launch_bounds__(kTileThreads) void k_render_direct(Binned b, Geom g
 #pragma unroll
     for (int c = 0; c < C; ++c) atomicAdd(la + (3 + c) * TP + f.lp, (acc_t)f.al[c]);
   };
-  if (!serial_records(g, r.beg, r.end, shade))
-    for (uint32_t i = r.beg + threadIdx.x; i < r.end; i += blockDim.x) shade(i);
+  if (!serial_records(g, r.beg, r.end, [&](uint32_t i) {
+        Head<C> f;
+        float w[3];
+        load_tail<false>(b, i, w);
+        if (load_head<C>(b, i, f)) shade(f, w);
+      })) {
+    constexpr int U = kEvalUnroll;
+    constexpr bool kNT = last_read_nt<C>();
+    Head<C> f[U];
+    float w[U][3];
+    for_records<U>(
+        r.beg, r.end,
+        [&](uint32_t i, int u) {
+          load_tail<kNT>(b, i, w[u]);
+          return load_head<C, kNT>(b, i, f[u]);
+        },
+        [&](int u) { shade(f[u], w[u]); });
+  }
   __syncthreads();
   for (uint32_t lp = threadIdx.x; lp < TP; lp += blockDim.x) {
     uint64_t p;

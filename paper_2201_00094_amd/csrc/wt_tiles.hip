@@ -317,13 +317,17 @@ hipError_t launch_build(const Geom& g, const Binned& b, void* coeffs, hipStream_
 
 hipError_t launch_evaluate(const Geom& g, const Binned& b, const void* coeffs, float* accum, hipStream_t s) {
   const size_t lds = lds_eval_bytes(g);
+  // M > 32: FP32 coefficients are half the LDS that the tile was sized for, and two workgroups share a compute unit where
+  // registers allow it: at one channel of 1024 threads, at three of 512 (512x512 at 8 per pixel, rank 8: one channel 391 us
+  // with 512 threads and 354 with 1024, three channels 966 and 1417)
+  const uint32_t threads = g.M > 32 && g.C == 3 ? kTileThreads / 2 : g.tthreads;
   return dispatch(g, [&](auto cc, auto* tag) {
     constexpr int C = decltype(cc)::value;
     using TS = std::remove_pointer_t<decltype(tag)>;
     auto k = (g.M <= 32) ? k_evaluate<C, TS, true> : k_evaluate<C, TS, false>;
     hipError_t err = prep(k, lds);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(g.tthreads), lds, s, b, g, (const TS*)coeffs, accum);
+    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(threads), lds, s, b, g, (const TS*)coeffs, accum);
     return hipGetLastError();
   });
 }
