@@ -1435,29 +1435,39 @@ __global__ __launch_bounds__(kSplitThreads) void k_split(Geom g, const uint32_t*
   }
 }
 
-// Small streams: the whole binning in one launch (after the header's reset), a workgroup per tile. Each reads every
-// pixel id, lists the fragments of its own tile in LDS and counts those of the tiles before it, which is where its
-// records start, and writes them there, consecutive lanes on consecutive records. The ids are read once per tile, from
-// L2, which costs less than the count, scan, scatter and seal one after the other (five launches that each wait for the
-// one before) up to kSmallReads ids in all; a list of 16-bit indices takes kSmallStream fragments at most.
-// 64x64 with 33,000 fragments: 29 -> 17 us a frame.
+// Small streams: the whole binning in one launch (after the header's reset), a workgroup per tile and part of the stream.
+// Each reads every pixel id, lists its part's fragments of its tile in LDS and counts those that come before them (of the
+// tiles below, and of the tile in earlier parts), which is where its records start, and writes them there, consecutive
+// lanes on consecutive records. The ids are read once per workgroup, from L2, which costs less than the count, scan,
+// scatter and seal one after the other (five launches that each wait for the one before) up to kSmallReads ids in all.
+// Parts bound what one compute unit moves (1.1 ns a record) when a tile holds most of the stream: with one part, 65,536
+// fragments of one tile took 78 us against 30 of the general way, with parts of kSmallPart 29; a list of 16-bit indices
+// takes kSmallStream fragments at most. 64x64 with 33,000 fragments: 29 -> 18 us a frame. (Binning alone, 256 tiles: 30,000
+// fragments in two parts, 15 M ids, 13 us against 24; 45,000 in three, 35 M, 21 and 23; 65,536 in four, 67 M, 34 and 23.)
 constexpr uint32_t kSmallStream = 65536;
-constexpr uint64_t kSmallReads = 16u << 20;
+constexpr uint32_t kSmallPart = 16384;
+constexpr uint64_t kSmallReads = 32u << 20;
+
+static uint32_t small_parts(uint64_t F) { return (uint32_t)((F + kSmallPart - 1) / kSmallPart); }
 
 template <int C, bool IDX>
-__global__ __launch_bounds__(1024) void k_bin_small(wt_fragments f, Geom g, int vec, uint32_t* __restrict__ offsets,
-                                                    uint32_t* __restrict__ order, uint32_t* __restrict__ head,
-                                                    uint32_t* __restrict__ tail, WsHeader* hdr,
-                                                    unsigned long long stamp, GradOut go) {
+__global__ __launch_bounds__(1024) void k_bin_small(wt_fragments f, Geom g, int vec, uint32_t parts,
+                                                    uint32_t* __restrict__ offsets, uint32_t* __restrict__ order,
+                                                    uint32_t* __restrict__ head, uint32_t* __restrict__ tail,
+                                                    WsHeader* hdr, unsigned long long stamp, GradOut go) {
   constexpr uint32_t DH = head_dwords(C), DT = tail_dwords(IDX);
   extern __shared__ uint16_t list[];
   __shared__ uint32_t mine, before, lost;
-  const uint32_t F = (uint32_t)f.count, me = blockIdx.x;
+  const uint32_t F = (uint32_t)f.count, me = blockIdx.x / parts, part = blockIdx.x - me * parts;
+  // its part of the stream, in groups of four ids
+  const uint32_t quads = vec ? F / 4 : 0;
+  const uint32_t lo = std::min(part * (kSmallPart / 4), quads), hi = std::min(lo + kSmallPart / 4, quads);
   if (threadIdx.x == 0) mine = before = lost = 0;
   __syncthreads();
   uint32_t below = 0, drops = 0;
+  // an id of its part: listed when it is in the tile; fragments in no tile are the first workgroups' to account for
   auto take = [&](uint32_t i, uint32_t p) {
-    if (p >= g.P) {  // in no tile: the first workgroup accounts for it
+    if (p >= g.P) {
       if (me == 0) {
         ++drops;
         if constexpr (IDX) zero_gradient<C>(go, i);
@@ -1468,9 +1478,20 @@ __global__ __launch_bounds__(1024) void k_bin_small(wt_fragments f, Geom g, int 
     if (t < me) ++below;
     if (t == me) list[atomicAdd(&mine, 1u)] = (uint16_t)i;
   };
-  const uint32_t quads = vec ? F / 4 : 0;
-  for (uint32_t q0 = threadIdx.x; q0 < quads; q0 += 2048) {
-    const bool two = q0 + 1024 < quads;
+  // ids [q0, q1) of the other parts: those below tile `top` come before its records
+  auto pass = [&](uint32_t q0, uint32_t q1, uint32_t top) {
+    for (uint32_t q = q0 + threadIdx.x; q < q1; q += 2048) {
+      const bool two = q + 1024 < q1;
+      const uint4 a = ((const uint4*)f.pixel)[q], b = ((const uint4*)f.pixel)[two ? q + 1024 : q];
+      const uint32_t p[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+      for (uint32_t k = 0; k < 8; ++k)
+        if ((k < 4 || two) && p[k] < g.P) below += tile_of(g, p[k]) < top ? 1u : 0u;
+    }
+  };
+  pass(0, lo, me + 1);
+  for (uint32_t q0 = lo + threadIdx.x; q0 < hi; q0 += 2048) {
+    const bool two = q0 + 1024 < hi;
     const uint4 a = ((const uint4*)f.pixel)[q0], b = ((const uint4*)f.pixel)[two ? q0 + 1024 : q0];
     const uint32_t pa[4] = {a.x, a.y, a.z, a.w}, pb[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
@@ -1480,7 +1501,15 @@ __global__ __launch_bounds__(1024) void k_bin_small(wt_fragments f, Geom g, int 
       for (uint32_t k = 0; k < 4; ++k) take(4 * (q0 + 1024) + k, pb[k]);
     }
   }
-  for (uint32_t i = 4 * quads + threadIdx.x; i < F; i += 1024) take(i, f.pixel[i]);
+  pass(hi, quads, me);
+  // (an unaligned stream, or the last ids)
+  for (uint32_t i = 4 * quads + threadIdx.x; i < F; i += 1024) {
+    const uint32_t at = i / kSmallPart;
+    if (at == part)
+      take(i, f.pixel[i]);
+    else if (f.pixel[i] < g.P)
+      below += tile_of(g, f.pixel[i]) < me + (at < part ? 1u : 0u) ? 1u : 0u;
+  }
   below = wave_sum(below);
   if ((threadIdx.x & 63) == 0 && below) atomicAdd(&before, below);
   __syncthreads();
@@ -1514,18 +1543,20 @@ __global__ __launch_bounds__(1024) void k_bin_small(wt_fragments f, Geom g, int 
   drops = wave_sum(drops);
   if ((threadIdx.x & 63) == 0 && drops) atomicAdd(&lost, drops);
   // all of the tile's records are in its first class
-  if (threadIdx.x < g.NX) offsets[me * g.NX + threadIdx.x] = threadIdx.x ? base + n : base;
+  if (part == 0 && threadIdx.x == 0) offsets[me * g.NX] = base;
+  if (part == parts - 1 && threadIdx.x < g.NX && (threadIdx.x || me == g.ntiles - 1))
+    offsets[(threadIdx.x ? me : g.ntiles) * g.NX + threadIdx.x] = base + n;
   __syncthreads();
   if (threadIdx.x == 0) {
-    order[me] = me;
     if (lost) atomicAdd(&hdr->dropped, (unsigned long long)lost);
-    if (me == g.ntiles - 1) offsets[g.ntiles * g.NX] = base + n;
+    if (part) return;
+    order[me] = me;
     if (me == 0) hdr->binned = stamp;
   }
 }
 
 static bool small_stream(const Geom& g, uint64_t F) {
-  return F > 0 && F <= kSmallStream && F * g.ntiles <= kSmallReads && g.lds_bins && !g.two && !g.serial;
+  return F > 0 && F <= kSmallStream && F * small_parts(F) * g.ntiles <= kSmallReads && g.lds_bins && !g.two && !g.serial;
 }
 
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
@@ -1755,12 +1786,9 @@ hipError_t launch_bin(const Geom& g, const wt_fragments& f, void* ws, const Layo
     hipLaunchKernelGGL(k_count_reset, dim3(1), dim3(256), 0, s, hdr, nullptr, (uint64_t)0);
     auto k = g.C == 1 ? (go.on ? k_bin_small<1, true> : k_bin_small<1, false>)
                       : (go.on ? k_bin_small<3, true> : k_bin_small<3, false>);
-    const size_t lds = (2 * f.count + 3) & ~(size_t)3;
-    if (lds > 65536 - 1024) {
-      hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k, dim3(g.ntiles), dim3(1024), lds, s, f, g, aligned16(f.pixel) ? 1 : 0,
+    const uint32_t parts = small_parts(f.count);
+    const size_t lds = (2 * std::min<uint64_t>(f.count, kSmallPart) + 3) & ~(size_t)3;
+    hipLaunchKernelGGL(k, dim3(g.ntiles * parts), dim3(1024), lds, s, f, g, aligned16(f.pixel) ? 1 : 0, parts,
                        (uint32_t*)(b + l.offsets), (uint32_t*)(b + l.order), (uint32_t*)(b + l.heads),
                        (uint32_t*)(b + l.tails), hdr, layout_stamp(g, l, go.on), go);
     return hipGetLastError();
