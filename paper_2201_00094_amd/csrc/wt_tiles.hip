@@ -205,13 +205,22 @@ __device__ __forceinline__ float smoothstep_formula(float e0, float e1, float x)
   return u * u * (3.f - 2.f * u);
 }
 
-// Images whose texels have 32-bit byte offsets, and row pitches and coordinates below 2^24: a texel's address is one
-// 24-bit multiply and an add on a base that stays in scalar registers, where 64-bit coordinates and addresses took most
-// of a tap's instructions (1920x1080, 5 taps 45 -> 41.5 us, 9 taps 78 -> 67). What is left is the gather's own cache
-// lines: a pixel's pair of texels with one 16-byte load (41.4 us), or a band of the image per XCD (40.8), changed little.
-static bool chromatic_small(const Geom& g) {
-  return (uint64_t)g.P * 12 < (1ull << 32) && g.H < (1u << 24) && g.W * 12ull < (1u << 24);
+// Images of two columns or more whose texels have 32-bit byte offsets, and row pitches and coordinates below 2^24: a texel's
+// address is one 24-bit multiply and an add on a base that stays in scalar registers, and a row's two texels of a tap, which
+// are neighbours, come with one 16-byte load (channel q of the left one in its first word, of the right one in its last).
+// The gather is bound by its requests and their cache lines: with a load per texel the scheduler drew a row's two loads
+// apart, and offsets without a common direction found the line gone at the second. 64-bit addresses and a load per texel,
+// 24-bit addresses, and with pairs, 1920x1080, smooth offsets and independent ones: 5 taps 37.5 and 87, 36.0 and 88, 30.1
+// and 68 us; 7 taps 54 and 107, 47 and 112, 38 and 76; 9 taps 71 and 152, 65 and 129, 56 and 105. (A band of the image per
+// XCD changed little.)
+// Three taps over a large three-channel accumulation wait on that accumulation: 3840x2160 147 us with 64-bit addresses, 153
+// with pairs. They keep the former.
+static bool chromatic_small(const Geom& g, uint32_t taps) {
+  if (taps == 3 && g.AW == 8 && g.P > (4u << 20)) return false;
+  return g.W >= 2 && (uint64_t)g.P * 12 < (1ull << 32) && g.H < (1u << 24) && g.W * 12ull < (1u << 24);
 }
+
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 // Tap i of k for one pixel: the bilinear sample of every channel with a non-zero spectral weight, accumulated
 // into num/den. The tap position is split into the pixel's integer coordinate and the offset's own integer and
@@ -237,25 +246,26 @@ __device__ __forceinline__ void chromatic_tap(const Geom& g, const float* __rest
   const coord_t Wm = (coord_t)g.W - 1, Hm = (coord_t)g.H - 1;
   const uint32_t x0 = (uint32_t)min(max(lx, (coord_t)0), Wm), x1 = (uint32_t)min(max(lx + 1, (coord_t)0), Wm);
   const uint32_t y0 = (uint32_t)min(max(ly, (coord_t)0), Hm), y1 = (uint32_t)min(max(ly + 1, (coord_t)0), Hm);
-  const float *a, *b, *c, *d;
-  if constexpr (SMALL) {
-    const uint32_t pitch = g.W * 12, r0 = __umul24(y0, pitch), r1 = __umul24(y1, pitch);
-    const uint32_t c0 = x0 * 12, c1 = x1 * 12;
-    const char* base = (const char*)bgimg;
-    a = (const float*)(base + (r0 + c0));
-    b = (const float*)(base + (r0 + c1));
-    c = (const float*)(base + (r1 + c0));
-    d = (const float*)(base + (r1 + c1));
-  } else {
-    a = bgimg + ((uint64_t)y0 * g.W + x0) * 3;
-    b = bgimg + ((uint64_t)y0 * g.W + x1) * 3;
-    c = bgimg + ((uint64_t)y1 * g.W + x0) * 3;
-    d = bgimg + ((uint64_t)y1 * g.W + x1) * 3;
-  }
+  const uint32_t xb = SMALL ? min(x0, (uint32_t)Wm - 1) : 0;  // a row's two texels are xb and xb + 1, or one of them
+  const char* base = (const char*)bgimg;
+  const uint32_t pitch = g.W * 12, at0 = __umul24(y0, pitch) + xb * 12, at1 = __umul24(y1, pitch) + xb * 12;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     if (w[q] == 0.f) continue;  // depends on the tap only (a constant when k is)
-    const float v = (1.f - fy) * ((1.f - fx) * a[q] + fx * b[q]) + fy * ((1.f - fx) * c[q] + fx * d[q]);
+    float ta, tb, tc, td;
+    if constexpr (SMALL) {
+      const f32x4_any r0 = *(const f32x4_any*)(base + (at0 + 4 * q)), r1 = *(const f32x4_any*)(base + (at1 + 4 * q));
+      ta = x0 == xb ? r0.x : r0.w;
+      tb = x1 == xb ? r0.x : r0.w;
+      tc = x0 == xb ? r1.x : r1.w;
+      td = x1 == xb ? r1.x : r1.w;
+    } else {
+      ta = bgimg[((uint64_t)y0 * g.W + x0) * 3 + q];
+      tb = bgimg[((uint64_t)y0 * g.W + x1) * 3 + q];
+      tc = bgimg[((uint64_t)y1 * g.W + x0) * 3 + q];
+      td = bgimg[((uint64_t)y1 * g.W + x1) * 3 + q];
+    }
+    const float v = (1.f - fy) * ((1.f - fx) * ta + fx * tb) + fy * ((1.f - fx) * tc + fx * td);
     num[q] += w[q] * v;
     den[q] += w[q];
   }
@@ -343,7 +353,7 @@ hipError_t launch_resolve_chromatic(const Geom& g, const float* accum, const flo
            : taps == 9 ? k_resolve_chromatic<9, S>
                        : k_resolve_chromatic<0, S>;
   };
-  auto k = chromatic_small(g) ? pick(std::true_type{}) : pick(std::false_type{});
+  auto k = chromatic_small(g, taps) ? pick(std::true_type{}) : pick(std::false_type{});
   hipLaunchKernelGGL(k, dim3(grid), dim3(256), 0, s, accum, g, bgimg, offset, dispersion, taps, out);
   return hipGetLastError();
 }
