@@ -329,8 +329,10 @@ hipError_t launch_evaluate(const Geom& g, const Binned& b, const void* coeffs, f
   const size_t lds = lds_eval_bytes(g);
   // M > 32: FP32 coefficients are half the LDS that the tile was sized for, and two workgroups share a compute unit where
   // registers allow it: at one channel of 1024 threads, at three of 512 (512x512 at 8 per pixel, rank 8: one channel 391 us
-  // with 512 threads and 354 with 1024, three channels 966 and 1417)
-  const uint32_t threads = g.M > 32 && g.C == 3 ? kTileThreads / 2 : g.tthreads;
+  // with 512 threads and 354 with 1024, three channels 966 and 1417), when there are tiles enough to share (5x30, rank 7,
+  // 885,000 fragments: 462 us with 512 threads, 380 with 1024). A single tile with all fragments of a large frame pays for
+  // it (300x200, rank 5, 300,000 fragments on 64 pixels: 1.52 ms with 512 threads, 1.03 with 1024, 2.75 with 256).
+  const uint32_t threads = g.M > 32 && g.C == 3 && g.ntiles > kComputeUnits ? kTileThreads / 2 : g.tthreads;
   return dispatch(g, [&](auto cc, auto* tag) {
     constexpr int C = decltype(cc)::value;
     using TS = std::remove_pointer_t<decltype(tag)>;
