@@ -1438,87 +1438,122 @@ __global__ __launch_bounds__(kSplitThreads) void k_split(Geom g, const uint32_t*
   }
 }
 
-// Small streams: the whole binning in one launch (after the header's reset), a workgroup per tile and part of the stream.
-// Each reads every pixel id, lists its part's fragments of its tile in LDS and counts those that come before them (of the
-// tiles below, and of the tile in earlier parts), which is where its records start, and writes them there, consecutive
-// lanes on consecutive records. The ids are read once per workgroup, from L2, which costs less than the count, scan,
-// scatter and seal one after the other (five launches that each wait for the one before) up to kSmallReads ids in all.
-// Parts bound what one compute unit moves (1.1 ns a record) when a tile holds most of the stream: with one part, 65,536
-// fragments of one tile took 78 us against 30 of the general way, with parts of kSmallPart 29; a list of 16-bit indices
-// takes kSmallStream fragments at most. 64x64 with 33,000 fragments: 29 -> 18 us a frame. (Binning alone, 256 tiles: 30,000
-// fragments in two parts, 15 M ids, 13 us against 24; 45,000 in three, 35 M, 21 and 23; 65,536 in four, 67 M, 34 and 23.)
+// Small streams: the whole binning in one launch (after the header's reset), P workgroups for every P tiles. Each reads every
+// pixel id, lists in LDS the fragments of its tiles that are in its part of the stream (one P-th) and counts those that come
+// before them (of the tiles below, and of its tiles in other parts), which is where its records start, and writes them
+// there, consecutive lanes on consecutive records. The ids are read once per tile, from L2, which costs less than the
+// count, scan, scatter and seal one after the other (five launches that each wait for the one before) up to kSmallReads ids
+// in all; lists of 16-bit indices take kSmallStream fragments at most. 64x64 with 33,000 fragments: 29 -> 18 us a frame.
+// Parts bound what one compute unit moves (1.1 ns a record) when a tile holds most of the stream, and cost compares when it
+// does not (binning alone, one channel; all fragments in one tile, or spread over 256; the general way 30 us and 28):
+// 32,768 fragments whole 41 us and 13.4, in two parts 26.5 and 13.4; 40,000 in two 31.7 and 13.7, in four 23.2 and 15.4;
+// 65,536 whole 78 and 16.7, in two 48 and 18.3, in four 34 and 21.
 constexpr uint32_t kSmallStream = 65536;
-constexpr uint32_t kSmallPart = 16384;
-constexpr uint64_t kSmallReads = 32u << 20;
+constexpr uint64_t kSmallReads = 16u << 20;
 
-static uint32_t small_parts(uint64_t F) { return (uint32_t)((F + kSmallPart - 1) / kSmallPart); }
+static uint32_t small_parts(uint64_t F) { return F <= 16384 ? 1 : F <= 40960 ? 2 : 4; }
+__host__ __device__ inline uint32_t small_quads(uint32_t F, uint32_t P) { return (F / 4 + P - 1) / P; }  // of a part
+// Entries of one tile's list: its part's whole groups of four, and the last part's rest.
+__host__ __device__ inline uint32_t small_list(uint32_t F, uint32_t P) { return 4 * small_quads(F, P) + 4; }
+static_assert(2 * (kSmallStream + 8 * 4) <= kLdsBytes - 1024, "the lists of all parts fit the LDS");
 
-template <int C, bool IDX>
-__global__ __launch_bounds__(1024) void k_bin_small(wt_fragments f, Geom g, int vec, uint32_t parts,
-                                                    uint32_t* __restrict__ offsets, uint32_t* __restrict__ order,
-                                                    uint32_t* __restrict__ head, uint32_t* __restrict__ tail,
-                                                    WsHeader* hdr, unsigned long long stamp, GradOut go) {
+template <int C, bool IDX, uint32_t P>
+__global__ __launch_bounds__(1024) void k_bin_small(wt_fragments f, Geom g, int vec, uint32_t* __restrict__ offsets,
+                                                    uint32_t* __restrict__ order, uint32_t* __restrict__ head,
+                                                    uint32_t* __restrict__ tail, WsHeader* hdr,
+                                                    unsigned long long stamp, GradOut go) {
   constexpr uint32_t DH = head_dwords(C), DT = tail_dwords(IDX);
-  extern __shared__ uint16_t list[];
-  __shared__ uint32_t mine, before, lost;
-  const uint32_t F = (uint32_t)f.count, me = blockIdx.x / parts, part = blockIdx.x - me * parts;
-  // its part of the stream, in groups of four ids
-  const uint32_t quads = vec ? F / 4 : 0;
-  const uint32_t lo = std::min(part * (kSmallPart / 4), quads), hi = std::min(lo + kSmallPart / 4, quads);
-  if (threadIdx.x == 0) mine = before = lost = 0;
+  extern __shared__ uint16_t list[];  // [P][small_list]
+  __shared__ uint32_t mine[P], earlier[P], later[P], before, lost;
+  const uint32_t F = (uint32_t)f.count, t0 = blockIdx.x / P * P, part = blockIdx.x - t0;
+  const uint32_t quads = vec ? F / 4 : 0, per = small_quads(F, P), stride = small_list(F, P);
+  const uint32_t lo = std::min(part * per, quads), hi = part == P - 1 ? quads : std::min(lo + per, quads);
+  if (threadIdx.x < P) mine[threadIdx.x] = earlier[threadIdx.x] = later[threadIdx.x] = 0;
+  if (threadIdx.x == 0) before = lost = 0;
   __syncthreads();
-  uint32_t below = 0, drops = 0;
-  // an id of its part: listed when it is in the tile; fragments in no tile are the first workgroups' to account for
+  uint32_t below = 0, drops = 0, early[P], late[P];
+#pragma unroll
+  for (uint32_t j = 0; j < P; ++j) early[j] = late[j] = 0;
+  // an id of its part: listed when it is in one of its tiles; fragments in no tile are the first workgroups' to account for
   auto take = [&](uint32_t i, uint32_t p) {
     if (p >= g.P) {
-      if (me == 0) {
+      if (t0 == 0) {
         ++drops;
         if constexpr (IDX) zero_gradient<C>(go, i);
       }
       return;
     }
     const uint32_t t = tile_of(g, p);
-    if (t < me) ++below;
-    if (t == me) list[atomicAdd(&mine, 1u)] = (uint16_t)i;
+    if (t < t0) ++below;
+#pragma unroll
+    for (uint32_t j = 0; j < P; ++j)
+      if (t == t0 + j) list[j * stride + atomicAdd(&mine[j], 1u)] = (uint16_t)i;
   };
-  // ids [q0, q1) of the other parts: those below tile `top` come before its records
-  auto pass = [&](uint32_t q0, uint32_t q1, uint32_t top) {
+  // an id of another part
+  auto count = [&](uint32_t p, uint32_t (&of)[P]) {
+    if (p >= g.P) return;
+    const uint32_t t = tile_of(g, p);
+    below += t < t0 ? 1u : 0u;
+#pragma unroll
+    for (uint32_t j = 0; j < P; ++j) of[j] += t == t0 + j ? 1u : 0u;
+  };
+  // groups of four ids [q0, q1), two in flight
+  auto each = [&](uint32_t q0, uint32_t q1, auto&& fn) {
     for (uint32_t q = q0 + threadIdx.x; q < q1; q += 2048) {
       const bool two = q + 1024 < q1;
       const uint4 a = ((const uint4*)f.pixel)[q], b = ((const uint4*)f.pixel)[two ? q + 1024 : q];
-      const uint32_t p[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+      const uint32_t pa[4] = {a.x, a.y, a.z, a.w}, pb[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
-      for (uint32_t k = 0; k < 8; ++k)
-        if ((k < 4 || two) && p[k] < g.P) below += tile_of(g, p[k]) < top ? 1u : 0u;
+      for (uint32_t k = 0; k < 4; ++k) fn(4 * q + k, pa[k]);
+      if (two) {
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) fn(4 * (q + 1024) + k, pb[k]);
+      }
     }
   };
-  pass(0, lo, me + 1);
-  for (uint32_t q0 = lo + threadIdx.x; q0 < hi; q0 += 2048) {
-    const bool two = q0 + 1024 < hi;
-    const uint4 a = ((const uint4*)f.pixel)[q0], b = ((const uint4*)f.pixel)[two ? q0 + 1024 : q0];
-    const uint32_t pa[4] = {a.x, a.y, a.z, a.w}, pb[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-    for (uint32_t k = 0; k < 4; ++k) take(4 * q0 + k, pa[k]);
-    if (two) {
-#pragma unroll
-      for (uint32_t k = 0; k < 4; ++k) take(4 * (q0 + 1024) + k, pb[k]);
-    }
-  }
-  pass(hi, quads, me);
-  // (an unaligned stream, or the last ids)
-  for (uint32_t i = 4 * quads + threadIdx.x; i < F; i += 1024) {
-    const uint32_t at = i / kSmallPart;
+  if constexpr (P > 1) each(0, lo, [&](uint32_t, uint32_t p) { count(p, early); });
+  each(lo, hi, take);
+  if constexpr (P > 1) each(hi, quads, [&](uint32_t, uint32_t p) { count(p, late); });
+  for (uint32_t i = 4 * quads + threadIdx.x; i < F; i += 1024) {  // an unaligned stream, or the last ids
+    const uint32_t at = P == 1 ? 0u : std::min(i / (4 * per), P - 1), p = f.pixel[i];
     if (at == part)
-      take(i, f.pixel[i]);
-    else if (f.pixel[i] < g.P)
-      below += tile_of(g, f.pixel[i]) < me + (at < part ? 1u : 0u) ? 1u : 0u;
+      take(i, p);
+    else if (at < part)
+      count(p, early);
+    else
+      count(p, late);
   }
   below = wave_sum(below);
   if ((threadIdx.x & 63) == 0 && below) atomicAdd(&before, below);
+  if constexpr (P > 1) {
+#pragma unroll
+    for (uint32_t j = 0; j < P; ++j) {
+      const uint32_t e = wave_sum(early[j]), l = wave_sum(late[j]);
+      if ((threadIdx.x & 63) == 0 && e) atomicAdd(&earlier[j], e);
+      if ((threadIdx.x & 63) == 0 && l) atomicAdd(&later[j], l);
+    }
+  }
   __syncthreads();
-  const uint32_t base = before, n = mine;
-  for (uint32_t k = threadIdx.x; k < n; k += 1024) {
-    const uint32_t i = list[k];
+  // its records of tile t0 + j are number[j] .. number[j + 1] - 1 of the lists and start at base[j]; the tile starts at first[j]
+  uint32_t number[P + 1], base[P], first[P + 1];
+  number[0] = 0;
+  first[0] = before;
+#pragma unroll
+  for (uint32_t j = 0; j < P; ++j) {
+    base[j] = first[j] + earlier[j];
+    first[j + 1] = base[j] + mine[j] + later[j];
+    number[j + 1] = number[j] + mine[j];
+  }
+  for (uint32_t k = threadIdx.x; k < number[P]; k += 1024) {
+    uint32_t at = k, slot = base[0] + k;  // its entry, its record
+#pragma unroll
+    for (uint32_t j = 1; j < P; ++j) {
+      if (k >= number[j]) {
+        at = j * stride + (k - number[j]);
+        slot = base[j] + (k - number[j]);
+      }
+    }
+    const uint32_t i = list[at];
     uint32_t w[DH + DT], tile;
     tile_locate(g, f.pixel[i], tile, w[0]);
     w[1] = __float_as_uint(f.depth[i]);
@@ -1540,26 +1575,30 @@ __global__ __launch_bounds__(1024) void k_bin_small(wt_fragments f, Geom g, int 
     Words<DT> t;
 #pragma unroll
     for (uint32_t j = 0; j < DT; ++j) t.w[j] = w[DH + j];
-    *(Words<DH>*)(head + (uint64_t)(base + k) * DH) = h;
-    *(Words<DT>*)(tail + (uint64_t)(base + k) * DT) = t;
+    *(Words<DH>*)(head + (uint64_t)slot * DH) = h;
+    *(Words<DT>*)(tail + (uint64_t)slot * DT) = t;
   }
   drops = wave_sum(drops);
   if ((threadIdx.x & 63) == 0 && drops) atomicAdd(&lost, drops);
-  // all of the tile's records are in its first class
-  if (part == 0 && threadIdx.x == 0) offsets[me * g.NX] = base;
-  if (part == parts - 1 && threadIdx.x < g.NX && (threadIdx.x || me == g.ntiles - 1))
-    offsets[(threadIdx.x ? me : g.ntiles) * g.NX + threadIdx.x] = base + n;
+  if (part == 0) {
+    // all of a tile's records are in its first class
+#pragma unroll
+    for (uint32_t j = 0; j < P; ++j) {
+      if (t0 + j >= g.ntiles) break;
+      if (threadIdx.x < g.NX) offsets[(t0 + j) * g.NX + threadIdx.x] = threadIdx.x ? first[j + 1] : first[j];
+      if (threadIdx.x == 0) order[t0 + j] = t0 + j;
+      if (threadIdx.x == 0 && t0 + j == g.ntiles - 1) offsets[g.ntiles * g.NX] = first[j + 1];
+    }
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
     if (lost) atomicAdd(&hdr->dropped, (unsigned long long)lost);
-    if (part) return;
-    order[me] = me;
-    if (me == 0) hdr->binned = stamp;
+    if (blockIdx.x == 0) hdr->binned = stamp;
   }
 }
 
 static bool small_stream(const Geom& g, uint64_t F) {
-  return F > 0 && F <= kSmallStream && F * small_parts(F) * g.ntiles <= kSmallReads && g.lds_bins && !g.two && !g.serial;
+  return F > 0 && F <= kSmallStream && F * g.ntiles <= kSmallReads && g.lds_bins && !g.two && !g.serial;
 }
 
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
@@ -1787,11 +1826,21 @@ hipError_t launch_bin(const Geom& g, const wt_fragments& f, void* ws, const Layo
     char* b = (char*)ws;
     WsHeader* hdr = (WsHeader*)(b + l.header);
     hipLaunchKernelGGL(k_count_reset, dim3(1), dim3(256), 0, s, hdr, nullptr, (uint64_t)0);
-    auto k = g.C == 1 ? (go.on ? k_bin_small<1, true> : k_bin_small<1, false>)
-                      : (go.on ? k_bin_small<3, true> : k_bin_small<3, false>);
-    const uint32_t parts = small_parts(f.count);
-    const size_t lds = (2 * std::min<uint64_t>(f.count, kSmallPart) + 3) & ~(size_t)3;
-    hipLaunchKernelGGL(k, dim3(g.ntiles * parts), dim3(1024), lds, s, f, g, aligned16(f.pixel) ? 1 : 0, parts,
+    const uint32_t P = small_parts(f.count);
+    auto form = [&](auto parts) {
+      constexpr uint32_t N = decltype(parts)::value;
+      return g.C == 1 ? (go.on ? k_bin_small<1, true, N> : k_bin_small<1, false, N>)
+                      : (go.on ? k_bin_small<3, true, N> : k_bin_small<3, false, N>);
+    };
+    auto k = P == 1   ? form(std::integral_constant<uint32_t, 1>{})
+             : P == 2 ? form(std::integral_constant<uint32_t, 2>{})
+                      : form(std::integral_constant<uint32_t, 4>{});
+    const size_t lds = (2ull * P * small_list((uint32_t)f.count, P) + 3) & ~(size_t)3;
+    if (lds > 65536 - 1024) {
+      hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k, dim3((g.ntiles + P - 1) / P * P), dim3(1024), lds, s, f, g, aligned16(f.pixel) ? 1 : 0,
                        (uint32_t*)(b + l.offsets), (uint32_t*)(b + l.order), (uint32_t*)(b + l.heads),
                        (uint32_t*)(b + l.tails), hdr, layout_stamp(g, l, go.on), go);
     return hipGetLastError();
