@@ -1444,14 +1444,15 @@ __global__ __launch_bounds__(kSplitThreads) void k_split(Geom g, const uint32_t*
 // there, consecutive lanes on consecutive records. The ids are read once per tile, from L2, which costs less than the
 // count, scan, scatter and seal one after the other (five launches that each wait for the one before) up to kSmallReads ids
 // in all; lists of 16-bit indices take kSmallStream fragments at most. 64x64 with 33,000 fragments: 29 -> 18 us a frame.
-// Parts bound what one compute unit moves (1.1 ns a record) when a tile holds most of the stream, and cost compares when it
-// does not (binning alone, one channel; all fragments in one tile, or spread over 256; the general way 30 us and 28):
-// 32,768 fragments whole 41 us and 13.4, in two parts 26.5 and 13.4; 40,000 in two 31.7 and 13.7, in four 23.2 and 15.4;
-// 65,536 whole 78 and 16.7, in two 48 and 18.3, in four 34 and 21.
+// Parts bound what one compute unit moves (1.1 ns a record) when a tile holds most of the stream, and cost reductions and
+// compares when it does not (binning alone, one channel; all fragments in one tile, or spread over 256; the general way 30
+// us and 28): 24,000 fragments whole 32 us and 13.3, in two parts 21 and 13; 32,768 whole 41 and 13.4, in two 26.5 and 13.4
+// (64x64 frame 18.9 whole, 19.8); 40,000 whole 50 and 13.4, in two 31.7 and 13.7, in four 23.2 and 15.4; 65,536 whole 78
+// and 16.7, in two 48 and 18.3, in four 34 and 21.
 constexpr uint32_t kSmallStream = 65536;
 constexpr uint64_t kSmallReads = 16u << 20;
 
-static uint32_t small_parts(uint64_t F) { return F <= 16384 ? 1 : F <= 40960 ? 2 : 4; }
+static uint32_t small_parts(uint64_t F) { return F <= 32768 ? 1 : F <= 40960 ? 2 : 4; }
 __host__ __device__ inline uint32_t small_quads(uint32_t F, uint32_t P) { return (F / 4 + P - 1) / P; }  // of a part
 // Entries of one tile's list: its part's whole groups of four, and the last part's rest.
 __host__ __device__ inline uint32_t small_list(uint32_t F, uint32_t P) { return 4 * small_quads(F, P) + 4; }
