@@ -2,6 +2,7 @@
 // argument; prints "bad 0" when it holds.
 #include <chrono>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <vector>
 
@@ -179,8 +180,17 @@ static void shapes() {
   expect(bounded < 0.5 * all, "time of the search", {0, 0, 3, 1, WT_F32, 0}, false);
 }
 
+// describe <width> <height> <rank> <channels> <flags> <gradient>: the frame's tiles and its binning levels.
+static int describe(char** a) {
+  auto n = [&](int i) { return (uint32_t)strtoul(a[i], nullptr, 10); };
+  const wt::Geom g = wt::make_geom(wt_frame_desc{n(0), n(1), n(2), n(3), WT_F32, n(4)}, n(5) != 0);
+  printf("tiles %u levels %u\nbad 0\n", g.ntiles, g.two ? 2u : g.lds_bins ? 1u : 0u);
+  return 0;
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
+  if (!strcmp(what, "describe") && argc == 8) return describe(argv + 2);
   if (!strcmp(what, "last_tile")) last_tile();
   else if (!strcmp(what, "limits")) limits();
   else if (!strcmp(what, "scratch")) scratch();

@@ -23,8 +23,8 @@ def check(tmp_path_factory):
                            os.path.join(ROOT, "tests", "host", "geom_check.cpp"), "-o", str(exe)],
                           stderr=subprocess.DEVNULL)
 
-    def run(name):
-        res = subprocess.run([str(exe), name], capture_output=True, text=True, timeout=300)
+    def run(name, *args):
+        res = subprocess.run([str(exe), name, *(str(a) for a in args)], capture_output=True, text=True, timeout=300)
         assert res.returncode == 0 and "bad 0" in res.stdout, res.stdout
         return res.stdout
     return run
@@ -57,3 +57,15 @@ def test_scratch_takes_what_the_largest_tiles_take(check):
 def test_tile_shape_search(check):
     """Every call makes its geometry anew, so the search of the tile shape is bounded; it finds what the full one finds."""
     check("shapes")
+
+
+def test_frames_of_the_gpu_tests(check):
+    """The binning levels and tiles that the GPU tests of them rely on: (width, height, rank, channels, flags, gradient)."""
+    for frame in [(2700, 1800, 4, 1, 0, 0), (1, 600000, 3, 1, 0, 0), (3, 300000, 3, 3, 0, 0), (640, 640, 8, 1, 4, 0),
+                  (3, 300000, 3, 3, 4, 0), (2600, 1400, 3, 3, 0, 0), (398, 38445, 6, 3, 0, 0), (1700, 1401, 3, 3, 0, 1),
+                  (2203, 1703, 4, 1, 0, 1), (2100, 1701, 3, 3, 0, 0), (1601, 1203, 4, 3, 1, 0), (2000, 1100, 4, 3, 0, 0)]:
+        assert "levels 2" in check("describe", *frame), frame
+    for frame, tiles in [((896, 1024, 5, 1, 0, 0), 3584), ((240, 3824, 5, 1, 0, 0), 3585), ((448, 512, 5, 3, 0, 0), 3584),
+                         ((120, 1912, 5, 3, 0, 0), 3585), ((896, 512, 5, 1, 0, 1), 3584), ((240, 1912, 5, 1, 0, 1), 3585),
+                         ((448, 512, 5, 3, 0, 1), 3584), ((120, 1912, 5, 3, 0, 1), 3585)]:
+        assert "tiles %d levels 1" % tiles in check("describe", *frame), frame
