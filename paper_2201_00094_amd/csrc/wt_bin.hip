@@ -63,6 +63,12 @@ static uint32_t tile_px_bytes(const Geom& g, bool backward) {
                    : 8 * (g.C * g.M + g.AL)) + (g.tight ? 8 : 0);
 }
 
+// The multiplier of row_tile for tiles TH rows high, or 0 where its conditions do not hold.
+static uint32_t row_multiplier(uint32_t H, uint32_t TH) {
+  const uint32_t m = ((1u << 20) + TH - 1) / TH;
+  return H <= (1u << 14) && TH <= 64 && (uint64_t)(H - 1) * m >> 32 == 0 ? m : 0;
+}
+
 static uint32_t log2_floor(uint32_t v) { return 31 - __builtin_clz(v); }
 
 // Tile of a frame, from the LDS bytes per pixel: TW a power of two, TH any height in [TW/2, 2 TW), and the workgroup size
@@ -112,7 +118,7 @@ static void pick_tile(Geom& g, uint32_t per_px) {
   }
   g.TW = 1u << g.lTW;
   g.divTH = make_fastdiv(g.TH);
-  g.mulTH = g.H <= (1u << 14) && g.TH >= 4 ? ((1u << 20) + g.TH - 1) / g.TH : 0;
+  g.mulTH = row_multiplier(g.H, g.TH);
   g.tile_px = g.TW * g.TH;
   g.tilesX = (g.W - 1) / g.TW + 1;
   g.tilesY = (g.H - 1) / g.TH + 1;
@@ -195,7 +201,7 @@ Geom super_geom(const Geom& g) {
   s.TW = 1u << s.lTW;
   s.TH = g.TH * g.SH;
   s.divTH = make_fastdiv(s.TH);
-  s.mulTH = g.H <= (1u << 14) && s.TH <= 64 ? ((1u << 20) + s.TH - 1) / s.TH : 0;
+  s.mulTH = row_multiplier(s.H, s.TH);
   s.tile_px = s.TW * s.TH;
   s.tilesX = g.sX;
   s.tilesY = g.sY;

@@ -114,7 +114,8 @@ __device__ __forceinline__ bool serial_records(const Geom& g, uint32_t beg, uint
 }
 
 // Tile row of frame row y. Rows below 2^14 and heights up to 64 take one 24-bit multiply: with m = ceil(2^20 / TH) the
-// excess y (m TH - 2^20) stays below 2^20, so the shifted product is the quotient, and y m stays below 2^32 for TH >= 4.
+// excess y (m TH - 2^20) stays below 2^20, so the shifted product is the quotient, as long as y m stays below 2^32 (from
+// four rows on it does for every such y; row_multiplier checks it for the frame's height).
 // (A shift would need power-of-two heights; the general quotient cost the smoke frame's count 12 of 94 us.)
 __device__ __forceinline__ uint32_t row_tile(const Geom& g, uint32_t y) {
   return g.mulTH ? __umul24(y, g.mulTH) >> 20 : fastdiv(y, g.divTH);

@@ -180,6 +180,26 @@ static void shapes() {
   expect(bounded < 0.5 * all, "time of the search", {0, 0, 3, 1, WT_F32, 0}, false);
 }
 
+// Row numbers by one 24-bit multiply, for tiles and super-tiles of every height that frames of up to 2^14 rows get.
+static void rows() {
+  for (uint32_t h : {1u, 2u, 100u, 4095u, 4096u, 4097u, 8192u, 8193u, 12288u, 16383u, 16384u, 16385u})
+    for (uint32_t w : {1u, 3u, 16u, 160u, 500u, 4000u})
+      each_form(w, h, [&](const wt_frame_desc& d, bool bwd) {
+        wt::Geom gs[2] = {wt::make_geom(d, bwd)};
+        gs[1] = wt::super_geom(gs[0]);
+        for (const wt::Geom& g : gs)
+          if (g.mulTH)
+            for (uint32_t y = 0; y < h; ++y) {
+              const uint32_t p = (y & 0xffffff) * (g.mulTH & 0xffffff);
+              if (p >> 20 != y / g.TH) {
+                expect(false, "row of a tile", d, bwd);
+                break;
+              }
+            }
+        expect(h > 16384 || gs[0].mulTH || gs[0].TH < 4, "one multiply for the usual frames", d, bwd);
+      });
+}
+
 // describe <width> <height> <rank> <channels> <flags> <gradient>: the frame's tiles and its binning levels.
 static int describe(char** a) {
   auto n = [&](int i) { return (uint32_t)strtoul(a[i], nullptr, 10); };
@@ -195,6 +215,7 @@ int main(int argc, char** argv) {
   else if (!strcmp(what, "limits")) limits();
   else if (!strcmp(what, "scratch")) scratch();
   else if (!strcmp(what, "shapes")) shapes();
+  else if (!strcmp(what, "rows")) rows();
   else return 2;
   printf("bad %d\n", bad);
   return bad != 0;

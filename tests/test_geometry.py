@@ -69,3 +69,7 @@ def test_frames_of_the_gpu_tests(check):
                          ((120, 1912, 5, 3, 0, 0), 3585), ((896, 512, 5, 1, 0, 1), 3584), ((240, 1912, 5, 1, 0, 1), 3585),
                          ((448, 512, 5, 3, 0, 1), 3584), ((120, 1912, 5, 3, 0, 1), 3585)]:
         assert "tiles %d levels 1" % tiles in check("describe", *frame), frame
+
+
+def test_rows_of_tiles(check):
+    check("rows")
