@@ -51,7 +51,7 @@
 #include <hip/hip_runtime_api.h>
 
 /* Largest fragment count a call takes: 2^32 - 2^20. Binned records are addressed by 32-bit indices, and a kernel's
- * loop over a tile's records may step up to 8,192 records past its last one before it stops, so counts stop well
+ * loop over a tile's records may step up to 16,384 records past its last one before it stops, so counts stop well
  * short of 2^32 (larger counts are refused with WT_ERR_RANGE, and wt_workspace_bytes returns 0 for them). */
 #define WT_MAX_FRAGMENTS 4293918720ull
 

@@ -179,17 +179,16 @@ Geom make_geom(const wt_frame_desc& d, bool backward) {
   g.sY = (g.tilesY - 1) / g.SH + 1;
   g.nsuper = g.sX * g.sY;
   g.NX = g.lds_bins ? kClasses : 1;
-  // Scatter chunks (powers of two): 4096 fragments where a 1024-record round and the tile tables (of the binning level
-  // that scatters) fit half the LDS and a chunk still holds more than one record per bin, else 8192. k_scatter_stream
-  // takes the former (see stream_scatter); what it leaves of three channels, k_scatter_staged takes in two workgroups of
-  // 512 threads per compute unit, so that one loads while the other ranks, stages and writes (glass 3840x2160, scatter
-  // phases: 7.86 ms with one workgroup of 1024 threads, 7.22 with two).
+  // Scatter chunks (powers of two): 4096 fragments up to kShortBins bins (of the binning level that scatters), where a chunk
+  // still holds more than one record per bin, else 8192. k_scatter_stream takes the former (see stream_scatter); what it
+  // leaves of three channels, k_scatter_staged takes in two workgroups of 512 threads per compute unit, so that one loads
+  // while the other ranks, stages and writes (glass 3840x2160, scatter phases: 7.86 ms with one workgroup of 1024 threads,
+  // 7.22 with two); a round of 1024 records of at most 40 bytes and the tables of kShortBins bins fit half the LDS.
   // (One channel, 50 M fragments, 4096 against 8192: 2,280 bins 0.678 ms and 0.718; 3,000 bins 0.692 and 0.725; at 4,080
-  // the longer chunk is faster, smoke frame 2.07 ms and 2.10. A one-channel record stages in at most 32 bytes, index or
-  // not, a three-channel one in at most 40: 1024 of them take 32 or 40 KB.)
+  // the longer chunk is faster, smoke frame 2.07 ms and 2.10.)
   const uint32_t bins = g.two ? g.nsuper : g.rb;
-  const bool short_chunk = g.lds_bins && bins <= kTwoWgBins &&
-                           8ull * bins + 1024ull * (g.C == 1 ? 32 : 40) <= kLdsBytes / 2 - 1024;
+  static_assert(8 * kShortBins + 1024 * 40 <= kLdsBytes / 2 - 1024, "a round and the tables fit half the LDS");
+  const bool short_chunk = g.lds_bins && bins <= kShortBins;
   g.sthreads = short_chunk && g.C == 3 ? 512 : 1024;
   g.chunk = short_chunk ? 4096 : 1024 * kPer;
   return g;
@@ -411,9 +410,12 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Streaming 16-byte loads (non-temporal: each fragment is read once), defined with the scatter below.
-template <bool NT>
-__device__ __forceinline__ uint4 load_stream_u4(const uint32_t* p);
+// Sixteen bytes of the stream, non-temporal (the histogram reads each pixel id once).
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint4 load_stream_u4(const uint32_t* p) {
+  const u32x4_t v = __builtin_nontemporal_load((const u32x4_t*)p);
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
 
 // ------------------------------------------------------------------------------------------------ histogram
 
@@ -448,7 +450,7 @@ __global__ __launch_bounds__(kHistThreads) void k_hist_lds(const uint32_t* __res
     for (int v = 0; v < 4; ++v) {
       const uint32_t u = u0 + v * kHistThreads + threadIdx.x;
       const uint32_t c = blockIdx.x + (u >> lnv) * gridDim.x;
-      q[v] = u < units ? load_stream_u4<true>(pixel + (uint64_t)c * g.chunk + 4 * (u & (nv - 1)))
+      q[v] = u < units ? load_stream_u4(pixel + (uint64_t)c * g.chunk + 4 * (u & (nv - 1)))
                        : make_uint4(0u, 0u, 0u, 0u);
     }
 #pragma unroll
@@ -718,67 +720,42 @@ __global__ __launch_bounds__(256) void k_super_counts(const uint32_t* __restrict
 
 // ------------------------------------------------------------------------------------------------ scatter
 
-
-// The fragment stream is read once. With two scatter workgroups per compute unit (PER = 4), non-temporal loads
-// keep it from evicting the partly written record lines that the L2 is completing (measured on the smoke frame:
-// 17% less HBM write traffic, scatter 1.96 -> 1.68 ms); with one workgroup per compute unit (PER = 8) they
-// made the scatter slower (2.05 -> 2.41 ms), so there the loads stay ordinary.
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-template <bool NT>
-__device__ __forceinline__ uint4 load_stream_u4(const uint32_t* p) {
-  if constexpr (NT) {
-    const u32x4_t v = __builtin_nontemporal_load((const u32x4_t*)p);
-    return make_uint4(v.x, v.y, v.z, v.w);
-  } else {
-    return *(const uint4*)p;
-  }
-}
-template <bool NT>
-__device__ __forceinline__ float4 load_stream_f4(const float* p) {
-  if constexpr (NT) {
-    const u32x4_t v = __builtin_nontemporal_load((const u32x4_t*)p);
-    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
-  } else {
-    return *(const float4*)p;
-  }
-}
-
 // One chunk's fragments, held in registers by the thread that loaded them.
-template <int C, int PER>
+template <int C>
 struct ChunkRegs {
-  static_assert(PER % 4 == 0, "vector loads take fragments four at a time");
-  uint32_t p[PER];
-  float x[PER];
-  float a[C * PER];
-  float c[3 * PER];
+  static_assert(kPer % 4 == 0, "vector loads take fragments four at a time");
+  uint32_t p[kPer];
+  float x[kPer];
+  float a[C * kPer];
+  float c[3 * kPer];
 };
 
-// Loads fragments [i0, i0 + PER) of the chunk at base; out-of-range slots get pixel id 0xffffffff.
-template <int C, int PER>
+// Loads fragments [i0, i0 + kPer) of the chunk at base; out-of-range slots get pixel id 0xffffffff. (Ordinary loads: with
+// one workgroup of this kernel per compute unit non-temporal ones took the smoke frame's scatter from 2.05 to 2.41 ms.)
+template <int C>
 __device__ __forceinline__ void load_chunk(const wt_fragments& f, uint32_t base, uint32_t i0, uint32_t n, int vec,
-                                           ChunkRegs<C, PER>& r) {
-  constexpr uint32_t kPer = PER;
+                                           ChunkRegs<C>& r) {
   if (vec && i0 + kPer <= n) {
     // pixel ids first: the tile count needs only them, and the other loads stay in flight meanwhile
 #pragma unroll
     for (uint32_t v = 0; v < kPer / 4; ++v) {
-      const uint4 p4 = load_stream_u4<false>(f.pixel + (uint64_t)base + i0 + 4 * v);
+      const uint4 p4 = *(const uint4*)(f.pixel + (uint64_t)base + i0 + 4 * v);
       r.p[4 * v + 0] = p4.x; r.p[4 * v + 1] = p4.y; r.p[4 * v + 2] = p4.z; r.p[4 * v + 3] = p4.w;
     }
 #pragma unroll
     for (uint32_t v = 0; v < kPer / 4; ++v) {
       const uint64_t i = (uint64_t)base + i0 + 4 * v;
-      const float4 x4 = load_stream_f4<false>(f.depth + i);
+      const float4 x4 = *(const float4*)(f.depth + i);
       r.x[4 * v + 0] = x4.x; r.x[4 * v + 1] = x4.y; r.x[4 * v + 2] = x4.z; r.x[4 * v + 3] = x4.w;
 #pragma unroll
       for (int q = 0; q < C; ++q) {
-        const float4 a4 = load_stream_f4<false>(f.alpha + C * i + 4 * q);
+        const float4 a4 = *(const float4*)(f.alpha + C * i + 4 * q);
         r.a[4 * C * v + 4 * q + 0] = a4.x; r.a[4 * C * v + 4 * q + 1] = a4.y;
         r.a[4 * C * v + 4 * q + 2] = a4.z; r.a[4 * C * v + 4 * q + 3] = a4.w;
       }
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
-        const float4 c4 = load_stream_f4<false>(f.rgb + 3 * i + 4 * q);
+        const float4 c4 = *(const float4*)(f.rgb + 3 * i + 4 * q);
         r.c[12 * v + 4 * q + 0] = c4.x; r.c[12 * v + 4 * q + 1] = c4.y;
         r.c[12 * v + 4 * q + 2] = c4.z; r.c[12 * v + 4 * q + 3] = c4.w;
       }
@@ -801,8 +778,8 @@ __device__ __forceinline__ void load_chunk(const wt_fragments& f, uint32_t base,
   }
 }
 
-template <int C, int PER>
-__device__ __forceinline__ bool has_nan(const ChunkRegs<C, PER>& r, uint32_t k) {
+template <int C>
+__device__ __forceinline__ bool has_nan(const ChunkRegs<C>& r, uint32_t k) {
   bool bad = isnan(r.x[k]);
 #pragma unroll
   for (int q = 0; q < C; ++q) bad |= isnan(r.a[C * k + q]);
@@ -822,8 +799,8 @@ __device__ __forceinline__ void to_forward(uint32_t* a, uint32_t* c) {
 }
 
 // Record dword j of fragment k (tile-local pixel `local`, stream index `src`), with the fragment's own alpha and colour.
-template <int C, int PER>
-__device__ __forceinline__ uint32_t record_word(const ChunkRegs<C, PER>& r, uint32_t k, uint32_t local, uint32_t src,
+template <int C>
+__device__ __forceinline__ uint32_t record_word(const ChunkRegs<C>& r, uint32_t k, uint32_t local, uint32_t src,
                                                 uint32_t j) {
   if (j == 0) return local;
   if (j == 1) return __float_as_uint(r.x[k]);
@@ -865,7 +842,7 @@ __device__ __forceinline__ void block_scan_inplace(uint32_t* cnt, uint32_t nt, u
   }
 }
 
-// The same over 16-bit counts, returning the total to every thread and storing it behind the table. Ends with a barrier.
+// The same over 16-bit counts, returning the total to every thread. Ends with a barrier.
 template <int THREADS>
 __device__ __forceinline__ uint32_t block_scan_total(uint16_t* cnt, uint32_t nt, uint32_t* wsum) {
   constexpr uint32_t NW = THREADS / 64;
@@ -895,7 +872,6 @@ __device__ __forceinline__ uint32_t block_scan_total(uint16_t* cnt, uint32_t nt,
     cnt[t] = (uint16_t)run;
     run += v;
   }
-  if (threadIdx.x == 0) cnt[nt] = (uint16_t)total;
   __syncthreads();
   return total;
 }
@@ -949,12 +925,6 @@ __device__ __forceinline__ void lds_get(const uint32_t* d, uint32_t* w) {
   }
 }
 
-// LDS: srec[S][SH + ST] uint4 one round of sorted records (the slot word holds the tile until the write), cnt[nt]
-// (counts, then first staged positions), gb[nt] (reserved base - run start, per round). The chunk's sorted order is
-// written in
-// rounds of S records (S = stage, a power of two chosen by the host to fit the LDS).
-// PER = 4 is meant for two workgroups per compute unit (LDS <= 80 KB, <= 64 VGPRs at eight waves per SIMD):
-// one workgroup's loads and stores overlap the other's ranking and staging.
 // The gradient of a fragment that is in no tile (its pixel is out of range) is written where the binning leaves it out;
 // every other gradient is written by the tile kernel.
 template <int C>
@@ -972,6 +942,11 @@ __device__ __forceinline__ void scatter_refuse(WsHeader* hdr) {
   ws_raise(hdr, kWsErrScatter);
 }
 
+// LDS: sh[stage][HW] and st[stage][DT] one round of records in tile order (head words and the tile, tail words), cnt[ntiles]
+// (the chunk's counts, then first staged positions), gb[ntiles] (reserved base - run start, per round). The chunk's order is
+// written in rounds of `stage` records, a power of two chosen by the host to fit the LDS. With 512 threads (three channels)
+// two workgroups share a compute unit (LDS <= 80 KB, four waves per SIMD): one's loads and stores overlap the other's
+// ranking and staging.
 template <int C, bool IDX, int THREADS>
 __global__ __launch_bounds__(THREADS, THREADS == 512 ? 4 : 1) void k_scatter_staged(wt_fragments f, Geom g, int vec,
                                                                     uint32_t stage,
@@ -994,9 +969,9 @@ __global__ __launch_bounds__(THREADS, THREADS == 512 ? 4 : 1) void k_scatter_sta
   const uint32_t n = std::min<uint32_t>(g.chunk, F - base);
   for (uint32_t t = threadIdx.x; t < g.ntiles; t += blockDim.x) cnt[t] = 0;
   if (threadIdx.x == 0) nvalid = refused = 0;
-  ChunkRegs<C, kPer> r;
+  ChunkRegs<C> r;
   const uint32_t i0 = threadIdx.x * kPer;
-  load_chunk<C, kPer>(f, base, i0, n, vec, r);
+  load_chunk<C>(f, base, i0, n, vec, r);
   // only the stream the preceding count counted, under the same layout, is scattered into its segments (the
   // stamp is loaded behind the chunk, so the check adds no wait of its own)
   if (hdr->counted != cstamp) {
@@ -1012,7 +987,7 @@ __global__ __launch_bounds__(THREADS, THREADS == 512 ? 4 : 1) void k_scatter_sta
     if (r.p[k] < g.P) {
       tile_locate(g, r.p[k], tile[k], local[k]);
       rank[k] = atomicAdd(&cnt[tile[k]], 1u);
-      nan_count += has_nan<C, kPer>(r, k) ? 1u : 0u;
+      nan_count += has_nan<C>(r, k) ? 1u : 0u;
       ++mine;
     } else if constexpr (IDX) {
       if (i0 + k < n) zero_gradient<C>(go, (uint64_t)base + i0 + k);
@@ -1034,9 +1009,9 @@ __global__ __launch_bounds__(THREADS, THREADS == 512 ? 4 : 1) void k_scatter_sta
       if (sp[k] < r0 || sp[k] >= r0 + stage) continue;  // also skips invalid slots (0xffffffff)
       uint32_t hw[HW], tw[DT];
 #pragma unroll
-      for (uint32_t j = 0; j < HW; ++j) hw[j] = j < DH ? record_word<C, kPer>(r, k, local[k], base + i0 + k, j) : tile[k];
+      for (uint32_t j = 0; j < HW; ++j) hw[j] = j < DH ? record_word<C>(r, k, local[k], base + i0 + k, j) : tile[k];
 #pragma unroll
-      for (uint32_t j = 0; j < DT; ++j) tw[j] = record_word<C, kPer>(r, k, local[k], base + i0 + k, DH + j);
+      for (uint32_t j = 0; j < DT; ++j) tw[j] = record_word<C>(r, k, local[k], base + i0 + k, DH + j);
       lds_put<HW>(sh + (size_t)(sp[k] - r0) * HW, hw);
       lds_put<DT>(st + (size_t)(sp[k] - r0) * DT, tw);
     }
@@ -1118,8 +1093,8 @@ struct Quad {
 // chunk's loads counted apart from the stores (an unrolled write) gave 40 us on the glass frame and cost 8 on smoke.
 // Reservations awaited before the scan instead: 3% to 6% slower. Streams of at least four fragments.
 // Three channels stage a record in eight words (the tile above the pixel's 18 bits: a super-tile has at most 64 x 2048
-// pixels, and there are at most kTwoWgBins bins), and the counts are 16-bit (a chunk's), so that a chunk and the tables
-// of kTwoWgBins bins fit: glass 1366x768, 3,182 bins: 594 us staged in rounds, 542 here; 1024x768 at 27, 2,496 bins, 426
+// pixels, and there are at most kShortBins bins), and the counts are 16-bit (a chunk's), so that a chunk and the tables
+// of kShortBins bins fit: glass 1366x768, 3,182 bins: 594 us staged in rounds, 542 here; 1024x768 at 27, 2,496 bins, 426
 // and 388; 1920x1080 rank 2, 3,240 bins, 1.20 ms and 1.12. At few bins neither changes the time.
 template <int C, bool IDX, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_scatter_stream(wt_fragments f, Geom g, uint32_t nchunks,
@@ -1127,14 +1102,14 @@ __global__ __launch_bounds__(THREADS) void k_scatter_stream(wt_fragments f, Geom
                                                             uint32_t* __restrict__ tail, WsHeader* hdr,
                                                             unsigned long long cstamp, uint32_t cap, GradOut go) {
   constexpr uint32_t PER = 4, DH = head_dwords(C), DT = tail_dwords(IDX), HW = DH + 1, CH = THREADS * PER;
-  constexpr uint32_t R = THREADS == 1024 ? 4 : 1;  // tiles per thread at most (kTwoWgBins, 512)
+  constexpr uint32_t R = THREADS == 1024 ? 4 : 1;  // tiles per thread at most (kShortBins, 512)
   constexpr bool kPacked = C == 3;  // eight words: pixel | tile << 18, depth, absorbances, colour
   extern __shared__ uint4 sm4[];
-  const uint32_t half = (g.ntiles + 2) / 2;
+  const uint32_t half = (g.ntiles + 1) / 2;
   uint32_t* sh = (uint32_t*)sm4;  // [CH][HW]: head words, then the tile; [CH][8] packed
   uint32_t* st = sh + CH * HW;    // [CH][DT]: tail words
   uint32_t* gb = kPacked ? sh + CH * 8 : st + CH * DT;  // [ntiles]: reserved base - first staged position
-  uint32_t* cnt = gb + g.ntiles;  // [ntiles + 1] 16-bit counts, then first staged positions, the total last
+  uint32_t* cnt = gb + g.ntiles;  // [ntiles] 16-bit counts, then first staged positions
   uint32_t* cnt2 = cnt + half;    // the same of the next chunk
   __shared__ uint32_t wsum[THREADS / 64];
   __shared__ uint32_t refused;
@@ -1268,9 +1243,9 @@ __global__ __launch_bounds__(1024) void k_scatter_global(wt_fragments f, Geom g,
   const uint32_t F = (uint32_t)f.count;
   const uint32_t base = blockIdx.x * g.chunk;
   const uint32_t n = std::min<uint32_t>(g.chunk, F - base);
-  ChunkRegs<C, kPer> r;
+  ChunkRegs<C> r;
   const uint32_t i0 = threadIdx.x * kPer;
-  load_chunk<C, kPer>(f, base, i0, n, vec, r);
+  load_chunk<C>(f, base, i0, n, vec, r);
   uint32_t nan_count = 0;
 #pragma unroll
   for (uint32_t k = 0; k < kPer; ++k) {
@@ -1281,7 +1256,7 @@ __global__ __launch_bounds__(1024) void k_scatter_global(wt_fragments f, Geom g,
     }
     uint32_t tile, local;
     tile_locate(g, r.p[k], tile, local);
-    nan_count += has_nan<C, kPer>(r, k) ? 1u : 0u;
+    nan_count += has_nan<C>(r, k) ? 1u : 0u;
     const uint64_t pos = atomicAdd(&cursors[tile * kCursorPad], 1u);
     if (pos >= cap) {  // inside the record arrays whatever the cursors hold (the seal checks the segments)
       scatter_refuse(hdr);
@@ -1289,7 +1264,7 @@ __global__ __launch_bounds__(1024) void k_scatter_global(wt_fragments f, Geom g,
     }
     uint32_t w[DH + DT];
 #pragma unroll
-    for (uint32_t j = 0; j < DH + DT; ++j) w[j] = record_word<C, kPer>(r, k, local, base + i0 + k, j);
+    for (uint32_t j = 0; j < DH + DT; ++j) w[j] = record_word<C>(r, k, local, base + i0 + k, j);
     if constexpr (!IDX) to_forward<C>(w + 2, w + DH);
 #pragma unroll
     for (uint32_t j = 0; j < DH; ++j) head[pos * DH + j] = w[j];
@@ -1638,20 +1613,20 @@ static hipError_t launch_scatter_staged(const Geom& g, const wt_fragments& f, in
   return hipGetLastError();
 }
 
-// k_scatter_stream takes every stream in short chunks that has at least four fragments; the tables of kTwoWgBins bins fit
+// k_scatter_stream takes every stream in short chunks that has at least four fragments; the tables of kShortBins bins fit
 // beside a chunk. Three channels need six chunks for each compute unit to pay for themselves: k_scatter_staged has as many
 // lanes to stage with there (512x512 at 16 per pixel 75 us staged, 79 as a stream; at 32 per pixel 151 and 137). With
-// their indexes they do not fit. With more bins than kTwoWgBins runs are one record long and writing is what counts
+// their indexes they do not fit. With more bins than kShortBins runs are one record long and writing is what counts
 // (3,840 bins, 1920x1080 rank 4: 1.51 ms staged, 1.53 as a stream).
 static size_t stream_lds(uint32_t chunk, uint32_t C, bool idx, uint32_t bins) {
-  return (size_t)chunk * (C == 3 ? 32 : staged_record_bytes(C, idx)) + 4 * (bins + 2 * (size_t)((bins + 2) / 2));
+  return (size_t)chunk * (C == 3 ? 32 : staged_record_bytes(C, idx)) + 4 * (bins + 2 * (size_t)((bins + 1) / 2));
 }
 
 static bool stream_scatter(const Geom& g, uint64_t F, bool idx) {
   if (!g.lds_bins || F < 4 || g.chunk > 4096) return false;
   return g.C == 1 || (!idx && F >= 6ull * kComputeUnits * 4096);
 }
-static_assert(4096 * 32 + 4 * (kTwoWgBins + 2 * ((kTwoWgBins + 2) / 2)) <= kLdsBytes - 1024 && kTwoWgBins < 4096 &&
+static_assert(4096 * 32 + 4 * (kShortBins + 2 * ((kShortBins + 1) / 2)) <= kLdsBytes - 1024 && kShortBins < 4096 &&
                   kMaxSub * kMaxTilePx <= 1u << 18 && staged_record_bytes(1, true) <= 32,
               "a short chunk and the tables of its bins fit the LDS, and a packed word its tile and pixel");
 

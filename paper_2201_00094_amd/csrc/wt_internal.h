@@ -17,7 +17,7 @@ constexpr uint32_t kCursorPad = 1;  // words per write cursor in the workspace's
 constexpr uint32_t kPer = 8;               // fragments per scatter thread (held in registers)
 constexpr uint32_t kMaxLdsBins = 8192;     // bins one scatter table holds (super-tiles of a two-level binning)
 constexpr uint32_t kMaxHistBins = 36864;   // tiles one histogram table holds (144 KB of LDS)
-constexpr uint32_t kTwoWgBins = 3584;      // bins up to which two scatter workgroups share a compute unit
+constexpr uint32_t kShortBins = 3584;      // bins up to which scatter chunks are 4096 fragments
 // Frames with more tiles are binned in two levels (super-tiles, then tiles): past the tables of one level. Below, runs of
 // single records cost less than moving every record twice (scatter phases, one level against two: three channels,
 // 56 M fragments, 6,200 tiles 1.35 and 1.61 ms; one channel, 133 M, 8,160 tiles 2.72 and 2.93 ms).
@@ -140,7 +140,7 @@ struct Geom {
   uint32_t TW, TH;       // tile extent in pixels (TW a power of two)
   uint32_t lTW;          // log2 of TW
   FastDiv divW, divTH;   // division by W and by TH
-  uint32_t mulTH;        // ceil(2^20 / TH) where y / TH is (y mulTH) >> 20 for every row (row_tile), or 0
+  uint32_t mulTH;        // ceil(2^20 / TH) where y / TH is (y mulTH) >> 20 for every row y (row_tile), or 0
   uint32_t tilesX, tilesY, ntiles, tile_px;
   uint32_t NX;           // write-frontier classes (kClasses, or 1 when the tile count is large)
   uint32_t lds_bins;     // 1: LDS-staged scatter; 0: one global atomic per fragment
